@@ -219,7 +219,10 @@ typedef struct {
                             16/8-bit graphs only).  SNP (skyline) graphs only: 3 = per-row
                             kernel; 4 = band blocks on FMAs (bit-identical to 3); 5 = band
                             blocks on MFMAs (four columns summed per MFMA: equal to 3-4 up
-                            to FP32 rounding).  Plan 0 on SNP graphs times 4 and 5 once. */
+                            to FP32 rounding).  Plan 0 on SNP graphs without long-range pairs
+                            runs all steps in one launch with the state on chip where the graph
+                            fits (plan 4's results bit for bit; not on a stream being captured),
+                            and otherwise the faster of 4 and 5, which it times once. */
     int32_t replica_tile; /* dense graphs, per-step plan, R >= 64: replicas per workgroup
                             (16, 32 or 64); 0 = the autotuner's choice (plan 0) or 64.
                             Every tile gives bit-identical results. */
@@ -296,12 +299,14 @@ qh_status qh_bsb_solve(const qh_graph *g, const qh_bsb_opts *opts, qh_result *re
 
 /* Step-loop plan chosen for (graph, replicas) by earlier solves.  plan_used: 0 = no solve
  * yet, 1 = one fused kernel per step, 2 = persistent (all steps in one cooperative
- * launch, state in registers, J in LDS).  With opts.plan = 0 the first solve of a
+ * launch; dense graphs: state in registers, J in LDS; SNP graphs: x in LDS, y and J in
+ * registers).  With opts.plan = 0 the first solve of a
  * (graph, replicas) pair times the candidates on scratch state (64 steps each) and keeps
  * the fastest: the per-step kernel with 64 (two or four tiles in flight), 32 and 16
  * replicas per workgroup (dense graphs, R >= 64) and the persistent plan where it fits
  * (every candidate gives bit-identical results); us_per_step holds those
- * measurements (0 when not measured).  Host output.
+ * measurements (0 when not measured).  SNP graphs time the two band kernels over four steps.
+ * Host output.
  * The persistent plan synchronises neighbouring workgroups with agent-scope
  * release / acquire on per-workgroup step counters. */
 typedef struct {

@@ -1,0 +1,91 @@
+// Persistent band solve of SNP graphs (all steps in one cooperative launch): tables shared by
+// the host planner, the single-graph solve and the batched solve.
+#pragma once
+
+#include "internal.h"
+
+namespace qh {
+
+constexpr int kBpWaves = 8;                  // waves per workgroup (two per SIMD)
+constexpr int kBpThreads = 64 * kBpWaves;
+constexpr int kBpPadRows = 32;               // LDS rows past the last held row (read-ahead, never used)
+
+// One graph of a launch.
+struct BandTeam {
+    const int64_t *bb_off;
+    const int32_t *bb_lo, *bb_w;
+    const uint8_t *bb_val;
+    float *x, *y;               // [n][R] state, in and out
+    const float *field;         // deformation field h [n] (nullptr: none)
+    float c0, bscale;
+    int32_t n;
+};
+
+// One workgroup's share of one replica group of one graph.
+struct BandJob {
+    int32_t team;
+    int32_t r0;                 // first replica
+    int32_t blk0, nblk;         // band blocks [blk0, blk0 + nblk) of kBandRows rows
+    int32_t in_a, in_b;         // blocks blk0 + [in_a, in_b) read own rows only; the others need neighbours' rows
+    int32_t pub_a, pub_b;       // blocks blk0 + [0, pub_a) and blk0 + [pub_b, nblk) are read by neighbours
+    int32_t xlo, xhi;           // rows held in LDS: [xlo, xhi), own rows included
+    int32_t w, nbr0, nbr1;      // index in the team; neighbours [nbr0, nbr1] (inclusive, self among them)
+    int32_t t0;                 // earlier jobs of the same team flags (each counts one call's steps)
+    int32_t flag_off;           // team's flags: [workgroup][wave] step counters
+    int32_t xch_rows;           // rows of one half of the team's exchange buffer
+    int64_t xch_off;            // floats; two halves of [xch_rows][RT]
+};
+
+struct BandPersistArgs {
+    int32_t R, kb, ke;
+    float dt, a0;
+    const float *pump;
+    const BandTeam *teams;
+    const BandJob *jobs;
+    const int32_t *job_ptr;     // [grid + 1]
+    float *xch;
+    int *flags, *err;
+    int64_t max_polls;
+    // single-graph solves: this call's c0 and field in place of the team's (single = 1)
+    int32_t single;
+    float c0;
+    const float *field;
+};
+
+// Host description of a launch: the jobs of every workgroup.
+struct BandLaunch {
+    int rt = 0;                 // replicas per group (16 or 32)
+    int um = 0;                 // band blocks per wave (kernel variant: 1, 2, 4 or 8)
+    int grid = 0;
+    int dtype = 0;
+    int64_t lds_bytes = 0, xch_floats = 0, n_flags = 0;
+    std::vector<BandJob> jobs;  // in launch order of each workgroup (job_ptr)
+    std::vector<int32_t> job_ptr;
+};
+
+// Partition of one graph's band blocks over `wpg` workgroups.
+struct BandSplit {
+    int wpg = 0, max_blocks = 0;
+    int64_t lds_rows = 0;       // most rows a workgroup holds (without the read-ahead rows)
+    std::vector<BandJob> part;  // geometry fields of each workgroup's job
+};
+
+// Plan of one SNP graph and replica count (device tables built once).
+struct BandPersist {
+    bool ok = false;
+    BandLaunch launch;
+    int passes = 0;             // most jobs of one workgroup
+    DevBuf<BandTeam> team;
+    DevBuf<BandJob> jobs;
+    DevBuf<int32_t> job_ptr;
+    DevBuf<float> xch;
+    DevBuf<int> flags;          // n_flags counters, then the error word
+};
+
+BandSplit split_band(const int32_t *bb_lo, const int32_t *bb_w, int64_t n_bblk, int wpg);
+bool build_band_plan(const qh_graph *g, SolvePlan &p, BandPersist &bp, hipStream_t st);
+void launch_band(const BandLaunch &bl, const BandPersistArgs &a, int discrete, hipStream_t st);
+void launch_band_plain(const BandLaunch &bl, const BandPersistArgs &a, hipStream_t st);
+void launch_band_discrete(const BandLaunch &bl, const BandPersistArgs &a, hipStream_t st);
+
+}  // namespace qh

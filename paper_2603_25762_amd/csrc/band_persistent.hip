@@ -1,0 +1,183 @@
+// Persistent band solve of SNP graphs: planner and launch (the kernel is in
+// band_persistent_kernel.h; the discrete variant's instantiations in
+// band_persistent_discrete.hip, so that the two halves compile in parallel).
+#include <algorithm>
+
+#include "band_persistent_kernel.h"
+
+namespace qh {
+
+static constexpr int64_t kBpLdsLimit = 160 * 1024;
+
+// Contiguous parts of the band blocks, as even as possible, with the rows each part holds, the
+// blocks that reach past its own rows, the blocks its neighbours reach, and the neighbour range
+// (made symmetric: "reads from" and "is read by" together).
+BandSplit split_band(const int32_t *bb_lo, const int32_t *bb_w, int64_t n_bblk, int wpg) {
+    BandSplit s;
+    s.wpg = wpg;
+    s.part.resize(wpg);
+    std::vector<int32_t> owner(n_bblk);
+    for (int w = 0; w < wpg; ++w) {
+        const int32_t b0 = (int32_t)(n_bblk * w / wpg), b1 = (int32_t)(n_bblk * (w + 1) / wpg);
+        BandJob &J = s.part[w];
+        J = BandJob{};
+        J.w = w;
+        J.blk0 = b0;
+        J.nblk = b1 - b0;
+        s.max_blocks = std::max(s.max_blocks, b1 - b0);
+        const int32_t own_lo = b0 * kBandRows, own_hi = b1 * kBandRows;
+        J.xlo = own_lo;
+        J.xhi = own_hi;
+        J.in_a = 0;
+        J.in_b = J.nblk;
+        for (int32_t b = b0; b < b1; ++b) {
+            owner[b] = w;
+            const int32_t lo = bb_lo[b], hi = bb_lo[b] + bb_w[b];
+            J.xlo = std::min(J.xlo, lo);
+            J.xhi = std::max(J.xhi, hi);
+            if (lo < own_lo) J.in_a = b - b0 + 1;                      // last block that reaches below
+            if (hi > own_hi) J.in_b = std::min(J.in_b, b - b0);        // first block that reaches above
+        }
+        if (J.in_a >= J.in_b) J.in_a = J.in_b = 0;
+        s.lds_rows = std::max<int64_t>(s.lds_rows, J.xhi - J.xlo);
+    }
+    for (int w = 0; w < wpg; ++w) {
+        s.part[w].nbr0 = s.part[w].nbr1 = w;
+        s.part[w].pub_a = 0;
+        s.part[w].pub_b = s.part[w].nblk;
+    }
+    for (int w = 0; w < wpg; ++w) {
+        BandJob &J = s.part[w];
+        const int32_t o0 = owner[J.xlo / kBandRows], o1 = owner[(J.xhi - 1) / kBandRows];
+        J.nbr0 = std::min(J.nbr0, o0);
+        J.nbr1 = std::max(J.nbr1, o1);
+        for (int v = o0; v <= o1; ++v) {
+            if (v == w) continue;
+            BandJob &V = s.part[v];
+            V.nbr0 = std::min(V.nbr0, w);
+            V.nbr1 = std::max(V.nbr1, w);
+            // rows [xlo, own_lo) and [own_hi, xhi) of w lie in v: the top blocks of a lower
+            // neighbour from row xlo on, the bottom blocks of an upper one up to row xhi
+            if (v < w) V.pub_b = std::min(V.pub_b, std::max(0, J.xlo / kBandRows - V.blk0));
+            else V.pub_a = std::max(V.pub_a, std::min(V.nblk, (J.xhi - 1) / kBandRows + 1 - V.blk0));
+        }
+    }
+    return s;
+}
+
+// whole chunks of 16 columns that the kernel variant keeps in registers per block
+static int held_chunks(int dtype, int um) { return (dtype == QH_F32 ? 32 : 48) / um - 1; }
+
+static int units_variant(int64_t blocks) {
+    const int64_t u = ceil_div(blocks, kBpWaves);
+    return u <= 1 ? 1 : u <= 2 ? 2 : u <= 4 ? 4 : u <= 8 ? 8 : 0;
+}
+
+// Chooses replicas per group, workgroups per graph and the kernel variant for one graph by the
+// estimated time of a step, fitted to measured ones (f16, us per step, estimate / measured):
+// 0.9 for a step's barriers and latencies; per band block of a SIMD 0.0195 per MFMA and 0.12;
+// 1.8 for the exchange with neighbours; 0.25 per chunk of 16 columns read from memory; times
+// the passes that the replica groups take.  2,001 SNPs, R = 128: 3.1 / 3.4; 7,768 SNPs, F32,
+// 36 quads wide, R = 128: 5.7 / 5.8; 100,000 SNPs, R = 64: 12.4 / 12.4; 250,000: 27.7 / 28.7.
+// The per-step kernels take their state's traffic at 4.6 TB/s and a launch, or the latency of
+// walking the band (2,001 SNPs 8.8, 7,768 SNPs 17.2, 250,000 56.6 measured); the plan has to
+// beat that by a tenth.
+bool build_band_plan(const qh_graph *g, SolvePlan &p, BandPersist &bp, hipStream_t st) {
+    bp.ok = false;
+    const int R = p.R;
+    const int64_t nb = g->n_bblk;
+    if (g->storage != QH_STORE_SKYLINE || g->l_nnz > 0 || nb == 0 || g->n >= ((int64_t)1 << 26)) return false;
+    int n_cu = 0, coop = 0;
+    QH_HIP(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, g->device));
+    QH_HIP(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, g->device));
+    if (!coop || n_cu < 1) return false;
+    const std::vector<int32_t> lo = download(g->bb_lo.p, nb, st), wd = download(g->bb_w.p, nb, st);
+    double quads = 0.0;
+    for (int32_t w : wd) quads += ceil_div(w, 4);
+    quads /= (double)nb;
+    struct Cand { double us; int rt, wpg, um, slots, passes; };
+    std::vector<Cand> cands;
+    for (int rt : {32, 16}) {
+        if (R % rt) continue;
+        const int ng = R / rt;
+        for (int bpw = 1; bpw <= 8 * kBpWaves; ++bpw) {
+            const int wpg = (int)ceil_div(nb, bpw);
+            if (wpg > n_cu || (bpw > 1 && (int)ceil_div(nb, bpw - 1) == wpg)) continue;
+            const int um = units_variant(ceil_div(nb, wpg));
+            const int held = held_chunks(g->bb_dtype, um);
+            double past = 0.0;
+            for (int32_t w : wd) past += std::max(0, w / 16 - held);
+            const int slots = std::min(ng, n_cu / wpg), passes = (int)ceil_div(ng, slots);
+            const double units = std::max(1.0, (double)ceil_div(nb, wpg) / 4.0);      // per SIMD
+            const double us = 0.9 + units * (quads * (rt / 16) * 0.0195 + 0.12 + past / nb * 0.25) +
+                              (wpg > 1 ? 1.8 : 0.0);
+            cands.push_back({us * passes, rt, wpg, um, slots, passes});
+        }
+    }
+    std::sort(cands.begin(), cands.end(), [](const Cand &a, const Cand &b) { return a.us < b.us; });
+    const double step_us = std::max({4.0, 1.5 + 0.43 * quads, 3.0 + (double)g->n * R * 16.0 / 4.6e6});
+    for (const Cand &c : cands) {
+        if (c.us > 0.9 * step_us) break;
+        BandSplit s = split_band(lo.data(), wd.data(), nb, c.wpg);
+        const int64_t lds = (s.lds_rows + kBpPadRows) * c.rt * 4;
+        if (lds > kBpLdsLimit || units_variant(s.max_blocks) != c.um) continue;
+        BandLaunch &bl = bp.launch;
+        bl = BandLaunch{};
+        bl.rt = c.rt;
+        bl.um = c.um;
+        bl.grid = c.wpg * c.slots;
+        bl.dtype = g->bb_dtype;
+        bl.lds_bytes = lds;
+        const int64_t rows = nb * kBandRows;
+        bl.xch_floats = c.wpg > 1 ? (int64_t)c.slots * 2 * rows * c.rt : 0;
+        bl.n_flags = (int64_t)bl.grid * kBpWaves;
+        bl.job_ptr.push_back(0);
+        for (int sl = 0; sl < c.slots; ++sl)
+            for (int w = 0; w < c.wpg; ++w) {
+                for (int q = sl, k = 0; q < R / c.rt; q += c.slots, ++k) {
+                    BandJob J = s.part[w];
+                    J.team = 0;
+                    J.r0 = q * c.rt;
+                    J.t0 = k;
+                    J.flag_off = sl * c.wpg * kBpWaves;
+                    J.xch_rows = (int32_t)rows;
+                    J.xch_off = (int64_t)sl * 2 * rows * c.rt;
+                    bl.jobs.push_back(J);
+                }
+                bl.job_ptr.push_back((int32_t)bl.jobs.size());
+            }
+        BandTeam T{};
+        T.bb_off = g->bb_off.p;
+        T.bb_lo = g->bb_lo.p;
+        T.bb_w = g->bb_w.p;
+        T.bb_val = g->bb_val.p;
+        T.x = p.xa.p;
+        T.y = p.y.p;
+        T.bscale = g->bb_scale;
+        T.n = (int32_t)g->n;
+        bp.passes = c.passes;
+        bp.team.alloc(1);
+        bp.team.upload(&T, 1, st);
+        bp.jobs.alloc(bl.jobs.size());
+        bp.jobs.upload(bl.jobs.data(), bl.jobs.size(), st);
+        bp.job_ptr.alloc(bl.job_ptr.size());
+        bp.job_ptr.upload(bl.job_ptr.data(), bl.job_ptr.size(), st);
+        bp.xch.alloc((size_t)bl.xch_floats);
+        bp.flags.alloc((size_t)bl.n_flags + 64);
+        QH_HIP(hipStreamSynchronize(st));
+        bp.ok = true;
+        return true;
+    }
+    return false;
+}
+
+void launch_band_plain(const BandLaunch &bl, const BandPersistArgs &a, hipStream_t st) {
+    launch_band_disc<false>(bl, a, st);
+}
+
+void launch_band(const BandLaunch &bl, const BandPersistArgs &a, int discrete, hipStream_t st) {
+    if (discrete) launch_band_discrete(bl, a, st);
+    else launch_band_plain(bl, a, st);
+}
+
+}  // namespace qh

@@ -15,6 +15,7 @@
 #include <mutex>
 #include <type_traits>
 
+#include "band_persistent.h"
 #include "formats.h"
 #include "internal.h"
 #include "persistent.h"
@@ -1375,6 +1376,44 @@ static void run_persistent(const qh_graph *g, SolvePlan &p, const float *pump, d
     if (err) fail(QH_EHIP, "persistent bSB kernel: a neighbour wait exceeded its poll limit");
 }
 
+// Steps [kb, ke) of an SNP graph in one cooperative launch on the band plan; the state is in
+// p.xa / p.y before and after.
+static void run_band(SolvePlan &p, const float *pump, double c0, double dt, double a0, int kb, int ke, int discrete,
+                     const float *field, hipStream_t st) {
+    BandPersist &bp = *p.bp;
+    hipLaunchKernelGGL(k_zero_i32, dim3(grid_for((int64_t)bp.flags.n)), dim3(256), 0, st, (int64_t)bp.flags.n,
+                       bp.flags.p);
+    QH_CHECK_LAUNCH();
+    BandPersistArgs a{};
+    a.R = p.R;
+    a.kb = kb;
+    a.ke = ke;
+    a.dt = (float)dt;
+    a.a0 = (float)a0;
+    a.pump = pump;
+    a.teams = bp.team.p;
+    a.jobs = bp.jobs.p;
+    a.job_ptr = bp.job_ptr.p;
+    a.xch = bp.xch.p;
+    a.flags = bp.flags.p;
+    a.err = bp.flags.p + bp.launch.n_flags + 32;
+    a.max_polls = (int64_t)1 << 27;
+    a.single = 1;
+    a.c0 = (float)c0;
+    a.field = field;
+    launch_band(bp.launch, a, discrete, st);
+}
+
+// Whether work on st is being recorded into a graph (a cooperative launch cannot be).
+static bool stream_capturing(hipStream_t st) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return cs != hipStreamCaptureStatusNone;
+}
+
 // Autotuner for plan 0 on dense 16/8-bit graphs: time a short run of each candidate on
 // scratch state -- one fused kernel per step, and the persistent launch -- and keep the
 // faster.  Both compute bit-identical results, so the choice only affects speed.
@@ -1440,13 +1479,14 @@ static void autotune_dense(const qh_graph *g, SolvePlan &p, const qh_bsb_opts *o
     p.run_depth = p.tuned_depth;
 }
 
-// SNP graphs: time the two band kernels (64 steps each from a seeded state) and keep the
-// faster; the band FMA kernel needs 64-replica tiles.
+// SNP graphs: time the two band kernels (a warm step, then four steps each) and keep the faster;
+// the band FMA kernel needs 64-replica tiles.  The two differ by 1.6x (2,001 SNPs, R = 128) to
+// 3.2x (the Pore-C chromosome graph), so four steps tell them apart; 64 steps twice cost a
+// quarter of a 1,000-step chromosome job.  The state's values do not matter to the timing.
 static void autotune_sky(const qh_graph *g, SolvePlan &p, const qh_bsb_opts *o, const float *pump, double c0,
                          double a0, hipStream_t st) {
-    const int64_t n = g->n;
     const int R = p.R;
-    const int nt = std::min(o->steps, 64);
+    const int nt = std::min(o->steps, 4);
     std::vector<int> cands;
     if (R >= 64) cands.push_back(kSkyBandFma);
     cands.push_back(kSkyBandMfma);
@@ -1460,16 +1500,11 @@ static void autotune_sky(const qh_graph *g, SolvePlan &p, const qh_bsb_opts *o, 
     for (size_t i = 0; i < cands.size(); ++i) {
         p.sky_kernel = cands[i];
         float ms = 0.0f;
-        for (int rep = 0; rep < 2; ++rep) {   // the first repetition warms caches and code
-            hipLaunchKernelGGL(k_init, dim3(grid_for(n * R)), dim3(256), 0, st, (uint64_t)0x5eed, n, R, p.xa.p,
-                               p.y.p);
-            QH_CHECK_LAUNCH();
-            x_to_h(g, p, n, R, o->variant == 1, st);
-            QH_HIP(hipEventRecord(e0, st));
-            run_steps(g, p, o, pump, c0, a0, 0, nt, st);
-            QH_HIP(hipEventRecord(e1, st));
-            QH_HIP(hipEventSynchronize(e1));
-        }
+        run_steps(g, p, o, pump, c0, a0, 0, 1, st);   // warms caches and code
+        QH_HIP(hipEventRecord(e0, st));
+        run_steps(g, p, o, pump, c0, a0, 0, nt, st);
+        QH_HIP(hipEventRecord(e1, st));
+        QH_HIP(hipEventSynchronize(e1));
         QH_HIP(hipEventElapsedTime(&ms, e0, e1));
         p.sky_us[cands[i]] = ms * 1000.0f / nt;
         if (i == 0 || ms < best) {
@@ -1579,6 +1614,18 @@ void bsb_solve(const qh_graph *g, const qh_bsb_opts *o, qh_result *res, hipStrea
     int final_half = 0;
     bool persistent = false;
     const bool want_persistent = o->plan == 0 || o->plan == 2;
+    // SNP graphs under plan 0: every step in one launch with the state on chip, where the graph
+    // fits (the band kernels' results bit for bit); a stream being captured takes the per-step
+    // launches
+    bool band = false;
+    if (!dense && o->plan == 0 && ke > kb && n > 0 && !stream_capturing(st)) {
+        if (!p.bp_tried) {
+            p.bp = std::make_shared<BandPersist>();
+            build_band_plan(g, p, *p.bp, st);
+            p.bp_tried = true;
+        }
+        band = p.bp->ok && (int64_t)p.bp->passes * (ke - kb) < ((int64_t)1 << 30);
+    }
     if (dense && ke > kb && n > 0) {
         if (dense16 && want_persistent && !p.pp_tried) {
             p.pp = std::make_shared<PersistPlan>();
@@ -1609,7 +1656,7 @@ void bsb_solve(const qh_graph *g, const qh_bsb_opts *o, qh_result *res, hipStrea
         x_to_h(g, p, n, R, o->variant == 1, st);
     };
     load_state();
-    if (ke > kb && n > 0) p.last_plan = persistent ? 2 : 1;
+    if (ke > kb && n > 0) p.last_plan = persistent || band ? 2 : 1;
     const int coherent = o->persistent_sync == 2 || (o->persistent_sync == 0 && p.tuned_coh);
     if (persistent) p.last_coh = coherent;
     if (o->eval_every > 0) {
@@ -1625,6 +1672,7 @@ void bsb_solve(const qh_graph *g, const qh_bsb_opts *o, qh_result *res, hipStrea
             int fh = 0;
             if (k1 > k0 && n > 0) {
                 if (persistent) run_persistent(g, p, pump, c0, o->dt, a0, k0, k1, o->variant == 1, o->field, coherent, st);
+                else if (band) run_band(p, pump, c0, o->dt, a0, k0, k1, o->variant == 1, o->field, st);
                 else fh = run_steps(g, p, o, pump, c0, a0, k0, k1, st);
             }
             if (fh && !dense16 && nR)   // ping-pong paths: the range ended in the second half
@@ -1648,6 +1696,8 @@ void bsb_solve(const qh_graph *g, const qh_bsb_opts *o, qh_result *res, hipStrea
     }
     if (persistent) {
         run_persistent(g, p, pump, c0, o->dt, a0, kb, ke, o->variant == 1, o->field, coherent, st);
+    } else if (band) {
+        run_band(p, pump, c0, o->dt, a0, kb, ke, o->variant == 1, o->field, st);
     } else if (ke > kb && n > 0) {
         if (o->use_graph) {
             auto key = std::make_tuple(kb, ke, (int)g->dtype, c0, o->dt, a0, pump, R,

@@ -106,11 +106,14 @@ inline int dtype_bytes(int dt) {
 }
 
 struct PersistPlan;
+struct BandPersist;
 
 // Cached state of one solve configuration (scratch buffers + captured graph).
 struct SolvePlan {
     std::shared_ptr<PersistPlan> pp;   // persistent dense plan (null until tried)
     bool pp_tried = false;
+    std::shared_ptr<BandPersist> bp;   // persistent band plan (null until tried)
+    bool bp_tried = false;
     int tuned_plan = 0;                // autotuner's choice for plan 0: 1 per-step, 2 persistent
     int last_plan = 0;                 // plan the last solve ran
     int sky_kernel = 0;                // SNP graphs: kSkyBandFma, kSkyBandMfma or kSkyRows

@@ -1444,3 +1444,39 @@ def test_release_cached_memory():
     assert qh.release_cached_memory() >= need
     assert torch.equal(qh.bsb_solve(g, 16, 50, seed=3)["best_cut"].cpu(), ref)
     g.free()
+
+
+BAND_PLAN_CASES = [
+    # n, gap_mean, dtype, R: one workgroup; a remainder row; several workgroups; 16 replicas only;
+    # bands wider than the registers hold (every variant reads columns from memory); replica
+    # groups that run one after another
+    (17, 1430.0, "f32", 16), (50, 1430.0, "bf16", 32), (300, 1430.0, "f16", 64), (1201, 1430.0, "f16", 48 * 4),
+    (2001, 1430.0, "f16", 128), (1500, 1430.0, "f32", 32), (900, 60.0, "f16", 16), (1301, 45.0, "f32", 64),
+    (9000, 400.0, "bf16", 64), (30011, 1430.0, "f16", 512), (40000, 1430.0, "f32", 256),
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,gap,dtype,R", BAND_PLAN_CASES)
+def test_band_plan_equals_per_step(n, gap, dtype, R):
+    """Plan 0 on an SNP graph (all steps in one launch where the graph fits) against the
+    per-row kernel, one launch per step: the same state bit for bit, over step ranges that
+    start from a kept state, with a field, and in the discrete variant."""
+    w = synth.snp_small(5, n_snp=n, gap_mean=gap)
+    g = gpu_graph(w, "snp_llr", dtype)
+    field = torch.linspace(-0.3, 0.3, n, dtype=torch.float32, device="cuda")
+    out = []
+    for plan in (3, 0):
+        x = torch.empty((n, R), dtype=torch.float32, device="cuda")
+        y = torch.empty_like(x)
+        got = []
+        for kw in (dict(step_end=1), dict(step_begin=1, step_end=4, init=False),
+                   dict(step_begin=4, step_end=25, init=False, field=field),
+                   dict(step_begin=25, step_end=32, init=False, discrete=True)):
+            qh.bsb_solve(g, R, 40, seed=9, x=x, y=y, plan=plan, readout=False, **kw)
+            got += [x.clone(), y.clone()]
+        r = qh.bsb_solve(g, R, 40, seed=9, plan=plan, eval_every=15, energy=True)
+        out.append(got + [r["best_spins"], r["cuts"], r["best_cut"], r["energy"]])
+    assert g.plan_info(R)["plan_used"] == 2
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
