@@ -216,7 +216,9 @@ typedef struct {
                             graph and option set); 0: plain stream launches */
     int32_t plan;        /* step-loop plan: 0 = autotuned; 1 = one fused kernel per step
                             (the tuned kernel when there is one); 2 = persistent (dense
-                            16/8-bit graphs only).  SNP (skyline) graphs only: 3 = per-row
+                            16/8-bit graphs only).  Plan 0 runs FP32 dense graphs in one launch
+                            too, where every row tile's stored tiles are consecutive (sorted
+                            reads), with plan 1's results.  SNP (skyline) graphs only: 3 = per-row
                             kernel; 4 = band blocks on FMAs (bit-identical to 3); 5 = band
                             blocks on MFMAs (four columns summed per MFMA: equal to 3-4 up
                             to FP32 rounding).  Plan 0 on SNP graphs without long-range pairs
@@ -301,11 +303,12 @@ qh_status qh_bsb_solve(const qh_graph *g, const qh_bsb_opts *opts, qh_result *re
  * yet, 1 = one fused kernel per step, 2 = persistent (all steps in one cooperative
  * launch; dense graphs: state in registers, J in LDS; SNP graphs: x in LDS, y and J in
  * registers).  With opts.plan = 0 the first solve of a
- * (graph, replicas) pair times the candidates on scratch state (64 steps each) and keeps
+ * (graph, replicas) pair times the candidates on scratch state (a few steps each) and keeps
  * the fastest: the per-step kernel with 64 (two or four tiles in flight), 32 and 16
  * replicas per workgroup (dense graphs, R >= 64) and the persistent plan where it fits
- * (every candidate gives bit-identical results); us_per_step holds those
- * measurements (0 when not measured).  SNP graphs time the two band kernels over four steps.
+ * (every candidate gives bit-identical results), or the two band kernels (SNP graphs); the
+ * arrays below hold those measurements (0 when not measured).  Graphs that plan 0 runs in one
+ * launch (see qh_bsb_opts.plan) are timed all the same, for plan 1 and this report.
  * Host output.
  * The persistent plan synchronises neighbouring workgroups with agent-scope
  * release / acquire on per-workgroup step counters. */
@@ -328,7 +331,8 @@ typedef struct {
 qh_status qh_solve_plan_info(const qh_graph *g, int32_t replicas, qh_plan_info *out);
 
 /* Runs the plan-0 autotuner for (graph, opts->replicas) on its own: the timing runs on
- * scratch state that qh_bsb_solve makes on its first plan-0 call, with opts' schedule.
+ * scratch state that qh_bsb_solve makes on its first plan-0 call, with opts' schedule; it
+ * chooses among the explicit plans (plan 0 itself may run a graph in one launch instead).
  * *chosen receives *opts with plan, replica_tile, tiles_in_flight and persistent_sync
  * set to the choice: a qh_bsb_solve with them runs the same kernels without tuning (and
  * gives the same results, every candidate being bit-identical).  us_per_step (host float

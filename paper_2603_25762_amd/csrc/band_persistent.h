@@ -1,4 +1,4 @@
-// Persistent band solve of SNP graphs (all steps in one cooperative launch): tables shared by
+// Persistent band solve (all steps in one cooperative launch): tables shared by
 // the host planner, the single-graph solve and the batched solve.
 #pragma once
 
@@ -70,12 +70,14 @@ struct BandSplit {
     std::vector<BandJob> part;  // geometry fields of each workgroup's job
 };
 
-// Plan of one SNP graph and replica count (device tables built once).
+// Plan of one graph and replica count (device tables built once).
 struct BandPersist {
     bool ok = false;
     BandLaunch launch;
     int passes = 0;             // most jobs of one workgroup
     DevBuf<BandTeam> team;
+    DevBuf<int64_t> off;        // dense graphs: the strips as band blocks
+    DevBuf<int32_t> lo, w;
     DevBuf<BandJob> jobs;
     DevBuf<int32_t> job_ptr;
     DevBuf<float> xch;

@@ -1,4 +1,4 @@
-// Persistent band solve of SNP graphs: planner and launch (the kernel is in
+// Persistent band solve (SNP graphs, FP32 dense graphs): planner and launch (the kernel is in
 // band_persistent_kernel.h; the discrete variant's instantiations in
 // band_persistent_discrete.hip, so that the two halves compile in parallel).
 #include <algorithm>
@@ -66,7 +66,28 @@ BandSplit split_band(const int32_t *bb_lo, const int32_t *bb_w, int64_t n_bblk, 
 }
 
 // whole chunks of 16 columns that the kernel variant keeps in registers per block
-static int held_chunks(int dtype, int um) { return (dtype == QH_F32 ? 32 : 48) / um - 1; }
+static int held_chunks(int dtype, int um) {
+    return dtype == kBpTiles ? 32 / um : (dtype == QH_F32 ? 32 : 48) / um - 1;
+}
+
+// The 16-row strips of a dense FP32 graph as band blocks over whole tiles: their first column,
+// width and offset.  False when some row tile's stored tiles are not consecutive (unsorted
+// reads).
+static bool strips_of(const qh_graph *g, std::vector<int64_t> &off, std::vector<int32_t> &lo, std::vector<int32_t> &w,
+                      hipStream_t st) {
+    const auto tptr = download(g->t_ptr.p, g->n_rt + 1, st), tcol = download(g->t_col.p, g->n_tiles, st);
+    for (int64_t rt = 0; rt < g->n_rt; ++rt) {
+        const int32_t t0 = tptr[rt], t1 = tptr[rt + 1];
+        if (t1 > t0 && tcol[t1 - 1] - tcol[t0] != t1 - 1 - t0) return false;
+        for (int s = 0; s < kTile / kBandRows; ++s) {
+            // (a row tile without stored tiles: zeros over its own rows)
+            off.push_back(t1 > t0 ? (int64_t)t0 * kTileElems * 4 + s * kTileElems : -1);
+            lo.push_back((int32_t)(t1 > t0 ? tcol[t0] : rt) * kTile);
+            w.push_back(std::max(t1 - t0, 1) * kTile);
+        }
+    }
+    return true;
+}
 
 static int units_variant(int64_t blocks) {
     const int64_t u = ceil_div(blocks, kBpWaves);
@@ -85,13 +106,22 @@ static int units_variant(int64_t blocks) {
 bool build_band_plan(const qh_graph *g, SolvePlan &p, BandPersist &bp, hipStream_t st) {
     bp.ok = false;
     const int R = p.R;
-    const int64_t nb = g->n_bblk;
-    if (g->storage != QH_STORE_SKYLINE || g->l_nnz > 0 || nb == 0 || g->n >= ((int64_t)1 << 26)) return false;
+    const bool tiles = g->storage == QH_STORE_DENSE;
+    const int64_t nb = tiles ? g->n_rt * (kTile / kBandRows) : g->n_bblk;
+    if ((tiles && g->dtype != QH_F32) || g->l_nnz > 0 || nb == 0 || g->n >= ((int64_t)1 << 26)) return false;
     int n_cu = 0, coop = 0;
     QH_HIP(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, g->device));
     QH_HIP(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, g->device));
     if (!coop || n_cu < 1) return false;
-    const std::vector<int32_t> lo = download(g->bb_lo.p, nb, st), wd = download(g->bb_w.p, nb, st);
+    const int dtype = tiles ? kBpTiles : g->bb_dtype;
+    std::vector<int64_t> off;
+    std::vector<int32_t> lo, wd;
+    if (tiles) {
+        if (!strips_of(g, off, lo, wd, st)) return false;
+    } else {
+        lo = download(g->bb_lo.p, nb, st);
+        wd = download(g->bb_w.p, nb, st);
+    }
     double quads = 0.0;
     for (int32_t w : wd) quads += ceil_div(w, 4);
     quads /= (double)nb;
@@ -104,7 +134,7 @@ bool build_band_plan(const qh_graph *g, SolvePlan &p, BandPersist &bp, hipStream
             const int wpg = (int)ceil_div(nb, bpw);
             if (wpg > n_cu || (bpw > 1 && (int)ceil_div(nb, bpw - 1) == wpg)) continue;
             const int um = units_variant(ceil_div(nb, wpg));
-            const int held = held_chunks(g->bb_dtype, um);
+            const int held = held_chunks(dtype, um);
             double past = 0.0;
             for (int32_t w : wd) past += std::max(0, w / 16 - held);
             const int slots = std::min(ng, n_cu / wpg), passes = (int)ceil_div(ng, slots);
@@ -115,7 +145,8 @@ bool build_band_plan(const qh_graph *g, SolvePlan &p, BandPersist &bp, hipStream
         }
     }
     std::sort(cands.begin(), cands.end(), [](const Cand &a, const Cand &b) { return a.us < b.us; });
-    const double step_us = std::max({4.0, 1.5 + 0.43 * quads, 3.0 + (double)g->n * R * 16.0 / 4.6e6});
+    const double step_us = tiles ? std::max(4.0, 3.0 + 0.1 * quads + (double)g->n * R * 16.0 / 4.6e6)
+                                 : std::max({4.0, 1.5 + 0.43 * quads, 3.0 + (double)g->n * R * 16.0 / 4.6e6});
     for (const Cand &c : cands) {
         if (c.us > 0.9 * step_us) break;
         BandSplit s = split_band(lo.data(), wd.data(), nb, c.wpg);
@@ -126,7 +157,7 @@ bool build_band_plan(const qh_graph *g, SolvePlan &p, BandPersist &bp, hipStream
         bl.rt = c.rt;
         bl.um = c.um;
         bl.grid = c.wpg * c.slots;
-        bl.dtype = g->bb_dtype;
+        bl.dtype = dtype;
         bl.lds_bytes = lds;
         const int64_t rows = nb * kBandRows;
         bl.xch_floats = c.wpg > 1 ? (int64_t)c.slots * 2 * rows * c.rt : 0;
@@ -147,13 +178,21 @@ bool build_band_plan(const qh_graph *g, SolvePlan &p, BandPersist &bp, hipStream
                 bl.job_ptr.push_back((int32_t)bl.jobs.size());
             }
         BandTeam T{};
-        T.bb_off = g->bb_off.p;
-        T.bb_lo = g->bb_lo.p;
-        T.bb_w = g->bb_w.p;
-        T.bb_val = g->bb_val.p;
+        if (tiles) {
+            bp.off.alloc(nb);
+            bp.off.upload(off.data(), nb, st);
+            bp.lo.alloc(nb);
+            bp.lo.upload(lo.data(), nb, st);
+            bp.w.alloc(nb);
+            bp.w.upload(wd.data(), nb, st);
+        }
+        T.bb_off = tiles ? bp.off.p : g->bb_off.p;
+        T.bb_lo = tiles ? bp.lo.p : g->bb_lo.p;
+        T.bb_w = tiles ? bp.w.p : g->bb_w.p;
+        T.bb_val = tiles ? g->t_val.p : g->bb_val.p;
         T.x = p.xa.p;
         T.y = p.y.p;
-        T.bscale = g->bb_scale;
+        T.bscale = tiles ? 1.0f : g->bb_scale;
         T.n = (int32_t)g->n;
         bp.passes = c.passes;
         bp.team.alloc(1);

@@ -1,5 +1,6 @@
-// The persistent band kernel (SNP graphs): all steps of a solve inside one launch, the whole
-// state and the couplings on chip.
+// The persistent band kernel (SNP graphs, and FP32 dense read graphs whose reads are sorted, so
+// that every row tile's stored tiles are consecutive): all steps of a solve inside one launch,
+// the whole state and the couplings on chip.
 //
 // A workgroup owns consecutive band blocks (16 rows each) of one group of RT replicas.  Its x
 // rows, and the neighbours' rows that its blocks reach, sit in LDS; its y and its couplings
@@ -104,15 +105,19 @@ __device__ inline void bp_lds_store(float *p, const BpVec<NB> &r) {
     __builtin_memcpy(__builtin_assume_aligned(p, 4 * NB), &r, 4 * NB);
 }
 
+// DT values of this kernel: a storage type of band blocks, or the FP32 tiles of a dense graph,
+// whose 16-row strips are band blocks over whole tiles
+constexpr int kBpTiles = 100;
+
 // couplings of one chunk of 16 columns: four MFMA A operands (quads of four columns), two per
 // register in 16-bit types
 template <int DT>
 struct BpChunk {
-    static constexpr int kRegs = DT == QH_F32 ? 4 : 2;
+    static constexpr int kRegs = DT == QH_F32 || DT == kBpTiles ? 4 : 2;
 };
 template <int DT>
 __device__ inline float bp_a(const uint32_t *j, int k) {   // quad k of a chunk, widened exactly
-    if constexpr (DT == QH_F32) return __uint_as_float(j[k]);
+    if constexpr (DT == QH_F32 || DT == kBpTiles) return __uint_as_float(j[k]);
     else if constexpr (DT == QH_F16) return f16_bits_to_f32((uint16_t)(k & 1 ? j[k >> 1] >> 16 : j[k >> 1]));
     else return __uint_as_float(k & 1 ? j[k >> 1] & 0xffff0000u : j[k >> 1] << 16);
 }
@@ -123,6 +128,15 @@ template <int DT>
 __device__ inline bp_rsrc_t bp_block(const uint8_t *val, const int64_t *bb_off, int blk, int W) {
     constexpr int EB = DT == QH_F32 ? 4 : 2;
     const int64_t off = ((const QH_CONST int64_t *)bb_off)[blk];
+    // tiles: off is the byte offset of the strip's part of its first stored tile (negative: the
+    // row tile has none, the block is all zeros); the strip's parts of its tiles are
+    // kTileElems * 4 bytes apart
+    // (W = 0: no unit, an empty buffer)
+    if constexpr (DT == kBpTiles) {
+        const bool any = off >= 0 && W >= kTile;
+        return __builtin_amdgcn_make_buffer_rsrc((void *)(val + (any ? off : 0)), 0,
+                                                 any ? (W / kTile - 1) * kTileElems * 4 + kTileElems : 0, 0x00027000);
+    }
     // raw dword buffer of gfx9: stride 0, 32-bit data format
     return __builtin_amdgcn_make_buffer_rsrc((void *)(val + off * EB), 0, W * kBandRows * EB, 0x00027000);
 }
@@ -130,7 +144,13 @@ __device__ inline bp_rsrc_t bp_block(const uint8_t *val, const int64_t *bb_off, 
 // of the quad's 64
 template <int DT>
 __device__ inline void bp_load_chunk(uint32_t *j, bp_rsrc_t blk, int c, int lane) {
-    if constexpr (DT == QH_F32) {
+    if constexpr (DT == kBpTiles) {
+        // a strip's part of a tile: four chunks, each lane's four quads together
+        const auto v = __builtin_amdgcn_raw_buffer_load_b128(blk, lane * 16 + (c >> 2) * (kTileElems * 4) + (c & 3) * 1024,
+                                                             0, 0);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) j[k] = v[k];
+    } else if constexpr (DT == QH_F32) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) j[k] = __builtin_amdgcn_raw_buffer_load_b32(blk, lane * 4 + (c * 4 + k) * 256, 0, 0);
     } else {
@@ -153,8 +173,10 @@ __global__ __launch_bounds__(kBpThreads, 2) void k_band_persistent(BandPersistAr
     extern __shared__ __attribute__((aligned(16))) float bp_x[];
     constexpr int RT = 16 * NB;
     constexpr int CR = BpChunk<DT>::kRegs;
-    constexpr int kRegs = DT == QH_F32 ? 128 : 96;
-    constexpr int MAXC = kRegs / UM / CR - 1;      // whole chunks of 16 columns held per block (and the last)
+    constexpr int kRegs = CR == 4 ? 128 : 96;
+    constexpr bool kWhole = DT == kBpTiles;        // blocks end with a whole chunk
+    // whole chunks of 16 columns held per block (and the last, partial one)
+    constexpr int MAXC = kRegs / UM / CR - (kWhole ? 0 : 1);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, g4 = lane >> 4;
@@ -185,7 +207,7 @@ __global__ __launch_bounds__(kBpThreads, 2) void k_band_persistent(BandPersistAr
         uint32_t uo[UM];                           // LDS rows of the unit's first column (low half) and own first row
         int uw[UM];                                // columns (0: no unit)
         int upub = 0;                              // bit i: neighbours read unit i's rows
-        uint32_t jr[UM][(MAXC + 1) * CR];
+        uint32_t jr[UM][kRegs / UM];
         BpVec<NB> ys[UM][4];
 #pragma unroll
         for (int i = 0; i < UM; ++i) {
@@ -202,7 +224,7 @@ __global__ __launch_bounds__(kBpThreads, 2) void k_band_persistent(BandPersistAr
             if (live && (rel < J.pub_a || rel >= J.pub_b)) upub |= 1 << i;
             const bp_rsrc_t rsrc = bp_block<DT>(T.bb_val, T.bb_off, blk, W);
 #pragma unroll
-            for (int c = 0; c <= MAXC; ++c) {
+            for (int c = 0; c < kRegs / UM / CR; ++c) {
                 bp_load_chunk<DT>(&jr[i][c * CR], rsrc, c < MAXC ? c : W >> 4, lane);
                 if (c % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // (bounds the loads in flight, and their registers)
             }
@@ -270,7 +292,7 @@ __global__ __launch_bounds__(kBpThreads, 2) void k_band_persistent(BandPersistAr
                 for (int i = 0; i < UM; ++i) {
                     __asm__ volatile("" : "+s"(uw[i]), "+s"(uo[i]));
 #pragma unroll
-                    for (int c = 0; c < (MAXC + 1) * CR; ++c) __asm__ volatile("" : "+v"(jr[i][c]));
+                    for (int c = 0; c < kRegs / UM; ++c) __asm__ volatile("" : "+v"(jr[i][c]));
                 }
                 // x rows of chunk c of unit i
                 auto read4 = [&](BpVec<NB> (&bv)[4], int i, int c) {
@@ -312,7 +334,7 @@ __global__ __launch_bounds__(kBpThreads, 2) void k_band_persistent(BandPersistAr
                         BpVec<NB> xo[4], last[4];          // the unit's own x; x rows of the last chunk
 #pragma unroll
                         for (int k = 0; k < 4; ++k) xo[k] = bp_lds<NB>(xop + k * RT);
-                        read4(last, i, nf);
+                        if constexpr (!kWhole) read4(last, i, nf);
                         BpVec<NB> bv[2][4];
 #pragma unroll
                         for (int k = 0; k < 4; ++k) bv[0][k] = first[k];
@@ -339,8 +361,10 @@ __global__ __launch_bounds__(kBpThreads, 2) void k_band_persistent(BandPersistAr
                         }
                         // the last chunk: columns past W multiply their couplings, 0, by 0 and not by
                         // whatever those rows of x hold
-                        const int Wl = W - 16 * nf - g4;   // columns of this lane's quad slots below W
-                        mfma4(&jr[i][MAXC * CR], last, 0 < Wl, 4 < Wl, 8 < Wl, 12 < Wl);
+                        if constexpr (!kWhole) {
+                            const int Wl = W - 16 * nf - g4;   // columns of this lane's quad slots below W
+                            mfma4(&jr[i][MAXC * CR], last, 0 < Wl, 4 < Wl, 8 < Wl, 12 < Wl);
+                        }
                         if (i + 1 < UM) read4(first, i + 1, 0);
 #pragma unroll
                         for (int b = 0; b < NB; ++b)
@@ -473,6 +497,7 @@ static void launch_band_disc(const BandLaunch &bl, const BandPersistArgs &a, hip
         case QH_F32: QH_BP(QH_F32); break;
         case QH_F16: QH_BP(QH_F16); break;
         case QH_BF16: QH_BP(QH_BF16); break;
+        case kBpTiles: QH_BP(kBpTiles); break;
         default: fail(QH_EUNSUPPORTED, "dtype not offered on skyline storage");
     }
 #undef QH_BP

@@ -1376,7 +1376,7 @@ static void run_persistent(const qh_graph *g, SolvePlan &p, const float *pump, d
     if (err) fail(QH_EHIP, "persistent bSB kernel: a neighbour wait exceeded its poll limit");
 }
 
-// Steps [kb, ke) of an SNP graph in one cooperative launch on the band plan; the state is in
+// Steps [kb, ke) of a graph in one cooperative launch on the band plan; the state is in
 // p.xa / p.y before and after.
 static void run_band(SolvePlan &p, const float *pump, double c0, double dt, double a0, int kb, int ke, int discrete,
                      const float *field, hipStream_t st) {
@@ -1416,12 +1416,15 @@ static bool stream_capturing(hipStream_t st) {
 
 // Autotuner for plan 0 on dense 16/8-bit graphs: time a short run of each candidate on
 // scratch state -- one fused kernel per step, and the persistent launch -- and keep the
-// faster.  Both compute bit-identical results, so the choice only affects speed.
+// faster.  Both compute bit-identical results, so the choice only affects speed.  A warm step
+// or two, then `nt` steps: 64 steps twice for each of four to six candidates took as long as a
+// 500-step solve, and the candidates differ by 10 % or more from the first steps on (1,501
+// reads, F32, R = 64: 14.3, 14.2, 8.6 and 8.2 us).
 static void autotune_dense(const qh_graph *g, SolvePlan &p, const qh_bsb_opts *o, const float *pump, double c0,
-                           double a0, hipStream_t st) {
+                           double a0, int nt, hipStream_t st) {
     const int64_t n = g->n;
     const int R = p.R;
-    const int nt = std::min(o->steps, 64);
+    nt = std::min(o->steps, nt);
     const bool pers_ok = p.pp && p.pp->ok;
     // per-step candidates (replica tile, tiles in flight for 64-replica tiles: 64 + depth 4
     // is coded as 65), then 0 = persistent
@@ -1446,17 +1449,17 @@ static void autotune_dense(const qh_graph *g, SolvePlan &p, const qh_bsb_opts *o
             p.run_depth = cand == 65 ? 4 : 2;
         }
         float ms = 0.0f;
+        hipLaunchKernelGGL(k_init, dim3(grid_for(n * R)), dim3(256), 0, st, (uint64_t)0x5eed, n, R, p.xa.p, p.y.p);
+        QH_CHECK_LAUNCH();
+        if (!x_pingpong(g)) x_to_h(g, p, n, R, o->variant == 1, st);
         for (int rep = 0; rep < 2; ++rep) {   // the first repetition warms caches and code
-            hipLaunchKernelGGL(k_init, dim3(grid_for(n * R)), dim3(256), 0, st, (uint64_t)0x5eed, n, R, p.xa.p,
-                               p.y.p);
-            QH_CHECK_LAUNCH();
-            if (!x_pingpong(g)) x_to_h(g, p, n, R, o->variant == 1, st);
+            const int ns = rep ? nt : std::min(nt, 2);
             QH_HIP(hipEventRecord(e0, st));
-            if (cand > 0) run_steps(g, p, o, pump, c0, a0, 0, nt, st);
-            else run_persistent(g, p, pump, c0, o->dt, a0, 0, nt, o->variant == 1, o->field, cand < 0, st);
+            if (cand > 0) run_steps(g, p, o, pump, c0, a0, 0, ns, st);
+            else run_persistent(g, p, pump, c0, o->dt, a0, 0, ns, o->variant == 1, o->field, cand < 0, st);
             QH_HIP(hipEventRecord(e1, st));
-            QH_HIP(hipEventSynchronize(e1));
         }
+        QH_HIP(hipEventSynchronize(e1));
         QH_HIP(hipEventElapsedTime(&ms, e0, e1));
         if (cand > 0 && (best_step == 0.0f || ms < best_step)) {
             best_step = ms;
@@ -1556,7 +1559,7 @@ void autotune(const qh_graph *g, const qh_bsb_opts *o, qh_bsb_opts *chosen, floa
             build_persistent_plan(g, R, *p.pp, st);
             p.pp_tried = true;
         }
-        if (!p.tuned_plan) autotune_dense(g, p, o, pump, c0, a0, st);
+        if (!p.tuned_plan) autotune_dense(g, p, o, pump, c0, a0, 16, st);
         if (dense16 && p.pp && p.pp->ok && p.tuned_plan == 2) {
             chosen->plan = 2;
             chosen->persistent_sync = p.tuned_coh ? 2 : 1;
@@ -1614,11 +1617,11 @@ void bsb_solve(const qh_graph *g, const qh_bsb_opts *o, qh_result *res, hipStrea
     int final_half = 0;
     bool persistent = false;
     const bool want_persistent = o->plan == 0 || o->plan == 2;
-    // SNP graphs under plan 0: every step in one launch with the state on chip, where the graph
-    // fits (the band kernels' results bit for bit); a stream being captured takes the per-step
-    // launches
+    // SNP graphs and FP32 dense graphs under plan 0: every step in one launch with the state on
+    // chip, where the graph fits (the per-step kernels' results bit for bit); a stream being
+    // captured takes the per-step launches
     bool band = false;
-    if (!dense && o->plan == 0 && ke > kb && n > 0 && !stream_capturing(st)) {
+    if (!dense16 && o->plan == 0 && ke > kb && n > 0 && !stream_capturing(st)) {
         if (!p.bp_tried) {
             p.bp = std::make_shared<BandPersist>();
             build_band_plan(g, p, *p.bp, st);
@@ -1632,7 +1635,8 @@ void bsb_solve(const qh_graph *g, const qh_bsb_opts *o, qh_result *res, hipStrea
             build_persistent_plan(g, R, *p.pp, st);
             p.pp_tried = true;
         }
-        if (o->plan == 0 && !p.tuned_plan) autotune_dense(g, p, o, pump, c0, a0, st);
+        // (a graph on the band plan is timed briefly, for the report and for later plan-1 solves)
+        if (o->plan == 0 && !p.tuned_plan) autotune_dense(g, p, o, pump, c0, a0, band ? 4 : 16, st);
         if (dense16 && want_persistent && p.pp->ok) persistent = o->plan == 2 || p.tuned_plan == 2;
     }
     // replica tile of the per-step dense kernel: the caller's, else the tuned one, else 64
