@@ -17,6 +17,8 @@ struct BandTeam {
     const uint8_t *bb_val;
     float *x, *y;               // [n][R] state, in and out
     const float *field;         // deformation field h [n] (nullptr: none)
+    const float *scale;         // FP8 tiles: row scales
+    const uint64_t *tiles;      // dense graphs: bit c of a strip's word is set when tile c of its range is stored
     float c0, bscale;
     int32_t n;
 };
@@ -58,6 +60,7 @@ struct BandLaunch {
     int um = 0;                 // band blocks per wave (kernel variant: 1, 2, 4 or 8)
     int grid = 0;
     int dtype = 0;
+    bool strips = false;        // the strip kernel (16/8-bit dense graphs), else the band kernel
     int64_t lds_bytes = 0, xch_floats = 0, n_flags = 0;
     std::vector<BandJob> jobs;  // in launch order of each workgroup (job_ptr)
     std::vector<int32_t> job_ptr;
@@ -75,9 +78,11 @@ struct BandPersist {
     bool ok = false;
     BandLaunch launch;
     int passes = 0;             // most jobs of one workgroup
+    bool gaps = false;          // dense graphs: some row tile's stored tiles are not consecutive
     DevBuf<BandTeam> team;
     DevBuf<int64_t> off;        // dense graphs: the strips as band blocks
     DevBuf<int32_t> lo, w;
+    DevBuf<uint64_t> tiles;
     DevBuf<BandJob> jobs;
     DevBuf<int32_t> job_ptr;
     DevBuf<float> xch;
@@ -89,5 +94,7 @@ bool build_band_plan(const qh_graph *g, SolvePlan &p, BandPersist &bp, hipStream
 void launch_band(const BandLaunch &bl, const BandPersistArgs &a, int discrete, hipStream_t st);
 void launch_band_plain(const BandLaunch &bl, const BandPersistArgs &a, hipStream_t st);
 void launch_band_discrete(const BandLaunch &bl, const BandPersistArgs &a, hipStream_t st);
+void launch_strip_plain(const BandLaunch &bl, const BandPersistArgs &a, hipStream_t st);
+void launch_strip_discrete(const BandLaunch &bl, const BandPersistArgs &a, hipStream_t st);
 
 }  // namespace qh

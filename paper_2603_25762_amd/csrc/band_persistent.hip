@@ -3,7 +3,7 @@
 // band_persistent_discrete.hip, so that the two halves compile in parallel).
 #include <algorithm>
 
-#include "band_persistent_kernel.h"
+#include "strip_persistent_kernel.h"
 
 namespace qh {
 
@@ -65,25 +65,32 @@ BandSplit split_band(const int32_t *bb_lo, const int32_t *bb_w, int64_t n_bblk, 
     return s;
 }
 
-// whole chunks of 16 columns that the kernel variant keeps in registers per block
-static int held_chunks(int dtype, int um) {
+// whole chunks of 16 columns that the kernel variant keeps in registers per block (strip)
+static int held_chunks(int dtype, int um, bool strips) {
+    if (strips) return kSpRegs / um / sp_tile_regs(dtype) * (kTile / 16);
     return dtype == kBpTiles ? 32 / um : (dtype == QH_F32 ? 32 : 48) / um - 1;
 }
 
-// The 16-row strips of a dense FP32 graph as band blocks over whole tiles: their first column,
-// width and offset.  False when some row tile's stored tiles are not consecutive (unsorted
-// reads).
+// The 16-row strips of a dense graph as band blocks over whole tiles: their first column, width,
+// the byte offset of their part of the first stored tile, and which tiles of the range are
+// stored (a row tile without stored tiles: none, over its own rows).  False when a range is
+// longer than a word has bits.
 static bool strips_of(const qh_graph *g, std::vector<int64_t> &off, std::vector<int32_t> &lo, std::vector<int32_t> &w,
-                      hipStream_t st) {
+                      std::vector<uint64_t> &tiles, bool &gaps, hipStream_t st) {
     const auto tptr = download(g->t_ptr.p, g->n_rt + 1, st), tcol = download(g->t_col.p, g->n_tiles, st);
+    const int64_t eb = dtype_bytes(g->dtype);
     for (int64_t rt = 0; rt < g->n_rt; ++rt) {
         const int32_t t0 = tptr[rt], t1 = tptr[rt + 1];
-        if (t1 > t0 && tcol[t1 - 1] - tcol[t0] != t1 - 1 - t0) return false;
+        const int32_t c0 = t1 > t0 ? tcol[t0] : (int32_t)rt, nt = t1 > t0 ? tcol[t1 - 1] - c0 + 1 : 1;
+        if (nt > 64) return false;
+        if (t1 > t0 && nt != t1 - t0) gaps = true;
+        uint64_t m = 0;
+        for (int32_t t = t0; t < t1; ++t) m |= 1ull << (tcol[t] - c0);
         for (int s = 0; s < kTile / kBandRows; ++s) {
-            // (a row tile without stored tiles: zeros over its own rows)
-            off.push_back(t1 > t0 ? (int64_t)t0 * kTileElems * 4 + s * kTileElems : -1);
-            lo.push_back((int32_t)(t1 > t0 ? tcol[t0] : rt) * kTile);
-            w.push_back(std::max(t1 - t0, 1) * kTile);
+            off.push_back(((int64_t)t0 * kTileElems + s * (kTileElems / 4)) * eb);
+            lo.push_back(c0 * kTile);
+            w.push_back(nt * kTile);
+            tiles.push_back(m);
         }
     }
     return true;
@@ -108,16 +115,19 @@ bool build_band_plan(const qh_graph *g, SolvePlan &p, BandPersist &bp, hipStream
     const int R = p.R;
     const bool tiles = g->storage == QH_STORE_DENSE;
     const int64_t nb = tiles ? g->n_rt * (kTile / kBandRows) : g->n_bblk;
-    if ((tiles && g->dtype != QH_F32) || g->l_nnz > 0 || nb == 0 || g->n >= ((int64_t)1 << 26)) return false;
+    const bool strips = tiles && g->dtype != QH_F32;
+    if (g->l_nnz > 0 || nb == 0 || g->n >= ((int64_t)1 << 26)) return false;
     int n_cu = 0, coop = 0;
     QH_HIP(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, g->device));
     QH_HIP(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, g->device));
     if (!coop || n_cu < 1) return false;
-    const int dtype = tiles ? kBpTiles : g->bb_dtype;
+    const int dtype = strips ? g->dtype : tiles ? kBpTiles : g->bb_dtype;
     std::vector<int64_t> off;
     std::vector<int32_t> lo, wd;
+    std::vector<uint64_t> tm;
     if (tiles) {
-        if (!strips_of(g, off, lo, wd, st)) return false;
+        bp.gaps = false;
+        if (!strips_of(g, off, lo, wd, tm, bp.gaps, st)) return false;
     } else {
         lo = download(g->bb_lo.p, nb, st);
         wd = download(g->bb_w.p, nb, st);
@@ -130,27 +140,28 @@ bool build_band_plan(const qh_graph *g, SolvePlan &p, BandPersist &bp, hipStream
     for (int rt : {32, 16}) {
         if (R % rt) continue;
         const int ng = R / rt;
-        for (int bpw = 1; bpw <= 8 * kBpWaves; ++bpw) {
+        for (int bpw = 1; bpw <= (strips ? 4 : 8) * kBpWaves; ++bpw) {
             const int wpg = (int)ceil_div(nb, bpw);
             if (wpg > n_cu || (bpw > 1 && (int)ceil_div(nb, bpw - 1) == wpg)) continue;
             const int um = units_variant(ceil_div(nb, wpg));
-            const int held = held_chunks(dtype, um);
+            const int held = held_chunks(dtype, um, strips);
             double past = 0.0;
             for (int32_t w : wd) past += std::max(0, w / 16 - held);
             const int slots = std::min(ng, n_cu / wpg), passes = (int)ceil_div(ng, slots);
             const double units = std::max(1.0, (double)ceil_div(nb, wpg) / 4.0);      // per SIMD
-            const double us = 0.9 + units * (quads * (rt / 16) * 0.0195 + 0.12 + past / nb * 0.25) +
-                              (wpg > 1 ? 1.8 : 0.0);
+            const double unit = strips ? quads / 16.0 * ((rt / 16) * 0.04 + 0.02) + 0.2 + past / nb * 0.1
+                                       : quads * (rt / 16) * 0.0195 + 0.12 + past / nb * 0.25;
+            const double us = 0.9 + units * unit + (wpg > 1 ? 1.8 : 0.0);
             cands.push_back({us * passes, rt, wpg, um, slots, passes});
         }
     }
     std::sort(cands.begin(), cands.end(), [](const Cand &a, const Cand &b) { return a.us < b.us; });
-    const double step_us = tiles ? std::max(4.0, 3.0 + 0.1 * quads + (double)g->n * R * 16.0 / 4.6e6)
+    const double step_us = strips ? std::max(4.5, 3.0 + quads / 16.0 * 0.2 + (double)g->n * R * 16.0 / 4.6e6) : tiles ? std::max(4.0, 3.0 + 0.1 * quads + (double)g->n * R * 16.0 / 4.6e6)
                                  : std::max({4.0, 1.5 + 0.43 * quads, 3.0 + (double)g->n * R * 16.0 / 4.6e6});
     for (const Cand &c : cands) {
         if (c.us > 0.9 * step_us) break;
         BandSplit s = split_band(lo.data(), wd.data(), nb, c.wpg);
-        const int64_t lds = (s.lds_rows + kBpPadRows) * c.rt * 4;
+        const int64_t lds = strips ? (s.lds_rows + kSpPadRows) * c.rt * 2 : (s.lds_rows + kBpPadRows) * c.rt * 4;
         if (lds > kBpLdsLimit || units_variant(s.max_blocks) != c.um) continue;
         BandLaunch &bl = bp.launch;
         bl = BandLaunch{};
@@ -158,6 +169,7 @@ bool build_band_plan(const qh_graph *g, SolvePlan &p, BandPersist &bp, hipStream
         bl.um = c.um;
         bl.grid = c.wpg * c.slots;
         bl.dtype = dtype;
+        bl.strips = strips;
         bl.lds_bytes = lds;
         const int64_t rows = nb * kBandRows;
         bl.xch_floats = c.wpg > 1 ? (int64_t)c.slots * 2 * rows * c.rt : 0;
@@ -185,11 +197,15 @@ bool build_band_plan(const qh_graph *g, SolvePlan &p, BandPersist &bp, hipStream
             bp.lo.upload(lo.data(), nb, st);
             bp.w.alloc(nb);
             bp.w.upload(wd.data(), nb, st);
+            bp.tiles.alloc(nb);
+            bp.tiles.upload(tm.data(), nb, st);
         }
         T.bb_off = tiles ? bp.off.p : g->bb_off.p;
         T.bb_lo = tiles ? bp.lo.p : g->bb_lo.p;
         T.bb_w = tiles ? bp.w.p : g->bb_w.p;
         T.bb_val = tiles ? g->t_val.p : g->bb_val.p;
+        T.scale = g->row_scale.p;
+        T.tiles = bp.tiles.p;
         T.x = p.xa.p;
         T.y = p.y.p;
         T.bscale = tiles ? 1.0f : g->bb_scale;
@@ -215,8 +231,13 @@ void launch_band_plain(const BandLaunch &bl, const BandPersistArgs &a, hipStream
 }
 
 void launch_band(const BandLaunch &bl, const BandPersistArgs &a, int discrete, hipStream_t st) {
-    if (discrete) launch_band_discrete(bl, a, st);
-    else launch_band_plain(bl, a, st);
+    if (bl.strips) {
+        if (discrete) launch_strip_discrete(bl, a, st);
+        else launch_strip_plain(bl, a, st);
+    } else {
+        if (discrete) launch_band_discrete(bl, a, st);
+        else launch_band_plain(bl, a, st);
+    }
 }
 
 }  // namespace qh

@@ -1,6 +1,5 @@
-// The persistent band kernel (SNP graphs, and FP32 dense read graphs whose reads are sorted, so
-// that every row tile's stored tiles are consecutive): all steps of a solve inside one launch,
-// the whole state and the couplings on chip.
+// The persistent band kernel (SNP graphs, and FP32 dense read graphs): all steps of a solve inside
+// one launch, the whole state and the couplings on chip.
 //
 // A workgroup owns consecutive band blocks (16 rows each) of one group of RT replicas.  Its x
 // rows, and the neighbours' rows that its blocks reach, sit in LDS; its y and its couplings
@@ -105,6 +104,23 @@ __device__ inline void bp_lds_store(float *p, const BpVec<NB> &r) {
     __builtin_memcpy(__builtin_assume_aligned(p, 4 * NB), &r, 4 * NB);
 }
 
+// Every wave of neighbours [nbr0, nbr1] (but w itself) has published step t - 1, or a wait gave up.
+__device__ inline void bp_wait(const BandPersistArgs &a, const int *flags, int nbr0, int nbr1, int w, int t, int lane) {
+    const int f0 = nbr0 * kBpWaves, nf = (nbr1 + 1) * kBpWaves - f0;
+    int64_t polls = 0;
+    for (int f = lane; f - lane < nf; f += 64) {
+        while (true) {
+            const bool late = f < nf && f / kBpWaves + nbr0 != w && bp_flag(flags + f0 + f) < t;
+            if (!__any(late)) break;
+            if ((++polls & 1023) == 0 && (polls > a.max_polls || bp_flag(a.err) != 0)) {
+                __hip_atomic_fetch_or(a.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                break;
+            }
+            __builtin_amdgcn_s_sleep(1);
+        }
+    }
+}
+
 // DT values of this kernel: a storage type of band blocks, or the FP32 tiles of a dense graph,
 // whose 16-row strips are band blocks over whole tiles
 constexpr int kBpTiles = 100;
@@ -128,26 +144,28 @@ template <int DT>
 __device__ inline bp_rsrc_t bp_block(const uint8_t *val, const int64_t *bb_off, int blk, int W) {
     constexpr int EB = DT == QH_F32 ? 4 : 2;
     const int64_t off = ((const QH_CONST int64_t *)bb_off)[blk];
-    // tiles: off is the byte offset of the strip's part of its first stored tile (negative: the
-    // row tile has none, the block is all zeros); the strip's parts of its tiles are
-    // kTileElems * 4 bytes apart
-    // (W = 0: no unit, an empty buffer)
-    if constexpr (DT == kBpTiles) {
-        const bool any = off >= 0 && W >= kTile;
-        return __builtin_amdgcn_make_buffer_rsrc((void *)(val + (any ? off : 0)), 0,
-                                                 any ? (W / kTile - 1) * kTileElems * 4 + kTileElems : 0, 0x00027000);
-    }
     // raw dword buffer of gfx9: stride 0, 32-bit data format
     return __builtin_amdgcn_make_buffer_rsrc((void *)(val + off * EB), 0, W * kBandRows * EB, 0x00027000);
+}
+// A strip's parts of its stored tiles (tile_bytes apart, part_bytes each) as a buffer; an empty
+// one when there are none.  bp_tile_off: byte offset of tile c of the strip's range, past the
+// buffer's end, where loads return 0, when that tile is not stored.
+__device__ inline bp_rsrc_t bp_strip(const uint8_t *val, int64_t off, uint64_t tiles, int tile_bytes, int part_bytes) {
+    const int nt = __builtin_popcountll(tiles);
+    return __builtin_amdgcn_make_buffer_rsrc((void *)(val + (nt ? off : 0)), 0,
+                                             nt ? (nt - 1) * tile_bytes + part_bytes : 0, 0x00027000);
+}
+__device__ inline int bp_tile_off(uint64_t tiles, int c, int tile_bytes) {
+    return (tiles >> c & 1 ? __builtin_popcountll(tiles & ((1ull << c) - 1)) : 64) * tile_bytes;
 }
 // chunk c of a block: lane l holds row l % 16 of column l / 16 of each quad, which is element l
 // of the quad's 64
 template <int DT>
-__device__ inline void bp_load_chunk(uint32_t *j, bp_rsrc_t blk, int c, int lane) {
+__device__ inline void bp_load_chunk(uint32_t *j, bp_rsrc_t blk, int c, int lane, uint64_t tiles = 0) {
     if constexpr (DT == kBpTiles) {
         // a strip's part of a tile: four chunks, each lane's four quads together
-        const auto v = __builtin_amdgcn_raw_buffer_load_b128(blk, lane * 16 + (c >> 2) * (kTileElems * 4) + (c & 3) * 1024,
-                                                             0, 0);
+        const auto v = __builtin_amdgcn_raw_buffer_load_b128(
+            blk, lane * 16 + bp_tile_off(tiles, c >> 2, kTileElems * 4) + (c & 3) * 1024, 0, 0);
 #pragma unroll
         for (int k = 0; k < 4; ++k) j[k] = v[k];
     } else if constexpr (DT == QH_F32) {
@@ -222,10 +240,13 @@ __global__ __launch_bounds__(kBpThreads, 2) void k_band_persistent(BandPersistAr
             uw[i] = W;
             uo[i] = (uint32_t)(L - xlo) | (uint32_t)(blk * kBandRows - xlo) << 16;
             if (live && (rel < J.pub_a || rel >= J.pub_b)) upub |= 1 << i;
-            const bp_rsrc_t rsrc = bp_block<DT>(T.bb_val, T.bb_off, blk, W);
+            const uint64_t tiles = kWhole && live ? ((const QH_CONST uint64_t *)T.tiles)[blk] : 0;
+            const bp_rsrc_t rsrc = kWhole ? bp_strip(T.bb_val, ((const QH_CONST int64_t *)T.bb_off)[blk], tiles,
+                                                     kTileElems * 4, kTileElems)
+                                          : bp_block<DT>(T.bb_val, T.bb_off, blk, W);
 #pragma unroll
             for (int c = 0; c < kRegs / UM / CR; ++c) {
-                bp_load_chunk<DT>(&jr[i][c * CR], rsrc, c < MAXC ? c : W >> 4, lane);
+                bp_load_chunk<DT>(&jr[i][c * CR], rsrc, c < MAXC ? c : W >> 4, lane, tiles);
                 if (c % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // (bounds the loads in flight, and their registers)
             }
 #pragma unroll
@@ -249,20 +270,7 @@ __global__ __launch_bounds__(kBpThreads, 2) void k_band_persistent(BandPersistAr
             for (int ph = 0; ph < 2; ++ph) {
                 if (ph == 1 && has_nbr) {
                     // the neighbours' step t - 1 is published: their rows -> LDS
-                    const int f0 = J.nbr0 * kBpWaves, nf = (J.nbr1 + 1) * kBpWaves - f0;
-                    int64_t polls = 0;
-                    for (int f = lane; f - lane < nf; f += 64) {
-                        while (true) {
-                            const bool late = f < nf && f / kBpWaves + J.nbr0 != J.w && bp_flag(flags + f0 + f) < t;
-                            if (!__any(late)) break;
-                            if ((++polls & 1023) == 0 &&
-                                (polls > a.max_polls || bp_flag(a.err) != 0)) {
-                                __hip_atomic_fetch_or(a.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                                break;
-                            }
-                            __builtin_amdgcn_s_sleep(1);
-                        }
-                    }
+                    bp_wait(a, flags, J.nbr0, J.nbr1, J.w, t, lane);
                     if (s > 0) {                   // (the first step's rows came with the initial state)
                         const float *src = xch + ((t - 1) & 1) * half;
                         const int own_lo = J.blk0 * kBandRows, own_hi = own_lo + nblk * kBandRows;
@@ -349,12 +357,16 @@ __global__ __launch_bounds__(kBpThreads, 2) void k_band_persistent(BandPersistAr
                             }
                         }
                         if (MAXC < nf) {                   // those past the register-held ones
-                            const bp_rsrc_t rsrc = bp_block<DT>(T.bb_val, T.bb_off, (orow + xlo) / kBandRows, W);
+                            const int blk = (orow + xlo) / kBandRows;
+                            const uint64_t tiles = kWhole ? ((const QH_CONST uint64_t *)T.tiles)[blk] : 0;
+                            const bp_rsrc_t rsrc = kWhole ? bp_strip(T.bb_val, ((const QH_CONST int64_t *)T.bb_off)[blk],
+                                                                     tiles, kTileElems * 4, kTileElems)
+                                                          : bp_block<DT>(T.bb_val, T.bb_off, blk, W);
 #pragma unroll 1
                             for (int c = MAXC; c < nf; ++c) {
                                 uint32_t jt[CR];
                                 BpVec<NB> bt[4];
-                                bp_load_chunk<DT>(jt, rsrc, c, lane);
+                                bp_load_chunk<DT>(jt, rsrc, c, lane, tiles);
                                 read4(bt, i, c);
                                 mfma4(jt, bt, true, true, true, true);
                             }

@@ -1617,27 +1617,28 @@ void bsb_solve(const qh_graph *g, const qh_bsb_opts *o, qh_result *res, hipStrea
     int final_half = 0;
     bool persistent = false;
     const bool want_persistent = o->plan == 0 || o->plan == 2;
-    // SNP graphs and FP32 dense graphs under plan 0: every step in one launch with the state on
-    // chip, where the graph fits (the per-step kernels' results bit for bit); a stream being
-    // captured takes the per-step launches
+    // plan 0: every step in one launch with state and couplings on chip, where the graph fits (the
+    // per-step kernels' results bit for bit); a stream being captured takes the per-step launches
     bool band = false;
-    if (!dense16 && o->plan == 0 && ke > kb && n > 0 && !stream_capturing(st)) {
+    if (o->plan == 0 && ke > kb && n > 0 && !stream_capturing(st)) {
         if (!p.bp_tried) {
             p.bp = std::make_shared<BandPersist>();
             build_band_plan(g, p, *p.bp, st);
             p.bp_tried = true;
         }
-        band = p.bp->ok && (int64_t)p.bp->passes * (ke - kb) < ((int64_t)1 << 30);
+        // (a column tile that a row tile skips multiplies by 0 there: the caller's own state or
+        // field might not be finite)
+        band = p.bp->ok && !(p.bp->gaps && (!o->init || o->field)) && (int64_t)p.bp->passes * (ke - kb) < ((int64_t)1 << 30);
     }
     if (dense && ke > kb && n > 0) {
-        if (dense16 && want_persistent && !p.pp_tried) {
+        if (dense16 && want_persistent && !band && !p.pp_tried) {
             p.pp = std::make_shared<PersistPlan>();
             build_persistent_plan(g, R, *p.pp, st);
             p.pp_tried = true;
         }
         // (a graph on the band plan is timed briefly, for the report and for later plan-1 solves)
         if (o->plan == 0 && !p.tuned_plan) autotune_dense(g, p, o, pump, c0, a0, band ? 4 : 16, st);
-        if (dense16 && want_persistent && p.pp->ok) persistent = o->plan == 2 || p.tuned_plan == 2;
+        if (dense16 && want_persistent && !band && p.pp->ok) persistent = o->plan == 2 || p.tuned_plan == 2;
     }
     // replica tile of the per-step dense kernel: the caller's, else the tuned one, else 64
     p.run_rt = R < 64 ? R : o->replica_tile ? o->replica_tile : p.tuned_rt ? p.tuned_rt : 64;
