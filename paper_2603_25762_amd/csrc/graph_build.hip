@@ -490,15 +490,28 @@ __global__ void k_fixed_to_f64(int64_t n, double *__restrict__ v) {
     }
 }
 
-// kept observations of a fragment whose SNP index, allele code, Phred confidence and skyline
-// row base k_snp_pairs stages in LDS (a longer fragment's later partners come from memory)
-constexpr int kFragLds = 512;
+// kept observations of a fragment whose SNP index, allele code and Phred confidence
+// k_snp_pairs stages in LDS (a longer fragment's later partners come from memory)
+constexpr int kFragLds = 128;
+
+// workgroups of a reduction onto one address (four per CU)
+constexpr int kReduceGroups = 1024;
 
 // Eqs. (9), (11)-(13) with the per-fragment factor alpha and the 1/(|S_i|-1)
 // normalisation of Eq. (14).  J = -w, so each pair term enters J with a + sign.
-// One wave per fragment f and a lane per kept observation (rank a), which handles the
-// pairs (a, b) with a < b <= a + L of the fragment.  In fixed-point mode a term of magnitude
-// 2^20 or more cannot be represented: *clamped is set and the build fails.
+// A workgroup takes gf consecutive fragments, a wave at a time one; a wave's lanes take
+// the pairs (a, a + d), 1 <= d <= L, in order of d, so that a fragment of 14 kept SNPs (91 pairs)
+// keeps 64 lanes busy, where a lane per SNP kept 14.  A term goes to the entry (u, v), u < v,
+// alone; k_mirror copies it to (v, u).  Neighbouring fragments of sorted reads cover the same
+// SNPs, so the group's sums build up in an LDS table (first SNP u x distance v - u) when its SNPs
+// span little enough, and each entry then takes one global atomic per group instead of one per
+// fragment.  Chromosome graph (527,000 fragments, 48 M pairs): a lane per SNP and both entries
+// 5.38 ms, pairs over the lanes and one entry 3.76 ms, with the table (and 23 KB of LDS
+// in place of 43, so that more waves hide the loads) 2.96 ms.  In
+// fixed-point mode a term of magnitude 2^20 or more cannot be represented: *clamped is set and
+// the build fails.
+constexpr int kPairFrags = 32;       // most fragments of a workgroup
+constexpr int kPairTable = 2048;     // entries
 __global__ __launch_bounds__(256) void k_snp_pairs(int64_t F, const int64_t *__restrict__ kept_obs,
                                                    const int64_t *__restrict__ kept_ptr,
                                                    const int32_t *__restrict__ snp, const int8_t *__restrict__ M,
@@ -509,49 +522,71 @@ __global__ __launch_bounds__(256) void k_snp_pairs(int64_t F, const int64_t *__r
                                                    const int32_t *__restrict__ s_lo, double *__restrict__ s_val64,
                                                    const int64_t *__restrict__ l_ptr,
                                                    const int32_t *__restrict__ l_col, double *__restrict__ l_val64,
-                                                   int fixed, int32_t *__restrict__ clamped) {
+                                                   int fixed, int32_t *__restrict__ clamped, int gf) {
     __shared__ double s_q[4][kFragLds];
-    __shared__ int64_t s_rb[4][kFragLds];   // skyline row base s_off[u] - s_lo[u] of each SNP
     __shared__ int32_t s_u[4][kFragLds];
     __shared__ int8_t s_m[4][kFragLds];
+    __shared__ unsigned long long s_tab[kPairTable];
+    __shared__ int32_t s_lo_u, s_hi_u, s_dist;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     double *sq = s_q[wave];
-    int64_t *srb = s_rb[wave];
     int32_t *su = s_u[wave];
     int8_t *sm = s_m[wave];
-    for (int64_t f0 = (int64_t)blockIdx.x * 4; f0 < F; f0 += (int64_t)gridDim.x * 4) {
-        const int64_t f = f0 + wave;
-        int64_t base = 0, ns = 0;
-        if (f < F) {
-            base = kept_ptr[f];
-            ns = kept_ptr[f + 1] - base;
+    auto add = [&](double *p, unsigned long long tq, double term) {
+        if (fixed) atomicAdd((unsigned long long *)p, tq);
+        else unsafeAtomicAdd(p, term);
+    };
+    for (int64_t g0 = (int64_t)blockIdx.x * gf; g0 < F; g0 += (int64_t)gridDim.x * gf) {
+        // the group's SNP span and longest in-band distance (a fragment's SNPs ascend)
+        if (threadIdx.x == 0) {
+            s_lo_u = INT32_MAX;
+            s_hi_u = -1;
+            s_dist = 0;
         }
-        if (ns >= 2)
+        __syncthreads();
+        if ((int)threadIdx.x < gf && g0 + threadIdx.x < F) {
+            const int64_t k0 = kept_ptr[g0 + threadIdx.x], k1 = kept_ptr[g0 + threadIdx.x + 1];
+            if (k1 - k0 >= 2) {
+                const int32_t u0 = snp[kept_obs[k0]], u1 = snp[kept_obs[k1 - 1]];
+                atomicMin(&s_lo_u, u0);
+                atomicMax(&s_hi_u, u1);
+                atomicMax(&s_dist, band_limit == 0 ? u1 - u0 : min(u1 - u0, band_limit));
+            }
+        }
+        __syncthreads();
+        const int32_t u0 = s_lo_u, dist = s_dist;
+        const int64_t span = (int64_t)s_hi_u - u0 + 1;
+        if (span < 2) continue;                   // (uniform: no pairs in the group)
+        const bool tab = span * dist <= kPairTable;
+        if (tab)
+            for (int e = threadIdx.x; e < (int)span * dist; e += 256) s_tab[e] = 0;
+        __syncthreads();
+        for (int64_t f = g0 + wave; f < g0 + gf && f < F; f += 4) {
+            const int64_t base = kept_ptr[f], ns = kept_ptr[f + 1] - base;
+            const int64_t L = ns >= 2 ? (int64_t)linkage_k * (ns - 1) / 10 : 0;
+            if (L < 1) continue;
             for (int64_t a = lane; a < ns && a < kFragLds; a += 64) {
                 const int64_t t = kept_obs[base + a];
-                const int32_t u = snp[t];
-                su[a] = u;
+                su[a] = snp[t];
                 sm[a] = M[t];
                 sq[a] = qconf[phred[t]];
-                srb[a] = s_off[u] - s_lo[u];
             }
-        __syncthreads();
-        const int64_t L = ns >= 2 ? (int64_t)linkage_k * (ns - 1) / 10 : 0;
-        const double af = (ns >= 2 && alpha) ? alpha[f] : 1.0;
-        for (int64_t a = lane; L >= 1 && a < ns; a += 64) {
-            const bool sa = a < kFragLds;
-            const int64_t ta = sa ? 0 : kept_obs[base + a];
-            const int32_t u = sa ? su[a] : snp[ta];
-            const int Mu = sa ? sm[a] : M[ta];
-            const double qu = sa ? sq[a] : qconf[phred[ta]];
-            const int64_t rbu = sa ? srb[a] : s_off[u] - s_lo[u];
-            const int64_t bmax = a + L < ns - 1 ? a + L : ns - 1;
-            for (int64_t b = a + 1; b <= bmax; ++b) {
-                const bool sb = b < kFragLds;
-                const int64_t tb = sb ? 0 : kept_obs[base + b];
-                const int32_t v = sb ? su[b] : snp[tb];
-                const int Mv = sb ? sm[b] : M[tb];
-                const double qv = sb ? sq[b] : qconf[phred[tb]];
+            __builtin_amdgcn_wave_barrier();      // (one wave's LDS accesses complete in order)
+            const double af = alpha ? alpha[f] : 1.0;
+            int64_t a = lane, d = 1;
+            while (true) {
+                // distance d has ns - d pairs (L <= ns - 1): the lane's place among those of all distances
+                while (d <= L && a >= ns - d) {
+                    a -= ns - d;
+                    ++d;
+                }
+                if (d > L) break;
+                const int64_t b = a + d;
+                const bool sa = a < kFragLds, sb = b < kFragLds;
+                const int64_t ta = sa ? 0 : kept_obs[base + a], tb = sb ? 0 : kept_obs[base + b];
+                const int32_t u = sa ? su[a] : snp[ta], v = sb ? su[b] : snp[tb];
+                const int Mu = sa ? sm[a] : M[ta], Mv = sb ? sm[b] : M[tb];
+                const double qu = sa ? sq[a] : qconf[phred[ta]], qv = sb ? sq[b] : qconf[phred[tb]];
                 const double p_cis = qu * qv + (1.0 - qu) * (1.0 - qv);
                 const double p_trans = qu * (1.0 - qv) + (1.0 - qu) * qv;
                 const double sgn = (Mu * Mv > 0) ? 1.0 : -1.0;
@@ -562,24 +597,54 @@ __global__ __launch_bounds__(256) void k_snp_pairs(int64_t F, const int64_t *__r
                 const double tc = term < -0x1p20 ? -0x1p20 : (term > 0x1p20 ? 0x1p20 : term);
                 if (fixed && !(fabs(term) < 0x1p20)) *clamped = 1;
                 const unsigned long long tq = (unsigned long long)(long long)__builtin_rint(tc * 0x1p40);
-                auto add = [&](double *p) {
-                    if (fixed) atomicAdd((unsigned long long *)p, tq);
-                    else unsafeAtomicAdd(p, term);
-                };
                 if (band_limit == 0 || v - u <= band_limit) {
-                    add(&s_val64[rbu + v]);
-                    add(&s_val64[(sb ? srb[b] : s_off[v] - s_lo[v]) + u]);
+                    const int at = (u - u0) * dist + (v - u - 1);
+                    if (tab && fixed) atomicAdd(&s_tab[at], tq);
+                    else if (tab) unsafeAtomicAdd((double *)&s_tab[at], term);
+                    else add(&s_val64[s_off[u] - s_lo[u] + v], tq, term);
                 } else {
                     int64_t lo = l_ptr[u], hi = l_ptr[u + 1];
                     while (lo < hi) { int64_t m = (lo + hi) >> 1; if (l_col[m] < v) lo = m + 1; else hi = m; }
-                    add(&l_val64[lo]);
-                    lo = l_ptr[v]; hi = l_ptr[v + 1];
-                    while (lo < hi) { int64_t m = (lo + hi) >> 1; if (l_col[m] < u) lo = m + 1; else hi = m; }
-                    add(&l_val64[lo]);
+                    add(&l_val64[lo], tq, term);
                 }
+                a += 64;
             }
+            __builtin_amdgcn_wave_barrier();
         }
         __syncthreads();
+        if (tab)
+            for (int e = threadIdx.x; e < (int)span * dist; e += 256) {
+                const unsigned long long w = s_tab[e];
+                if (w == 0) continue;             // (+0: nothing was added, or the terms cancelled)
+                const int32_t u = u0 + e / dist, v = u + 1 + e % dist;
+                add(&s_val64[s_off[u] - s_lo[u] + v], w, __builtin_bit_cast(double, w));
+            }
+        __syncthreads();
+    }
+}
+
+// The entries (v, u), u < v, from (u, v): a wave per row v of the skyline (0 where row u does not
+// reach v, as the pair is not linked) and of the long-range CSR (whose pattern is symmetric).
+__global__ __launch_bounds__(256) void k_mirror(int64_t n, const int64_t *__restrict__ s_off,
+                                                const int32_t *__restrict__ s_lo, const int32_t *__restrict__ s_len,
+                                                double *s_val64, const int64_t *__restrict__ l_ptr,
+                                                const int32_t *__restrict__ l_col, double *l_val64) {
+    const int lane = threadIdx.x & 63;
+    for (int64_t v = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); v < n; v += (int64_t)gridDim.x * 4) {
+        const int32_t lo = s_lo[v];
+        const int64_t off = s_off[v];
+        for (int64_t u = lo + lane; u < v; u += 64) {
+            const int64_t e = v - s_lo[u];
+            s_val64[off + u - lo] = e >= 0 && e < s_len[u] ? s_val64[s_off[u] + e] : 0.0;
+        }
+        if (!l_ptr) continue;
+        for (int64_t e = l_ptr[v] + lane; e < l_ptr[v + 1]; e += 64) {
+            const int32_t u = l_col[e];
+            if (u >= v) continue;
+            int64_t a = l_ptr[u], z = l_ptr[u + 1];
+            while (a < z) { const int64_t m = (a + z) >> 1; if (l_col[m] < v) a = m + 1; else z = m; }
+            l_val64[e] = l_val64[a];
+        }
     }
 }
 
@@ -637,7 +702,8 @@ __global__ void k_quantize(int64_t n, const double *__restrict__ src, int dtype,
 // Band blocks: element (block b, column offset j, row i) = J[16b + i][bb_lo[b] + j], zero
 // outside the row's skyline range (and on the diagonal, which is zero anyway).
 // Largest |value| of an FP64 array, as the bits of a non-negative double (which order like
-// the values), reduced over the wave before one atomic.
+// the values), reduced over the workgroup before one atomic (all atomics meet on one address:
+// one per wave of a full grid took 1.8 ms on the chromosome graph's 10 M values).
 __global__ void k_absmax_bits(int64_t m, const double *__restrict__ v, unsigned long long *__restrict__ out) {
     unsigned long long hi = 0;
     for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < m; e += (int64_t)gridDim.x * blockDim.x) {
@@ -649,7 +715,13 @@ __global__ void k_absmax_bits(int64_t m, const double *__restrict__ v, unsigned 
         const unsigned long long o = __shfl_xor(hi, d);
         hi = o > hi ? o : hi;
     }
-    if ((threadIdx.x & 63) == 0 && hi) atomicMax(out, hi);
+    __shared__ unsigned long long sh[4];
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = hi;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < 4; ++w) hi = sh[w] > hi ? sh[w] : hi;
+        if (hi) atomicMax(out, hi);
+    }
 }
 
 // Exponent range of nonzero BF16 band values: ext[0] = largest biased exponent, ext[1] =
@@ -663,15 +735,27 @@ __global__ void k_band_exp_range(int64_t m, const uint16_t *__restrict__ v, int3
         hi = max(hi, ex);
         lo = min(lo, ex);
     }
-    // wave-wide max / min first: one pair of atomics per wave
+    // workgroup-wide max / min first: one pair of atomics per workgroup, of at most kReduceGroups
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) {
         hi = max(hi, __shfl_xor(hi, d));
         lo = min(lo, __shfl_xor(lo, d));
     }
-    if ((threadIdx.x & 63) == 0 && hi >= 0) {
-        atomicMax(&ext[0], hi);
-        atomicMin(&ext[1], lo);
+    __shared__ int32_t sh[2][4];
+    if ((threadIdx.x & 63) == 0) {
+        sh[0][threadIdx.x >> 6] = hi;
+        sh[1][threadIdx.x >> 6] = lo;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < 4; ++w) {
+            hi = max(hi, sh[0][w]);
+            lo = min(lo, sh[1][w]);
+        }
+        if (hi >= 0) {
+            atomicMax(&ext[0], hi);
+            atomicMin(&ext[1], lo);
+        }
     }
 }
 
@@ -1391,10 +1475,13 @@ void build_snp_graph(qh_graph *g, const qh_reads *r, const qh_snps *s, int linka
     if (n_kept) {
         DevBuf<int32_t> clamped(1);
         clamped.zero(st);
-        hipLaunchKernelGGL(k_snp_pairs, dim3(grid_for(F, 4, 1 << 20)), dim3(256), 0, st, F,
+        // fragments per workgroup: enough for the table to gather many additions, few enough that a
+        // small graph's fragments still spread over the chip
+        const int gf = (int)std::min<int64_t>(kPairFrags, std::max<int64_t>(4, F / 2048 / 4 * 4));
+        hipLaunchKernelGGL(k_snp_pairs, dim3(grid_for(F, gf, 1 << 20)), dim3(256), 0, st, F,
                            kept_obs_d.p, kept_ptr_d.p, r->snp, M.p, r->phred, r->alpha, qconf,
                            linkage_k, (int32_t)band_limit, g->s_off.p, g->s_lo.p, s_val64.p, g->l_ptr.p,
-                           g->l_col.p, l_val64.p, g->deterministic, clamped.p);
+                           g->l_col.p, l_val64.p, g->deterministic, clamped.p, gf);
         QH_CHECK_LAUNCH();
         if (g->deterministic) {
             if (download(clamped.p, 1, st)[0])
@@ -1410,6 +1497,11 @@ void build_snp_graph(qh_graph *g, const qh_reads *r, const qh_snps *s, int linka
     // master CSR
     DevBuf<int64_t> cnt(n);
     const int64_t *lp = l_nnz ? g->l_ptr.p : nullptr;
+    if (n_kept) {
+        hipLaunchKernelGGL(k_mirror, dim3(grid_for(n, 4)), dim3(256), 0, st, (int64_t)n, g->s_off.p, g->s_lo.p,
+                           g->s_len.p, s_val64.p, lp, g->l_col.p, l_val64.p);
+        QH_CHECK_LAUNCH();
+    }
     if (n) {
         hipLaunchKernelGGL(k_sky_row_nnz, dim3(grid_for(n)), dim3(256), 0, st, (int64_t)n, g->s_off.p, g->s_len.p,
                            s_val64.p, lp, l_val64.p, cnt.p);
@@ -1439,9 +1531,9 @@ void build_snp_graph(qh_graph *g, const qh_reads *r, const qh_snps *s, int linka
         DevBuf<unsigned long long> mx(1);
         mx.zero(st);
         if (slots)
-            hipLaunchKernelGGL(k_absmax_bits, dim3(grid_for(slots)), dim3(256), 0, st, slots, s_val64.p, mx.p);
+            hipLaunchKernelGGL(k_absmax_bits, dim3(grid_for(slots, 256, kReduceGroups)), dim3(256), 0, st, slots, s_val64.p, mx.p);
         if (l_nnz)
-            hipLaunchKernelGGL(k_absmax_bits, dim3(grid_for(l_nnz)), dim3(256), 0, st, l_nnz, l_val64.p, mx.p);
+            hipLaunchKernelGGL(k_absmax_bits, dim3(grid_for(l_nnz, 256, kReduceGroups)), dim3(256), 0, st, l_nnz, l_val64.p, mx.p);
         QH_CHECK_LAUNCH();
         unsigned long long bits = 0;
         QH_HIP(hipMemcpyAsync(&bits, mx.p, sizeof(bits), hipMemcpyDeviceToHost, st));
@@ -1508,7 +1600,7 @@ void build_snp_graph(qh_graph *g, const qh_reads *r, const qh_snps *s, int linka
                 const int32_t init[2] = {-1, 1 << 30};
                 DevBuf<int32_t> ext(2);
                 ext.upload(init, 2, st);
-                hipLaunchKernelGGL(k_band_exp_range, dim3(grid_for(boff[nb])), dim3(256), 0, st, boff[nb],
+                hipLaunchKernelGGL(k_band_exp_range, dim3(grid_for(boff[nb], 256, kReduceGroups)), dim3(256), 0, st, boff[nb],
                                    (const uint16_t *)g->bb_val.p, ext.p);
                 QH_CHECK_LAUNCH();
                 int32_t hl[2];

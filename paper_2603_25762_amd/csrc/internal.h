@@ -371,6 +371,44 @@ __device__ inline uint64_t sm64_draw(uint64_t seed, uint64_t k) {
     return z ^ (z >> 31);
 }
 
+// Counts of +1 and -1 spins per component (c = -1: none), one wave over vertices u0, u0 + stride,
+// ... (64 at a time): a wave adds up while its vertices stay in one component, which a
+// chromosome's do, and then adds once (an atomic per vertex on one component's counter took
+// 1.9 ms for 250,000 vertices).
+__device__ inline void count_sides(int64_t u0, int64_t stride, int64_t n, const int32_t *__restrict__ comp,
+                                   const int8_t *__restrict__ spins, int32_t *__restrict__ plus,
+                                   int32_t *__restrict__ minus) {
+    const int lane = threadIdx.x & 63;
+    int32_t cur = -1, p = 0, m = 0;
+    auto flush = [&]() {
+        if (lane == 0 && cur >= 0) {
+            if (p) atomicAdd(&plus[cur], p);
+            if (m) atomicAdd(&minus[cur], m);
+        }
+    };
+    for (; u0 < n; u0 += stride) {
+        const int64_t u = u0 + lane;
+        const int32_t c = u < n ? comp[u] : -1;
+        const bool up = c >= 0 && spins[u] > 0;
+        const unsigned long long in = __ballot(c >= 0);
+        if (!in) continue;
+        const int32_t c0 = __shfl(c, __ffsll((long long)in) - 1);
+        if (__all(c < 0 || c == c0)) {
+            if (c0 != cur) {
+                flush();
+                cur = c0;
+                p = m = 0;
+            }
+            const int np = __popcll(__ballot(up));
+            p += np;
+            m += __popcll(in) - np;
+        } else if (c >= 0) {
+            atomicAdd(up ? &plus[c] : &minus[c], 1);
+        }
+    }
+    flush();
+}
+
 SolvePlan &solve_plan(const qh_graph *g, int R, hipStream_t st);
 // Between these two calls on one thread, new plans' state buffers are collected instead of
 // cleared one by one; the end clears them all with one kernel (and synchronises st).

@@ -45,12 +45,8 @@ __global__ void k_phase_vote(int32_t n_snp, const int64_t *__restrict__ cov_ptr,
 
 __global__ void k_comp_sizes(int64_t n, const int32_t *__restrict__ comp, const int8_t *__restrict__ spins,
                              int32_t *__restrict__ plus, int32_t *__restrict__ minus) {
-    for (int64_t u = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; u < n;
-         u += (int64_t)gridDim.x * blockDim.x) {
-        int c = comp[u];
-        if (c < 0) continue;
-        if (spins[u] > 0) atomicAdd(&plus[c], 1); else atomicAdd(&minus[c], 1);
-    }
+    const int64_t w = (int64_t)blockIdx.x * (blockDim.x / 64) + threadIdx.x / 64;
+    count_sides(w * 64, (int64_t)gridDim.x * blockDim.x, n, comp, spins, plus, minus);
 }
 
 __global__ void k_phase_parity(int64_t n, const int32_t *__restrict__ comp, const int8_t *__restrict__ spins,
@@ -111,7 +107,7 @@ void phase_noalloc(const qh_graph *g, const int8_t *spins, int8_t *h1, int32_t *
     // the counters keep the previous call's values: clear them (a kernel, so that a captured
     // stream records no memset node)
     hipLaunchKernelGGL(k_zero_counts, dim3(grid_for(2 * nc)), dim3(256), 0, st, 2 * nc, cnt);
-    hipLaunchKernelGGL(k_comp_sizes, dim3(grid_for(g->n)), dim3(256), 0, st, g->n, g->comp.p, spins, cnt, cnt + nc);
+    hipLaunchKernelGGL(k_comp_sizes, dim3(std::min(grid_for(g->n), 256)), dim3(256), 0, st, g->n, g->comp.p, spins, cnt, cnt + nc);
     hipLaunchKernelGGL(k_phase_parity, dim3(grid_for(g->n)), dim3(256), 0, st, g->n, g->comp.p, spins, cnt, cnt + nc,
                        g->init_h1.p, h1, block);
     QH_CHECK_LAUNCH();
@@ -128,7 +124,7 @@ void phase(const qh_graph *g, const int8_t *spins, int8_t *h1, int32_t *block, h
     if (!g->n) return;
     DevBuf<int32_t> cnt(2 * std::max<int64_t>(g->n_comp, 1));
     cnt.zero(st);
-    hipLaunchKernelGGL(k_comp_sizes, dim3(grid_for(g->n)), dim3(256), 0, st, g->n, g->comp.p, spins, cnt.p,
+    hipLaunchKernelGGL(k_comp_sizes, dim3(std::min(grid_for(g->n), 256)), dim3(256), 0, st, g->n, g->comp.p, spins, cnt.p,
                        cnt.p + std::max<int64_t>(g->n_comp, 1));
     hipLaunchKernelGGL(k_phase_parity, dim3(grid_for(g->n)), dim3(256), 0, st, g->n, g->comp.p, spins, cnt.p,
                        cnt.p + std::max<int64_t>(g->n_comp, 1), g->init_h1.p, h1, block);
@@ -187,12 +183,9 @@ __global__ void k_comp_sizes_batched(const PhaseDesc *__restrict__ D, const int2
                                      const int8_t *__restrict__ spins, int32_t *__restrict__ cnt) {
     const int2 it = items[blockIdx.x];
     const PhaseDesc &d = D[it.x];
-    const int64_t u = (int64_t)it.y + threadIdx.x;
-    if (u >= d.n) return;
-    const int c = d.comp[u];
-    if (c < 0) return;
     int32_t *plus = cnt + d.cnt_off, *minus = plus + d.n_cnt;
-    if (spins[d.spin_off + u] > 0) atomicAdd(&plus[c], 1); else atomicAdd(&minus[c], 1);
+    const int64_t u0 = (int64_t)it.y + threadIdx.x / 64 * 64;
+    count_sides(u0, d.n, d.n, d.comp, spins + d.spin_off, plus, minus);   // (64 vertices)
 }
 
 __global__ void k_phase_parity_batched(const PhaseDesc *__restrict__ D, const int2 *__restrict__ items,

@@ -130,16 +130,43 @@ __device__ inline void cut_chunks_body(int64_t bx, int64_t gx, int64_t n_chunks,
     }
 }
 
-// cut_rc[r][c] = sum of the component's chunk partials, chunks in order
+// cut_rc[r][c] = sum of the component's chunk partials, chunks in order; a workgroup item is one
+// component and kReduceR replicas.  A component of more than kStage chunks stages them through LDS, so
+// that the partials arrive with all threads' loads in flight and the serial sum reads LDS: a
+// chromosome's 7,813 chunks took 1.25 ms as a chain of loads.
+constexpr int kStage = 64;
+constexpr int kStageElems = 4096;
+constexpr int kReduceR = 16;
+__host__ __device__ inline int reduce_blocks(int R) { return (R + kReduceR - 1) / kReduceR; }
 __device__ inline void cut_reduce_body(int64_t bx, int64_t gx, int64_t n_comp, int R,
                                        const int32_t *__restrict__ comp_chunk_ptr, const double *__restrict__ part,
                                        double *__restrict__ cut_rc) {
-    for (int64_t c = bx; c < n_comp; c += gx)
-        for (int r = threadIdx.x; r < R; r += blockDim.x) {
-            double acc = 0.0;
-            for (int ch = comp_chunk_ptr[c]; ch < comp_chunk_ptr[c + 1]; ++ch) acc += part[(int64_t)ch * R + r];
-            cut_rc[(int64_t)r * n_comp + c] = acc;
+    __shared__ double sh[kStageElems];
+    const int nrb = reduce_blocks(R);
+    for (int64_t it = bx; it < n_comp * nrb; it += gx) {
+        const int64_t c = it / nrb;
+        const int r0 = (int)(it - c * nrb) * kReduceR, rb = min(R - r0, kReduceR);   // this item's replicas
+        const int ch0 = comp_chunk_ptr[c], ch1 = comp_chunk_ptr[c + 1];
+        double acc = 0.0;
+        if (ch1 - ch0 <= kStage) {
+            if ((int)threadIdx.x < rb)
+                for (int ch = ch0; ch < ch1; ++ch) acc += part[(int64_t)ch * R + r0 + threadIdx.x];
+        } else {
+            const int nst = min(kStageElems / rb, 1024);                 // chunks per stage
+            for (int b = ch0; b < ch1; b += nst) {
+                const int m = min(nst, ch1 - b);
+                __syncthreads();
+                for (int e = threadIdx.x; e < m * rb; e += blockDim.x)
+                    sh[e] = part[(int64_t)(b + e / rb) * R + r0 + e % rb];
+                __syncthreads();
+                if ((int)threadIdx.x < rb) {
+#pragma unroll 8
+                    for (int ch = 0; ch < m; ++ch) acc += sh[ch * rb + threadIdx.x];
+                }
+            }
         }
+        if ((int)threadIdx.x < rb) cut_rc[(int64_t)(r0 + threadIdx.x) * n_comp + c] = acc;
+    }
 }
 
 __device__ inline void select_body(int64_t bx, int64_t gx, int64_t n_comp, int R, const double *__restrict__ cut_rc,
@@ -383,7 +410,7 @@ void readout(const ReadoutView &g, SolvePlan &p, int R, const float *xfin, const
                            g.m_ptr, g.m_col, g.m_val, p.spins.p, p.rowcut.p);
         hipLaunchKernelGGL(k_cut_chunks, dim3(grid_for(g.n_chunks * R)), dim3(256), 0, st, g.n_chunks, R,
                            g.chunk_begin, g.chunk_end, p.rowcut.p, p.part.p);
-        hipLaunchKernelGGL(k_cut_reduce, dim3((unsigned)std::min<int64_t>(nc, 1 << 20)), dim3(256), 0, st, nc, R,
+        hipLaunchKernelGGL(k_cut_reduce, dim3((unsigned)std::min<int64_t>(nc * reduce_blocks(R), 1 << 20)), dim3(256), 0, st, nc, R,
                            g.comp_chunk_ptr, p.part.p, p.cut_rc.p);
         hipLaunchKernelGGL(k_select, dim3(grid_for(nc)), dim3(256), 0, st, nc, R, p.cut_rc.p, p.best_r.p);
         hipLaunchKernelGGL(k_replica_totals, dim3(grid_for(R)), dim3(256), 0, st, nc, R, p.cut_rc.p, res->cuts);
@@ -461,7 +488,7 @@ void readout(const ReadoutView &g, SolvePlan &p, int R, const float *xfin, const
                            g.m_ptr, g.m_col, g.m_val, res->best_spins, p.rowcut.p);
         hipLaunchKernelGGL(k_cut_chunks, dim3(grid_for(g.n_chunks)), dim3(256), 0, st, g.n_chunks, 1,
                            g.chunk_begin, g.chunk_end, p.rowcut.p, p.part1.p);
-        hipLaunchKernelGGL(k_cut_reduce, dim3((unsigned)std::min<int64_t>(nc, 1 << 20)), dim3(64), 0, st, nc, 1,
+        hipLaunchKernelGGL(k_cut_reduce, dim3((unsigned)std::min<int64_t>(nc, 1 << 20)), dim3(256), 0, st, nc, 1,
                            g.comp_chunk_ptr, p.part1.p, p.cut1.p);
         hipLaunchKernelGGL(k_selected_total, dim3(1), dim3(256), 0, st, nc, p.cut1.p, (const int32_t *)nullptr,
                            res->best_cut);
@@ -649,7 +676,7 @@ void readout_batched(const std::vector<ReadoutDesc> &descs_in, int R, bool greed
     fill(kSigns, [&](const ReadoutDesc &d) { return grid_for(d.n * R); });
     fill(kRowsR, [&](const ReadoutDesc &d) { return grid_for(d.n_ord * rows_threads(R)); });
     fill(kChunksR, [&](const ReadoutDesc &d) { return grid_for(d.n_chunks * R); });
-    fill(kReduce, [&](const ReadoutDesc &d) { return (int)std::max<int64_t>(1, std::min<int64_t>(d.n_comp, 1 << 20)); });
+    fill(kReduce, [&](const ReadoutDesc &d) { return (int)std::max<int64_t>(1, std::min<int64_t>(d.n_comp * reduce_blocks(R), 1 << 20)); });
     fill(kComp, [&](const ReadoutDesc &d) { return grid_for(d.n_comp); });
     fill(kOne, [&](const ReadoutDesc &) { return 1; });
     fill(kVert, [&](const ReadoutDesc &d) { return grid_for(d.n); });
@@ -692,7 +719,7 @@ void readout_batched(const std::vector<ReadoutDesc> &descs_in, int R, bool greed
     }
     if (total(kRows1)) hipLaunchKernelGGL(kb_cut_rows, dim3(total(kRows1)), dim3(256), 0, st, T, W, nb, R, 1);
     if (total(kChunks1)) hipLaunchKernelGGL(kb_cut_chunks, dim3(total(kChunks1)), dim3(256), 0, st, T, W, nb, R, 1);
-    hipLaunchKernelGGL(kb_cut_reduce, dim3(total(kReduce)), dim3(64), 0, st, T, W, nb, R, 1);
+    hipLaunchKernelGGL(kb_cut_reduce, dim3(total(kReduce)), dim3(256), 0, st, T, W, nb, R, 1);
     hipLaunchKernelGGL(kb_totals, dim3(total(kOne)), dim3(256), 0, st, T, W, nb, R, 1);
     QH_CHECK_LAUNCH();
     int32_t badb = 0;

@@ -28,12 +28,8 @@ namespace qh {
 
 __global__ void k_ref_counts(int64_t n, const int32_t *__restrict__ comp, const int8_t *__restrict__ s,
                              int32_t *__restrict__ plus, int32_t *__restrict__ minus) {
-    for (int64_t u = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; u < n; u += (int64_t)gridDim.x * blockDim.x) {
-        const int c = comp[u];
-        if (c < 0) continue;
-        if (s[u] > 0) atomicAdd(&plus[c], 1);
-        else atomicAdd(&minus[c], 1);
-    }
+    const int64_t w = (int64_t)blockIdx.x * (blockDim.x / 64) + threadIdx.x / 64;
+    count_sides(w * 64, (int64_t)gridDim.x * blockDim.x, n, comp, s, plus, minus);
 }
 
 // active[c]: 0 = component left alone this round, else the spin value of its S_min
@@ -168,7 +164,7 @@ void refine(qh_graph *g, const qh_bsb_opts *o, int max_rounds, float deform, int
                 QH_HIP(hipStreamSynchronize(st));   // tk is reused by the next attempt
             }
             cnt.zero(st);
-            hipLaunchKernelGGL(k_ref_counts, dim3(grid_of(n)), dim3(256), 0, st, n, g->comp.p, best.p, cnt.p,
+            hipLaunchKernelGGL(k_ref_counts, dim3(std::min(grid_of(n), 256)), dim3(256), 0, st, n, g->comp.p, best.p, cnt.p,
                                cnt.p + nc);
             QH_CHECK_LAUNCH();
             QH_HIP(hipMemcpyAsync(pm.data(), cnt.p, 2 * nc * sizeof(int32_t), hipMemcpyDeviceToHost, st));

@@ -1519,3 +1519,61 @@ def test_dense_one_launch_equals_per_step(reads, snps, span, R, order, dtype):
     assert g.plan_info(R)["plan_used"] == 2
     for a, b in zip(*out):
         assert torch.equal(a, b)
+
+
+def _pair_reads(kind, seed=8):
+    """Reads of the SNP pair sums' edges: "sorted" 40,000 reads of 2-9 SNPs in order (workgroups of
+    16 whose sums fit the LDS table), "shuffled" the same in no order (they do not), "long" reads of
+    127-300 SNPs around the 128 that a wave stages, "interleaved" pairs (u, u + 3)."""
+    rng = np.random.default_rng(seed)
+    n = 420
+    if kind == "interleaved":
+        first, count, step = np.arange(n - 3), np.full(n - 3, 2), 3
+    elif kind == "long":
+        count = np.array([127, 128, 129, 190, 300, 2])
+        first, step = np.sort(rng.integers(0, n - count.max(), count.size)), 1
+    else:
+        count, step = rng.integers(2, 10, 40000), 1
+        first = rng.integers(0, n - count)
+        o = np.argsort(first, kind="stable")
+        first, count = (first[o], count[o]) if kind == "sorted" else (first, count)
+    w = synth.snp_small(seed, n_snp=n)
+    w.frag_ptr = np.concatenate([[0], np.cumsum(count)]).astype(np.int64)
+    t = np.arange(w.frag_ptr[-1]) - np.repeat(w.frag_ptr[:-1], count)
+    w.snp = (np.repeat(first, count) + step * t).astype(np.int32)
+    w.allele = rng.integers(0, 2, w.snp.size).astype(w.allele.dtype)
+    w.phred = rng.integers(5, 40, w.snp.size).astype(np.uint8)
+    w.alpha = None
+    return w
+
+
+@pytest.mark.parametrize("kind,k,band", [("sorted", 10, 0), ("sorted", 3, 2), ("shuffled", 10, 0),
+                                         ("long", 10, 0), ("long", 2, 30), ("interleaved", 10, 0)])
+@pytest.mark.parametrize("fixed", [False, True])
+def test_snp_pair_sums(kind, k, band, fixed):
+    """Eq. (14) sums of grouped, staged and mirrored pairs against the oracle: 1e-12 of the summed
+    |terms|, and in fixed-point mode 2^-41 per term of an entry (at most the deepest SNP's reads)."""
+    w = _pair_reads(kind)
+    g = qh.build_graph(*(qh.to_device(a) for a in (w.frag_ptr, w.snp, w.allele, w.phred, w.init_h1)),
+                       kind="snp_llr", dtype="f32", linkage_k=k, band_limit=band, deterministic=fixed)
+    go = oracle_graph(w, "snp_llr", k)
+    D = cpu(g.export_rows(0, go.n))
+    tol = 1e-12 * snp_abs_terms(w, k) + (np.bincount(w.snp).max() * 2.0 ** -41 if fixed else 0.0)
+    assert np.all(np.abs(D - go.dense()) <= tol)
+    assert np.array_equal(D, D.T)
+    # one spin set per component, its sides counted over whole waves and mixed ones
+    comp, nc = oracle.components(go)
+    s = np.where(np.random.default_rng(2).random(go.n) < 0.4, 1, -1).astype(np.int8)
+    h1, blk = qh.phase(g, torch.tensor(s, device="cuda"))
+    ho, bo = oracle.phase_parity(comp, nc, s, w.init_h1)
+    assert np.array_equal(cpu(h1), ho) and np.array_equal(cpu(blk), bo)
+
+
+@pytest.mark.parametrize("R", [16, 64])
+def test_readout_component_of_many_chunks(R):
+    """A component of 282 chunks of 32 vertices: staged sums of several stages."""
+    _readout_case(synth.snp_small(23, n_snp=9000), "snp_llr", R, 4, False)
+
+
+def test_readout_integer_component_of_many_chunks():
+    _readout_case(synth.read_small(24, n_snp=2500, n_reads=2300, span=(10, 40)), "read_signed", 32, 5, True)
