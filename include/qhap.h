@@ -350,18 +350,21 @@ qh_status qh_autotune(const qh_graph *g, const qh_bsb_opts *opts, qh_bsb_opts *c
  * bit for bit.  R must be 16, 32 or 64; init = 1; the whole schedule; no long-range
  * couplings; each graph at most once per batch.  opts->plan: 1 = one launch per step over
  * work items of every block (a dense row tile, or four band blocks); 2 = one persistent
- * launch with whole blocks per workgroup (longest-processing-time placement); 0 = time
- * both on this batch (8 steps each) and cache the faster for this list of graphs and R.
+ * launch with whole blocks per workgroup (longest-processing-time placement); 0 = blocks
+ * whose state and couplings fit on chip run all steps in one launch per class (storage x
+ * dtype), as teams of workgroups; for the others both plans are timed on this batch (8 steps
+ * each) and the faster is cached for this list of graphs and R.
  * Results are packed: block b's vertices start at vertex_offset[b] (= sum of the
  * previous blocks' n) in best_spins / x / y, and its replicas at b * R in cuts.
  *  best_spins int8 [sum n]; cuts double [n_blocks * R]; best_cut double [n_blocks];
  *  selected_cut double [n_blocks] (optional); x, y optional float [sum n * R];
- *  plan_used (host output) the plan that ran.  Greedy is applied per block when
- *  requested.  opts->use_graph = 1 runs the per-step plan from a captured hipGraph: the step
+ *  plan_used (host output) the plan that ran (plan 0: the plan of the blocks that do not run as
+ *  teams, 1 when all do).  Greedy is applied per block when requested.  opts->use_graph = 1 runs the per-step plan from a captured hipGraph: the step
  *  launches are captured once per list of graphs, R and schedule (steps, dt, a0, pump, seed)
  *  and replayed by later calls with the same ones (the library keeps the last few batches);
  *  results are those of plan 1, bit for bit.  use_graph with plan 2 is EUNSUPPORTED, and
- *  plan 0 with use_graph runs plan 1 without tuning.  eval_every must be 0.  readout = 0
+ *  plan 0 with use_graph runs plan 1 without tuning for the blocks that are not teams (whose
+ *  launches cannot be captured and are enqueued on every call).  eval_every must be 0.  readout = 0
  *  runs the dynamics only (the result arrays other than x and y may then be NULL).
  *  Synchronises the stream. */
 typedef struct {

@@ -14,7 +14,8 @@ LIB = os.path.join(OUT_DIR, "libqhap.so")
 OBJ_DIR = os.path.join(ROOT, "_build", "qhap")
 
 SOURCES = ["api.hip", "graph_build.hip", "bsb.hip", "bsb_persistent.hip", "bsb_persistent_field.hip", "band_persistent.hip",
-           "band_persistent_discrete.hip", "strip_persistent.hip", "strip_persistent_discrete.hip", "phase.hip", "batched.hip", "refine.hip", "readout.hip", "memory.hip"]
+           "band_persistent_discrete.hip", "strip_persistent.hip", "strip_persistent_discrete.hip", "phase.hip", "batched.hip",
+           "batched_persistent.hip", "refine.hip", "readout.hip", "memory.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",

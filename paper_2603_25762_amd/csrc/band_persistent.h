@@ -10,6 +10,10 @@ constexpr int kBpWaves = 8;                  // waves per workgroup (two per SIM
 constexpr int kBpThreads = 64 * kBpWaves;
 constexpr int kBpPadRows = 32;               // LDS rows past the last held row (read-ahead, never used)
 
+// DT values of the band kernel: a storage type of band blocks, or the FP32 tiles of a dense graph,
+// whose 16-row strips are band blocks over whole tiles
+constexpr int kBpTiles = 100;
+
 // One graph of a launch.
 struct BandTeam {
     const int64_t *bb_off;
@@ -89,8 +93,39 @@ struct BandPersist {
     DevBuf<int> flags;          // n_flags counters, then the error word
 };
 
+constexpr int64_t kBpLdsLimit = 160 * 1024;
+constexpr int kSpPadRows = kTile;   // strip kernel: LDS rows past the last held row (read-ahead, never used)
+// LDS of a workgroup that holds `rows` rows of rt replicas
+inline int64_t band_lds_bytes(int64_t rows, int rt, bool strips) {
+    return strips ? (rows + kSpPadRows) * rt * 2 : (rows + kBpPadRows) * rt * 4;
+}
+int band_held_chunks(int dtype, int um, bool strips);
+double band_step_us(double quads, double past, int64_t blocks, int wpg, int rt, bool strips);
+
 BandSplit split_band(const int32_t *bb_lo, const int32_t *bb_w, int64_t n_bblk, int wpg);
 bool build_band_plan(const qh_graph *g, SolvePlan &p, BandPersist &bp, hipStream_t st);
+// The blocks of a batch that run as teams of the persistent kernels, and their launches.
+struct BatchTeams {
+    struct Launch {
+        BandLaunch launch;      // (jobs and job_ptr unused: the tables below)
+        int64_t ptr_at = 0;     // its workgroups' pointers in ptr
+        double us = 0.0;        // estimated time of a step of all its teams
+    };
+    std::vector<char> in;       // blocks
+    std::vector<Launch> launches;
+    DevBuf<int32_t> geo, ptr;
+    DevBuf<int64_t> off;
+    DevBuf<uint64_t> tiles;
+    DevBuf<BandTeam> teams;
+    DevBuf<BandJob> jobs;
+    DevBuf<float> xch;
+    DevBuf<int> flags;          // n_flags counters, then the error word
+    int64_t n_flags = 0;
+};
+void plan_batch_teams(const qh_graph *const *gs, const std::vector<SolvePlan *> &plans,
+                      const std::vector<BlockDesc> &desc, const qh_bsb_opts *o, BatchTeams &bt, hipStream_t st);
+void run_batch_teams(BatchTeams &bt, const qh_bsb_opts *o, double a0, const float *pump, hipStream_t st);
+
 void launch_band(const BandLaunch &bl, const BandPersistArgs &a, int discrete, hipStream_t st);
 void launch_band_plain(const BandLaunch &bl, const BandPersistArgs &a, hipStream_t st);
 void launch_band_discrete(const BandLaunch &bl, const BandPersistArgs &a, hipStream_t st);

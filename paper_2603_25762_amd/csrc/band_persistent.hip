@@ -7,8 +7,6 @@
 
 namespace qh {
 
-static constexpr int64_t kBpLdsLimit = 160 * 1024;
-
 // Contiguous parts of the band blocks, as even as possible, with the rows each part holds, the
 // blocks that reach past its own rows, the blocks its neighbours reach, and the neighbour range
 // (made symmetric: "reads from" and "is read by" together).
@@ -66,7 +64,7 @@ BandSplit split_band(const int32_t *bb_lo, const int32_t *bb_w, int64_t n_bblk, 
 }
 
 // whole chunks of 16 columns that the kernel variant keeps in registers per block (strip)
-static int held_chunks(int dtype, int um, bool strips) {
+int band_held_chunks(int dtype, int um, bool strips) {
     if (strips) return kSpRegs / um / sp_tile_regs(dtype) * (kTile / 16);
     return dtype == kBpTiles ? 32 / um : (dtype == QH_F32 ? 32 : 48) / um - 1;
 }
@@ -101,12 +99,21 @@ static int units_variant(int64_t blocks) {
     return u <= 1 ? 1 : u <= 2 ? 2 : u <= 4 ? 4 : u <= 8 ? 8 : 0;
 }
 
+// Estimated time of a step of one team, us: `blocks` band blocks (strips) per workgroup, `quads` of
+// columns each, `past` chunks of 16 columns of a block read from memory.  Fitted to measured
+// steps (f16, estimate / measured): 0.9 for a step's barriers and latencies; per band block of
+// a SIMD 0.0195 per MFMA and 0.12; 1.8 for the exchange with neighbours; 0.25 per chunk read from
+// memory.  2,001 SNPs, R = 128: 3.1 / 3.4; 7,768 SNPs, F32, 36 quads wide, R = 128: 5.7 / 5.8;
+// 100,000 SNPs, R = 64: 12.4 / 12.4; 250,000: 27.7 / 28.7.
+double band_step_us(double quads, double past, int64_t blocks, int wpg, int rt, bool strips) {
+    const double units = std::max(1.0, (double)blocks / 4.0);      // per SIMD
+    const double unit = strips ? quads / 16.0 * ((rt / 16) * 0.04 + 0.02) + 0.2 + past * 0.1
+                               : quads * (rt / 16) * 0.0195 + 0.12 + past * 0.25;
+    return 0.9 + units * unit + (wpg > 1 ? 1.8 : 0.0);
+}
+
 // Chooses replicas per group, workgroups per graph and the kernel variant for one graph by the
-// estimated time of a step, fitted to measured ones (f16, us per step, estimate / measured):
-// 0.9 for a step's barriers and latencies; per band block of a SIMD 0.0195 per MFMA and 0.12;
-// 1.8 for the exchange with neighbours; 0.25 per chunk of 16 columns read from memory; times
-// the passes that the replica groups take.  2,001 SNPs, R = 128: 3.1 / 3.4; 7,768 SNPs, F32,
-// 36 quads wide, R = 128: 5.7 / 5.8; 100,000 SNPs, R = 64: 12.4 / 12.4; 250,000: 27.7 / 28.7.
+// estimated time of a step times the passes that the replica groups take.
 // The per-step kernels take their state's traffic at 4.6 TB/s and a launch, or the latency of
 // walking the band (2,001 SNPs 8.8, 7,768 SNPs 17.2, 250,000 56.6 measured); the plan has to
 // beat that by a tenth.
@@ -144,14 +151,11 @@ bool build_band_plan(const qh_graph *g, SolvePlan &p, BandPersist &bp, hipStream
             const int wpg = (int)ceil_div(nb, bpw);
             if (wpg > n_cu || (bpw > 1 && (int)ceil_div(nb, bpw - 1) == wpg)) continue;
             const int um = units_variant(ceil_div(nb, wpg));
-            const int held = held_chunks(dtype, um, strips);
+            const int held = band_held_chunks(dtype, um, strips);
             double past = 0.0;
             for (int32_t w : wd) past += std::max(0, w / 16 - held);
             const int slots = std::min(ng, n_cu / wpg), passes = (int)ceil_div(ng, slots);
-            const double units = std::max(1.0, (double)ceil_div(nb, wpg) / 4.0);      // per SIMD
-            const double unit = strips ? quads / 16.0 * ((rt / 16) * 0.04 + 0.02) + 0.2 + past / nb * 0.1
-                                       : quads * (rt / 16) * 0.0195 + 0.12 + past / nb * 0.25;
-            const double us = 0.9 + units * unit + (wpg > 1 ? 1.8 : 0.0);
+            const double us = band_step_us(quads, past / nb, ceil_div(nb, wpg), wpg, rt, strips);
             cands.push_back({us * passes, rt, wpg, um, slots, passes});
         }
     }
@@ -161,7 +165,7 @@ bool build_band_plan(const qh_graph *g, SolvePlan &p, BandPersist &bp, hipStream
     for (const Cand &c : cands) {
         if (c.us > 0.9 * step_us) break;
         BandSplit s = split_band(lo.data(), wd.data(), nb, c.wpg);
-        const int64_t lds = strips ? (s.lds_rows + kSpPadRows) * c.rt * 2 : (s.lds_rows + kBpPadRows) * c.rt * 4;
+        const int64_t lds = band_lds_bytes(s.lds_rows, c.rt, strips);
         if (lds > kBpLdsLimit || units_variant(s.max_blocks) != c.um) continue;
         BandLaunch &bl = bp.launch;
         bl = BandLaunch{};

@@ -121,10 +121,6 @@ __device__ inline void bp_wait(const BandPersistArgs &a, const int *flags, int n
     }
 }
 
-// DT values of this kernel: a storage type of band blocks, or the FP32 tiles of a dense graph,
-// whose 16-row strips are band blocks over whole tiles
-constexpr int kBpTiles = 100;
-
 // couplings of one chunk of 16 columns: four MFMA A operands (quads of four columns), two per
 // register in 16-bit types
 template <int DT>

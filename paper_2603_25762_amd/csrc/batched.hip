@@ -9,8 +9,9 @@
 //    longest-processing-time rule on estimated bytes per step; the steps of a block are
 //    separated by workgroup barriers only.  Best when every block is small.
 //
-// Plan 0 times both on the batch (a few steps each) and caches the faster for that list of
-// graphs and replica count.  Either way the arithmetic and its order are those of the
+// Plan 0 first gives the blocks that the persistent kernels hold on chip to teams of workgroups
+// (batched_persistent.hip); for the rest it times both plans (a few steps each) and caches the
+// faster for that list of graphs and replica count.  Either way the arithmetic and its order are those of the
 // single-graph kernels, so block b's result equals qh_bsb_solve on graph b, bit for bit.
 #include <algorithm>
 #include <map>
@@ -19,7 +20,7 @@
 #include <queue>
 #include <vector>
 
-#include "internal.h"
+#include "band_persistent.h"
 
 namespace qh {
 
@@ -147,13 +148,30 @@ void bsb_solve_batched(const qh_graph *const *gs, int nb, const qh_bsb_opts *o, 
         }
     }
 
-    std::vector<double> cost(nb);
-    for (int b = 0; b < nb; ++b) cost[b] = block_cost(gs[b], R);
-    std::vector<int> order(nb);
+    // plan 0: the blocks that the persistent kernels take as teams of workgroups (a cooperative launch
+    // cannot be recorded into a graph of the caller's); the rest below.  The teams' blocks come
+    // last in the block table.
+    BatchTeams bt;
+    bt.in.assign(nb, 0);
+    if (o->plan == 0 && o->steps > 0 && !stream_capturing(st)) plan_batch_teams(gs, plans, desc, o, bt, st);
+    std::vector<int> rest;
+    std::vector<BlockDesc> table;
+    for (int b = 0; b < nb; ++b)
+        if (!bt.in[b]) {
+            rest.push_back(b);
+            table.push_back(desc[b]);
+        }
+    const int nr = (int)rest.size();
+    for (int b = 0; b < nb; ++b)
+        if (bt.in[b]) table.push_back(desc[b]);
+
+    std::vector<double> cost(nr);
+    for (int b = 0; b < nr; ++b) cost[b] = block_cost(gs[rest[b]], R);
+    std::vector<int> order(nr);
     std::iota(order.begin(), order.end(), 0);
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return cost[a] > cost[b]; });
     DevBuf<BlockDesc> d_desc(nb);
-    QH_HIP(hipMemcpyAsync(d_desc.p, desc.data(), nb * sizeof(BlockDesc), hipMemcpyHostToDevice, st));
+    QH_HIP(hipMemcpyAsync(d_desc.p, table.data(), nb * sizeof(BlockDesc), hipMemcpyHostToDevice, st));
 
     // per-step plan: work items grouped by class (storage x dtype); within a class the blocks
     // are spread over the XCDs by the longest-processing-time rule on their bytes per step
@@ -163,16 +181,11 @@ void bsb_solve_batched(const qh_graph *const *gs, int nb, const qh_bsb_opts *o, 
     std::vector<int2> items;
     int64_t class_ptr[kBatchClasses + 1] = {0};
     std::vector<XcdSplit> splits(kBatchClasses);
-    auto class_of = [](const qh_graph *g) {
-        if (g->storage == QH_STORE_DENSE)
-            return g->dtype == QH_F32 ? 0 : g->dtype == QH_F16 ? 1 : g->dtype == QH_BF16 ? 2 : 3;
-        return g->bb_dtype == QH_F32 ? 4 : g->bb_dtype == QH_F16 ? 5 : 6;
-    };
     for (int c = 0; c < kBatchClasses; ++c) {
         std::vector<std::vector<int32_t>> lists(kXcds);
         double load[kXcds] = {0};
         for (int b : order) {
-            if (class_of(gs[b]) != c) continue;
+            if (batch_class(gs[rest[b]]) != c) continue;
             const int x = (int)(std::min_element(load, load + kXcds) - load);
             load[x] += cost[b];
             lists[x].push_back(b);
@@ -181,7 +194,7 @@ void bsb_solve_batched(const qh_graph *const *gs, int nb, const qh_bsb_opts *o, 
         xs.off[0] = 0;
         for (int x = 0; x < kXcds; ++x) {
             for (int b : lists[x]) {
-                const qh_graph *g = gs[b];
+                const qh_graph *g = gs[rest[b]];
                 const int64_t m = g->storage == QH_STORE_DENSE ? g->n_rt : ceil_div(g->n_bblk, 4);
                 for (int64_t i = 0; i < m; ++i) items.push_back(make_int2(b, (int)i));
             }
@@ -197,7 +210,7 @@ void bsb_solve_batched(const qh_graph *const *gs, int nb, const qh_bsb_opts *o, 
     // whole-block plan: longest-processing-time placement of blocks on workers
     int cus = 0;
     QH_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    const int workers = (int)std::min<int64_t>(nb, (int64_t)std::max(cus, 1) * batched_workers_per_cu(R));
+    const int workers = (int)std::min<int64_t>(nr, (int64_t)std::max(cus, 1) * batched_workers_per_cu(R));
     using Load = std::pair<double, int>;
     std::priority_queue<Load, std::vector<Load>, std::greater<Load>> heap;
     for (int w = 0; w < workers; ++w) heap.push({0.0, w});
@@ -209,19 +222,19 @@ void bsb_solve_batched(const qh_graph *const *gs, int nb, const qh_bsb_opts *o, 
         heap.push({l.first + cost[b], l.second});
     }
     std::vector<int32_t> sptr(workers + 1, 0), sched;
-    sched.reserve(nb);
+    sched.reserve(nr);
     for (int w = 0; w < workers; ++w) {
         sched.insert(sched.end(), lists[w].begin(), lists[w].end());
         sptr[w + 1] = (int32_t)sched.size();
     }
-    DevBuf<int32_t> d_sptr(workers + 1), d_sched(nb);
+    DevBuf<int32_t> d_sptr(workers + 1), d_sched(nr);
     QH_HIP(hipMemcpyAsync(d_sptr.p, sptr.data(), (workers + 1) * sizeof(int32_t), hipMemcpyHostToDevice, st));
-    QH_HIP(hipMemcpyAsync(d_sched.p, sched.data(), nb * sizeof(int32_t), hipMemcpyHostToDevice, st));
+    if (nr) QH_HIP(hipMemcpyAsync(d_sched.p, sched.data(), nr * sizeof(int32_t), hipMemcpyHostToDevice, st));
 
     auto run = [&](int plan, int steps, uint64_t seed) {
         if (plan == 2) launch_batched(R, workers, d_desc.p, d_sptr.p, d_sched.p, steps, (float)o->dt, (float)a0, pump,
                                       seed, st);
-        else launch_batched_steps(R, nb, d_desc.p, d_items.p, class_ptr, splits.data(), steps, (float)o->dt,
+        else launch_batched_steps(R, nr, d_desc.p, d_items.p, class_ptr, splits.data(), steps, (float)o->dt,
                                   (float)a0, pump, seed, st);
     };
     // use_graph: the per-step plan replayed from a captured hipGraph.  The capture reads the
@@ -229,10 +242,10 @@ void bsb_solve_batched(const qh_graph *const *gs, int nb, const qh_bsb_opts *o, 
     // it on every call (same graphs and R: same layout), so a replay sees this call's c0,
     // variant and field.
     auto run_captured = [&](int steps, uint64_t seed) {
-        std::vector<uint64_t> key(nb + 2);
-        for (int b = 0; b < nb; ++b) key[b] = gs[b]->serial;
-        key[nb] = (uint64_t)R;
-        key[nb + 1] = (uint64_t)dev;
+        std::vector<uint64_t> key(nr + 2);
+        for (int b = 0; b < nr; ++b) key[b] = gs[rest[b]]->serial;
+        key[nr] = (uint64_t)R;
+        key[nr + 1] = (uint64_t)dev;
         std::lock_guard<std::mutex> lk(g_plan_mu);
         CapturedBatch *cb = nullptr;
         for (size_t i = 0; i < g_captured.size(); ++i)
@@ -244,7 +257,7 @@ void bsb_solve_batched(const qh_graph *const *gs, int nb, const qh_bsb_opts *o, 
         if (!cb) {
             cb = new CapturedBatch();
             cb->key = key;
-            cb->desc.alloc(nb);
+            cb->desc.alloc(nr);
             cb->items.alloc(std::max<int64_t>(n_items, 1));
             if (n_items)
                 QH_HIP(hipMemcpyAsync(cb->items.p, items.data(), n_items * sizeof(int2), hipMemcpyHostToDevice, st));
@@ -260,7 +273,7 @@ void bsb_solve_batched(const qh_graph *const *gs, int nb, const qh_bsb_opts *o, 
             if (old->exec) (void)hipGraphExecDestroy(old->exec);
             delete old;
         }
-        QH_HIP(hipMemcpyAsync(cb->desc.p, desc.data(), nb * sizeof(BlockDesc), hipMemcpyHostToDevice, st));
+        QH_HIP(hipMemcpyAsync(cb->desc.p, table.data(), nr * sizeof(BlockDesc), hipMemcpyHostToDevice, st));
         const auto args = std::make_tuple(steps, (float)o->dt, (float)a0, pump, seed);
         if (!cb->exec || cb->args != args) {
             if (cb->exec) { (void)hipGraphExecDestroy(cb->exec); cb->exec = nullptr; }
@@ -269,7 +282,7 @@ void bsb_solve_batched(const qh_graph *const *gs, int nb, const qh_bsb_opts *o, 
             hipGraph_t graph = nullptr;
             QH_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
             try {
-                launch_batched_steps(R, nb, cb->desc.p, cb->items.p, cb->class_ptr, cb->splits.data(), steps,
+                launch_batched_steps(R, nr, cb->desc.p, cb->items.p, cb->class_ptr, cb->splits.data(), steps,
                                      (float)o->dt, (float)a0, pump, seed, cs);
             } catch (...) {
                 hipGraph_t junk = nullptr;
@@ -290,10 +303,10 @@ void bsb_solve_batched(const qh_graph *const *gs, int nb, const qh_bsb_opts *o, 
     if (o->use_graph && o->plan == 2)
         fail(QH_EUNSUPPORTED, "the whole-block plan is one launch already; use_graph applies to the per-step plan");
     int plan = o->plan == 2 ? 2 : 1;
-    if (o->plan == 0 && o->steps > 0 && !o->use_graph) {
-        std::vector<uint64_t> key(nb + 1);
-        for (int b = 0; b < nb; ++b) key[b] = gs[b]->serial;
-        key[nb] = (uint64_t)R;
+    if (o->plan == 0 && o->steps > 0 && !o->use_graph && nr) {
+        std::vector<uint64_t> key(nr + 1);
+        for (int b = 0; b < nr; ++b) key[b] = gs[rest[b]]->serial;
+        key[nr] = (uint64_t)R;
         plan = cached_batch_plan(key);
         if (!plan) {
             // time both plans on the real buffers (a few steps each; the state is re-seeded below)
@@ -316,13 +329,17 @@ void bsb_solve_batched(const qh_graph *const *gs, int nb, const qh_bsb_opts *o, 
             store_batch_plan(key, plan);
         }
     }
-    if (o->steps > 0) {
+    if (!bt.launches.empty()) {
+        launch_batched_init(R, nb - nr, d_desc.p + nr, o->seed, st);
+        run_batch_teams(bt, o, a0, pump, st);
+    }
+    if (o->steps > 0 && nr) {
         if (o->use_graph) run_captured(o->steps, o->seed);
         else run(plan, o->steps, o->seed);
     }
     res->plan_used = plan;
-    // the per-step plan ping-pongs x like the single-graph solve; the whole-block plan
-    // leaves the final x in the first half
+    // the per-step plan ping-pongs x like the single-graph solve; the whole-block plan and the
+    // teams leave the final x in the first half
     const int final_half = plan == 1 ? (o->steps & 1) : 0;
 
     if (!o->readout) {   // dynamics only: the final state of every block, when asked for
@@ -332,7 +349,7 @@ void bsb_solve_batched(const qh_graph *const *gs, int nb, const qh_bsb_opts *o, 
             SolvePlan &p = *plans[b];
             const int64_t nR = g->n * R;
             const bool pingpong = !(g->storage == QH_STORE_DENSE && g->dtype != QH_F32);
-            const float *xfin = (pingpong && final_half) ? p.xb.p : p.xa.p;
+            const float *xfin = (pingpong && final_half && !bt.in[b]) ? p.xb.p : p.xa.p;
             if (res->x && nR)
                 QH_HIP(hipMemcpyAsync(res->x + off * R, xfin, nR * sizeof(float), hipMemcpyDeviceToDevice, st));
             if (res->y && nR)
@@ -352,7 +369,7 @@ void bsb_solve_batched(const qh_graph *const *gs, int nb, const qh_bsb_opts *o, 
         SolvePlan &p = *plans[b];
         const int64_t nR = g->n * R;
         const bool pingpong = !(g->storage == QH_STORE_DENSE && g->dtype != QH_F32);
-        const float *xfin = (pingpong && final_half) ? p.xb.p : p.xa.p;
+        const float *xfin = (pingpong && final_half && !bt.in[b]) ? p.xb.p : p.xa.p;
         if (res->x && nR)
             QH_HIP(hipMemcpyAsync(res->x + voff * R, xfin, nR * sizeof(float), hipMemcpyDeviceToDevice, st));
         if (res->y && nR)

@@ -665,9 +665,9 @@ __global__ __launch_bounds__(64) void k_band_step(
 // Initial state of one block by one workgroup: the single-graph counter layout with the
 // block's n, and the 16-bit product copy for dense 16/8-bit blocks.
 template <int64_t R>
-__device__ inline void block_init(const BlockDesc &B, uint64_t seed, int tid) {
+__device__ inline void block_init(const BlockDesc &B, uint64_t seed, int64_t t0, int64_t stride) {
     const int64_t n = B.n;
-    for (int64_t t = tid; t < n * R; t += 256) {
+    for (int64_t t = t0; t < n * R; t += stride) {
         const int64_t i = t / R, r = t - i * R;
         const uint64_t c = 2ull * ((uint64_t)r * (uint64_t)n + (uint64_t)i);
         const float xv = (float)(0.2 * ((double)(sm64_draw(seed, c) >> 11) * 0x1.0p-53) - 0.1);
@@ -698,7 +698,7 @@ __global__ __launch_bounds__(256) void k_batched(const BlockDesc *__restrict__ b
         const BlockDesc B = blocks[sched[k]];
         const int64_t n = B.n;
         float *xb = B.x, *yb = B.y;
-        block_init<R>(B, seed, tid);
+        block_init<R>(B, seed, tid, 256);
         const bool dense16 = B.kind == 0 && B.dtype != QH_F32;
         StepArgs sa{B.c0, dt, a0, pump, 0, B.discrete, B.bscale, B.field};
         float *cur = xb, *oth = B.xs;
@@ -908,7 +908,7 @@ __global__ __launch_bounds__(256) void k_batched_rowtile(const BlockDesc *__rest
 
 template <int NB>
 __global__ __launch_bounds__(256) void k_batched_init(const BlockDesc *__restrict__ blocks, uint64_t seed) {
-    block_init<NB * 16>(blocks[blockIdx.x], seed, threadIdx.x);
+    block_init<NB * 16>(blocks[blockIdx.x], seed, (int64_t)blockIdx.y * 256 + threadIdx.x, 256 * (int64_t)gridDim.y);
 }
 
 // classes: 0-3 dense F32/F16/BF16/FP8, 4-6 band F32/F16/BF16 (kBatchClasses in total)
@@ -920,6 +920,14 @@ static unsigned xcd_grid(const XcdSplit &xs, int per) {
     return (unsigned)(m * kXcds);
 }
 
+// Fewer row tiles than this (two per SIMD): four waves per row tile (k_batched_step) instead of
+// one.  A wave walks its row tile's stored tiles one after another, so few row tiles take as long
+// as the longest one, whose four strips four waves walk in a quarter of the time; with many, the B
+// fragments loaded once per row tile instead of once per strip count more.  FP8, R = 32,
+// k_batched_rowtile / k_batched_step per step: 1,091 row tiles 83 / 45 us, 1,485 83 / 42,
+// 4,224 152 / 165, 9,510 268 / 336.
+constexpr int64_t kRowtileItems = 2048;
+
 template <int NB>
 static void launch_class(int cls, hipStream_t st, const BlockDesc *blocks, const int2 *items, const XcdSplit &xs,
                          int k, float dt, float a0, const float *pump) {
@@ -927,7 +935,8 @@ static void launch_class(int cls, hipStream_t st, const BlockDesc *blocks, const
     hipLaunchKernelGGL((k_batched_step<KD, DTV, NB>), dim3(xcd_grid(xs, 1)), dim3(256), 0, st, blocks, items, xs, \
                        k, dt, a0, pump)
 #define QH_RT(DTV)                                                                                           \
-    hipLaunchKernelGGL((k_batched_rowtile<DTV, NB>), dim3(xcd_grid(xs, 4)), dim3(256), 0, st, blocks, items, xs, \
+    if (xs.off[kXcds] < kRowtileItems) QH_CLS(0, DTV);                                                        \
+    else hipLaunchKernelGGL((k_batched_rowtile<DTV, NB>), dim3(xcd_grid(xs, 4)), dim3(256), 0, st, blocks, items, xs, \
                        k, dt, a0, pump)
     switch (cls) {
         case 0: QH_CLS(0, QH_F32); break;
@@ -965,6 +974,19 @@ static SideStream &side_stream(int dev) {
     return s;
 }
 
+// Initial state of every block, several workgroups per block.
+void launch_batched_init(int R, int nb, const BlockDesc *blocks, uint64_t seed, hipStream_t st) {
+    if (nb == 0) return;
+    const dim3 grid((unsigned)nb, (unsigned)std::max(1, std::min(32, 4096 / nb)));
+    switch (R) {
+        case 16: hipLaunchKernelGGL(k_batched_init<1>, grid, dim3(256), 0, st, blocks, seed); break;
+        case 32: hipLaunchKernelGGL(k_batched_init<2>, grid, dim3(256), 0, st, blocks, seed); break;
+        case 64: hipLaunchKernelGGL(k_batched_init<4>, grid, dim3(256), 0, st, blocks, seed); break;
+        default: fail(QH_EUNSUPPORTED, "batched solves take 16, 32 or 64 replicas");
+    }
+    QH_CHECK_LAUNCH();
+}
+
 // The dense classes (bound by HBM bandwidth) and the band classes (bound by load latency)
 // touch disjoint blocks, so their step chains run concurrently: the band classes go to a
 // side stream forked from `st` after the initial state and joined back before return (a
@@ -987,11 +1009,10 @@ void launch_batched_steps(int R, int nb, const BlockDesc *blocks, const int2 *it
         ev_fork = side.fork;
         ev_join = side.join;
     }
+    launch_batched_init(R, nb, blocks, seed, st);
     {
 #define QH_BSTEPS(NBV)                                                                                    \
     do {                                                                                                  \
-        hipLaunchKernelGGL(k_batched_init<NBV>, dim3(nb), dim3(256), 0, st, blocks, seed);               \
-        QH_CHECK_LAUNCH();                                                                                \
         if (fork) {                                                                                       \
             QH_HIP(hipEventRecord(ev_fork, st));                                                          \
             QH_HIP(hipStreamWaitEvent(sb, ev_fork, 0));                                                   \
@@ -1405,7 +1426,7 @@ static void run_band(SolvePlan &p, const float *pump, double c0, double dt, doub
 }
 
 // Whether work on st is being recorded into a graph (a cooperative launch cannot be).
-static bool stream_capturing(hipStream_t st) {
+bool stream_capturing(hipStream_t st) {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
         (void)hipGetLastError();

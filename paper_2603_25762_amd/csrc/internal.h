@@ -353,6 +353,11 @@ int batched_workers_per_cu(int R);
 // work items (x = block, y = row tile of a dense block or group of four band blocks);
 // class c's items are items[class_ptr[c] .. class_ptr[c + 1])
 constexpr int kBatchClasses = 7;   // dense F32/F16/BF16/FP8, band F32/F16/BF16
+inline int batch_class(const qh_graph *g) {
+    if (g->storage == QH_STORE_DENSE)
+        return g->dtype == QH_F32 ? 0 : g->dtype == QH_F16 ? 1 : g->dtype == QH_BF16 ? 2 : 3;
+    return g->bb_dtype == QH_F32 ? 4 : g->bb_dtype == QH_F16 ? 5 : 6;
+}
 // The items of one class split into one list per XCD: XCD x (the XCD that runs workgroup
 // blockIdx.x when blockIdx.x % 8 == x) works through items [off[x], off[x + 1]) of the
 // class, in order.  Whole blocks go to one XCD (their x copy stays in that XCD's L2).
@@ -360,6 +365,8 @@ constexpr int kXcds = 8;
 struct XcdSplit {
     int64_t off[kXcds + 1];
 };
+void launch_batched_init(int R, int nb, const BlockDesc *blocks, uint64_t seed, hipStream_t st);
+bool stream_capturing(hipStream_t st);
 void launch_batched_steps(int R, int nb, const BlockDesc *blocks, const int2 *items, const int64_t *class_ptr,
                           const XcdSplit *splits, int steps, float dt, float a0, const float *pump, uint64_t seed,
                           hipStream_t st);

@@ -24,7 +24,6 @@ namespace qh {
 typedef _Float16 sp_half8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 sp_bf16x8_t __attribute__((ext_vector_type(8)));
 
-constexpr int kSpPadRows = kTile;   // LDS rows past the last held row (read-ahead, never used)
 constexpr int kSpRegs = 128;        // registers of couplings per lane
 
 // registers per stored tile of a strip (two fragments)

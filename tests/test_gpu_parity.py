@@ -1577,3 +1577,49 @@ def test_readout_component_of_many_chunks(R):
 
 def test_readout_integer_component_of_many_chunks():
     _readout_case(synth.read_small(24, n_snp=2500, n_reads=2300, span=(10, 40)), "read_signed", 32, 5, True)
+
+
+@pytest.fixture(scope="module")
+def team_batch():
+    """300 SNP blocks (bf16) and 300 read blocks (fp8) of 20-300 vertices: more teams of a class than
+    the chip has workgroups; and larger blocks of every storage and type, whose teams have several
+    (700 shuffled reads over 200,000 SNPs: row tiles skip column tiles)."""
+    ws, kinds, dtypes = [], [], []
+    for i, w in enumerate(synth.batched_blocks(91, n_blocks=600, n_lo=20, n_hi=300).blocks):
+        ws.append(w), kinds.append("read_signed" if i % 2 == 0 else "snp_llr"), dtypes.append("fp8" if i % 2 == 0 else "bf16")
+    for i, d in enumerate(["f32", "f16", "bf16", "fp8"]):
+        ws.append(synth.read_small(30 + i, 400, 1300 - 150 * i, (20, 120))), kinds.append("read_signed"), dtypes.append(d)
+    for i, d in enumerate(["f32", "f16", "bf16"]):
+        ws.append(synth.snp_small(40 + i, 2500 - 400 * i)), kinds.append("snp_llr"), dtypes.append(d)
+    w = synth.read_small(6, 200000, 700, (3, 40))
+    perm = np.random.default_rng(1).permutation(700)
+    cnt = np.diff(w.frag_ptr)
+    idx = np.concatenate([np.arange(w.frag_ptr[f], w.frag_ptr[f + 1]) for f in perm])
+    w.frag_ptr = np.concatenate([[0], np.cumsum(cnt[perm])]).astype(np.int64)
+    w.snp, w.allele, w.phred = w.snp[idx], w.allele[idx], w.phred[idx]
+    ws.append(w), kinds.append("read_signed"), dtypes.append("f16")
+    specs = []
+    for w, k, t in zip(ws, kinds, dtypes):
+        d = device_reads(w)
+        specs.append(dict(frag_ptr=d["frag_ptr"], snp=d["snp"], allele=d["allele"], phred=d["phred"],
+                          init_h1=d["init_h1"], kind=k, dtype=t, alpha=d["alpha"], deterministic=True))
+    gs = qh.build_graphs(specs)
+    yield gs
+    for g in gs:
+        g.free()
+
+
+@pytest.mark.parametrize("R", [16, 32, 64])
+@pytest.mark.parametrize("variant", ["plain", "discrete", "field", "graph", "small"])
+def test_batch_teams_equal_per_step(team_batch, R, variant):
+    """Plan 0 (blocks as teams of the persistent kernels) against one launch per step: every block's
+    state and results, bit for bit."""
+    gs = team_batch[-8:] if variant == "small" else team_batch
+    n = sum(g.info()["n"] for g in gs)
+    kw = dict(discrete=variant == "discrete", return_state=True, seed=5)
+    if variant == "field":
+        kw["field"] = torch.linspace(-0.3, 0.3, n, dtype=torch.float32, device="cuda")
+    a = qh.bsb_solve_batched(gs, R, 31, plan=1, **kw)
+    b = qh.bsb_solve_batched(gs, R, 31, plan=0, use_graph=variant == "graph", **kw)
+    for k in ("x", "y", "cuts", "selected_cut", "best_spins", "best_cut"):
+        assert torch.equal(a[k], b[k]), k
