@@ -11,7 +11,7 @@
 // finite; the solver takes the per-step kernels where it might not be (a state or field of the
 // caller's).  Testing for it here instead cost 10-15 % (a branch per tile).
 //
-// What bounds it: the exchange and the barriers of a step (about 3 us), LDS reads of the copy
+// What bounds it: the exchange and the barriers of a step (about 2.5 us), LDS reads of the copy
 // behind them (2 KB per tile, strip and 16 replicas).  The tile-staging persistent kernel
 // (persistent_kernel.h) moves every neighbour's column tile whole and re-reads J from LDS each
 // step.
@@ -160,26 +160,9 @@ __global__ __launch_bounds__(kBpThreads, 2) void k_strip_persistent(BandPersistA
                     // the neighbours' step t - 1 is published: their rows -> LDS
                     bp_wait(a, flags, J.nbr0, J.nbr1, J.w, t, lane);
                     if (s > 0) {                   // (the first step's rows came with the initial state)
-                        // both regions are whole groups of eight rows: 8-byte words
-                        const QH_GLOBAL uint64_t *src =
-                            (const QH_GLOBAL uint64_t *)(xch + ((t - 1) & 1) * half + (int64_t)xlo * RT);
-                        uint64_t *dst = (uint64_t *)sp_x;
-                        const int own_lo = (J.blk0 * kBandRows - xlo) * (RT / 4);
-                        const int own_hi = own_lo + nblk * kBandRows * (RT / 4);
-                        const int total = own_lo + (J.xhi - xlo) * (RT / 4) - own_hi;
-                        for (int e0 = tid; e0 < total; e0 += 8 * kBpThreads) {
-                            uint64_t v[8];
-#pragma unroll
-                            for (int k = 0; k < 8; ++k) {
-                                const int e = e0 + k * kBpThreads, at = e < own_lo ? e : e - own_lo + own_hi;
-                                if (e < total) v[k] = __hip_atomic_load(src + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                            }
-#pragma unroll
-                            for (int k = 0; k < 8; ++k) {
-                                const int e = e0 + k * kBpThreads, at = e < own_lo ? e : e - own_lo + own_hi;
-                                if (e < total) dst[at] = v[k];
-                            }
-                        }
+                        const int own = (J.blk0 * kBandRows - xlo) * RT * 2;
+                        bp_fetch(sp_x, xch + ((t - 1) & 1) * half + (int64_t)xlo * RT, own, own + nblk * kBandRows * RT * 2,
+                                 (J.xhi - xlo) * RT * 2, wave, lane);
                     }
                     bp_barrier();
                 }
