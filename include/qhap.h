@@ -226,7 +226,8 @@ typedef struct {
                             fits (plan 4's results bit for bit; not on a stream being captured),
                             and otherwise the faster of 4 and 5, which it times once. */
     int32_t replica_tile; /* dense graphs, per-step plan, R >= 64: replicas per workgroup
-                            (16, 32 or 64); 0 = the autotuner's choice (plan 0) or 64.
+                            (16, 32 or 64); 0 = the autotuner's choice (plan 0), or
+                            the widest that fills the GPU.
                             Every tile gives bit-identical results. */
     int32_t variant;     /* 0: ballistic SB (the coupling takes x_j); 1: discrete SB, the
                             same update with sgn(x_j) (sgn(0) = +1) in the coupling term */

@@ -1435,6 +1435,18 @@ bool stream_capturing(hipStream_t st) {
     return cs != hipStreamCaptureStatusNone;
 }
 
+// Replica tile of the per-step dense kernel where none was tuned or asked for.  Tiles of 64 replicas
+// read J least often, but leave most of the chip idle when they make fewer workgroups than
+// it has CUs; FP32 tiles of 16 reread too much.  us per step with 64 / 32 / 16 replicas per
+// workgroup (workgroups at 64): 3,000 reads F16, R = 64 (47) 7.6 / 6.2 / 5.3; F32 15.8 / 9.2 / 10.1;
+// F16, R = 128 (94) 7.9 / 6.6 / 6.3; 8,000 reads F16, R = 64 (125) 8.2 / 6.5 / 6.9; BF16, R = 256
+// (500) 11.5 / 13.4 / 17.2.
+static int default_tile(const qh_graph *g, int R) {
+    const int64_t wgs = g->n_rt * (R / 64);
+    if (wgs >= 256) return 64;
+    return g->dtype == QH_F32 || wgs >= 96 ? 32 : 16;
+}
+
 // Autotuner for plan 0 on dense 16/8-bit graphs: time a short run of each candidate on
 // scratch state -- one fused kernel per step, and the persistent launch -- and keep the
 // faster.  Both compute bit-identical results, so the choice only affects speed.  A warm step
@@ -1661,8 +1673,8 @@ void bsb_solve(const qh_graph *g, const qh_bsb_opts *o, qh_result *res, hipStrea
         if (o->plan == 0 && !p.tuned_plan) autotune_dense(g, p, o, pump, c0, a0, band ? 4 : 16, st);
         if (dense16 && want_persistent && !band && p.pp->ok) persistent = o->plan == 2 || p.tuned_plan == 2;
     }
-    // replica tile of the per-step dense kernel: the caller's, else the tuned one, else 64
-    p.run_rt = R < 64 ? R : o->replica_tile ? o->replica_tile : p.tuned_rt ? p.tuned_rt : 64;
+    // replica tile of the per-step dense kernel: the caller's, else the tuned one, else by the fill
+    p.run_rt = R < 64 ? R : o->replica_tile ? o->replica_tile : p.tuned_rt ? p.tuned_rt : default_tile(g, R);
     p.run_depth = o->tiles_in_flight ? o->tiles_in_flight
                                      : (!o->replica_tile && p.tuned_rt == p.run_rt) ? p.tuned_depth : 2;
     if (o->plan == 2 && !persistent)

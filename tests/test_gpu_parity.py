@@ -1623,3 +1623,17 @@ def test_batch_teams_equal_per_step(team_batch, R, variant):
     b = qh.bsb_solve_batched(gs, R, 31, plan=0, use_graph=variant == "graph", **kw)
     for k in ("x", "y", "cuts", "selected_cut", "best_spins", "best_cut"):
         assert torch.equal(a[k], b[k]), k
+
+
+@pytest.mark.parametrize("reads,R,dtype", [(64, 64, "f16"), (1600, 256, "f16"), (1600, 256, "f32"), (4100, 256, "fp8")])
+def test_default_replica_tile_bit_exact(reads, R, dtype):
+    """The per-step dense kernel's replica tile chosen by the fill (16, 32, 32 and 64 replicas)
+    against tiles of 64."""
+    g = gpu_graph(synth.read_small(9, reads * 3 // 2, reads, (20, 60)), "read_signed", dtype)
+    n = g.info()["n"]
+    out = []
+    for tile in (0, 64):
+        x, y = torch.empty((n, R), device="cuda"), torch.empty((n, R), device="cuda")
+        qh.bsb_solve(g, R, 40, seed=3, x=x, y=y, plan=1, replica_tile=tile, readout=False)
+        out.append((x, y))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
