@@ -365,8 +365,8 @@ __global__ __launch_bounds__(kBpThreads, 2) void k_band_persistent(BandPersistAr
                             }
                         }
                         // the last chunk: columns past W multiply their couplings, 0, by 0 and not by
-                        // whatever those rows of x hold; quads past W are left out (a quarter of the
-                        // MFMAs of a block of 44 columns in whole chunks: 250,000 SNPs 27.7 -> 25.9 us)
+                        // whatever those rows of x hold; quads past W are left out (one in twelve to one
+                        // in four for blocks of 44 to 48 columns; 250,000 SNPs 27.7 -> 25.9 us)
                         if constexpr (!kWhole) {
                             const int Wl = W - 16 * nf - g4;   // columns of this lane's quad slots below W
                             const int Wu = W - 16 * nf;

@@ -1169,7 +1169,7 @@ static void launch_step(const qh_graph *g, SolvePlan &p, const StepArgs &sa, int
     const int R = p.R;
     const int64_t n = g->n;
     if (g->storage == QH_STORE_DENSE) {
-        const int RT = R >= 64 ? p.run_rt : R;
+        const int RT = std::min(p.run_rt, R);
         const int64_t G = g->n_rt * (R / RT);
         if (G == 0) return;
         float *xin = cur ? p.xb.p : p.xa.p;
@@ -1440,8 +1440,10 @@ bool stream_capturing(hipStream_t st) {
 // it has CUs; FP32 tiles of 16 reread too much.  us per step with 64 / 32 / 16 replicas per
 // workgroup (workgroups at 64): 3,000 reads F16, R = 64 (47) 7.6 / 6.2 / 5.3; F32 15.8 / 9.2 / 10.1;
 // F16, R = 128 (94) 7.9 / 6.6 / 6.3; 8,000 reads F16, R = 64 (125) 8.2 / 6.5 / 6.9; BF16, R = 256
-// (500) 11.5 / 13.4 / 17.2.
+// (500) 11.5 / 13.4 / 17.2.  R = 32 in 16- and 8-bit types likewise halves its tile where
+// that leaves CUs idle (3,000 reads F16 (46) 5.9 / 4.9; 8,000 (125) 6.2 / 5.4).
 static int default_tile(const qh_graph *g, int R) {
+    if (R < 64) return R == 32 && g->dtype != QH_F32 && g->n_rt < 192 ? 16 : R;
     const int64_t wgs = g->n_rt * (R / 64);
     if (wgs >= 256) return 64;
     return g->dtype == QH_F32 || wgs >= 96 ? 32 : 16;
@@ -1674,7 +1676,7 @@ void bsb_solve(const qh_graph *g, const qh_bsb_opts *o, qh_result *res, hipStrea
         if (dense16 && want_persistent && !band && p.pp->ok) persistent = o->plan == 2 || p.tuned_plan == 2;
     }
     // replica tile of the per-step dense kernel: the caller's, else the tuned one, else by the fill
-    p.run_rt = R < 64 ? R : o->replica_tile ? o->replica_tile : p.tuned_rt ? p.tuned_rt : default_tile(g, R);
+    p.run_rt = o->replica_tile ? o->replica_tile : p.tuned_rt ? p.tuned_rt : default_tile(g, R);
     p.run_depth = o->tiles_in_flight ? o->tiles_in_flight
                                      : (!o->replica_tile && p.tuned_rt == p.run_rt) ? p.tuned_depth : 2;
     if (o->plan == 2 && !persistent)

@@ -126,7 +126,7 @@ struct SolvePlan {
     int last_coh = 0;                  // variant of the last persistent run
     int tuned_rt = 0;                  // autotuner's replica tile for the per-step dense kernel
     int tuned_depth = 2;               // autotuner's tiles in flight for 64-replica tiles (2 or 4)
-    int run_rt = 64;                   // replica tile of the dense step launches (R >= 64)
+    int run_rt = 64;                   // replica tile of the dense step launches (at most R)
     int run_depth = 2;                 // tiles in flight of those launches
     int R = 0;
     int64_t n_pad = 0;
