@@ -5,7 +5,8 @@ log-uniform sizes of 50-5,000 vertices, even blocks dense read graphs stored as 
 per-row scales, odd blocks SNP graphs stored as BF16 (skyline band), R = 32 replicas, 500
 bSB steps (the paper's count for graphs below 5,000 nodes), dt = 0.5, linear pump, c0 auto
 per block.  One benchmark step = one batched solve of all blocks: seeded initial state,
-500 fused bSB steps of every block (the per-step plan replayed from a captured hipGraph),
+500 fused bSB steps of every block (blocks that fit on chip as teams of workgroups, one launch
+for all steps; the others' per-step launches replayed from a captured hipGraph),
 FP64 cuts of every replica and component, per-component selection and the greedy pass.
 The graphs are built before the timed region (the metric counts solver work; graph
 construction and time-to-phase are reported beside it).
@@ -88,6 +89,9 @@ def kernel_source_hash(kernel):
     h = hashlib.sha256()
     if kernel.startswith("k_dense_persistent"):
         h.update(open(os.path.join(csrc, "persistent_kernel.h"), "rb").read())
+    elif kernel.startswith(("k_band_persistent", "k_strip_persistent")):
+        for name in ("band_persistent.h", "band_persistent_kernel.h", "strip_persistent_kernel.h"):
+            h.update(open(os.path.join(csrc, name), "rb").read())
     else:
         src = open(os.path.join(csrc, "bsb.hip")).read()
         h.update(_section(src, "struct StepArgs", "// skyline band + long-range CSR").encode())
@@ -311,7 +315,7 @@ def bench_batched(a):
     nnz = sum(i["nnz"] for i in infos)
     dense = [i for i, inf in enumerate(infos) if inf["storage"] == 0]
     sparse = [i for i, inf in enumerate(infos) if inf["storage"] != 0]
-    plan = 1 if use_graph else a.plan
+    plan = a.plan if not use_graph or a.plan == 1 else 0
     kw = dict(dt=DT, seed=SEED, use_graph=use_graph, plan=plan)
 
     def job(_):
@@ -320,15 +324,19 @@ def bench_batched(a):
     ms, r = _timed_jobs(job, a.steps, a.warmup)
     value = nnz * R * STEPS / (ms * 1e-3)
 
-    # dominant kernel: the dense FP8 class (one launch per step over every dense block's row
-    # tiles), timed with HIP events on the library's stream: the dense blocks solved as a
-    # batch of their own, dynamics only, so the 500 launches of that class are all it runs
+    # the dense blocks and the SNP blocks solved as batches of their own, dynamics only, timed with
+    # HIP events on the library's stream.  Dominant kernel: k_batched_rowtile, which the dense
+    # blocks that do not fit on chip run; its roofline is of plan 1, one launch per step over
+    # every dense block's row tiles
     sub_d = [gs[i] for i in dense]
     sub_s = [gs[i] for i in sparse]
     qh.bsb_solve_batched(sub_d, R, STEPS, readout=False, **kw)              # capture / warm
     dense_us = event_ms(lambda: qh.bsb_solve_batched(sub_d, R, STEPS, readout=False, **kw)) * 1e3 / STEPS
     qh.bsb_solve_batched(sub_s, R, STEPS, readout=False, **kw)
     band_us = event_ms(lambda: qh.bsb_solve_batched(sub_s, R, STEPS, readout=False, **kw)) * 1e3 / STEPS
+    kw1 = dict(kw, plan=1)
+    qh.bsb_solve_batched(sub_d, R, STEPS, readout=False, **kw1)
+    rowtile_us = event_ms(lambda: qh.bsb_solve_batched(sub_d, R, STEPS, readout=False, **kw1)) * 1e3 / STEPS
     n_d = np.array([infos[i]["n"] for i in dense], dtype=np.float64)
     t_d = np.array([infos[i]["dense_tiles"] for i in dense], dtype=np.float64)
     # per dense block and step: its stored 64 x 64 FP8 tiles (all-zero tiles are not stored),
@@ -338,11 +346,10 @@ def bench_batched(a):
     dense_flops = float(2 * 4096 * t_d.sum() * R)
     n_s = np.array([infos[i]["n"] for i in sparse], dtype=np.float64)
     band_bytes = float(sum(infos[i]["stored_bytes"] - 16 * infos[i]["n"] for i in sparse) + 16 * n_s.sum() * R)
-    roof = roofline("hbm", dense_bytes, dense_flops, dense_us, "fp8", "k_batched_rowtile<fp8>",
+    roof = roofline("hbm", dense_bytes, dense_flops, rowtile_us, "fp8", "k_batched_rowtile<fp8>",
                     steps_per_launch=1, per_step_us={"dense_fp8_class": round(dense_us, 2),
                                                      "band_class": round(band_us, 2)},
-                    band_class_hbm_frac=round(band_bytes / (band_us * 1e-6) / 1e9 / PEAK_HBM_GBS, 4),
-                    band_class_bytes_per_launch=int(band_bytes),
+                    band_class_state_bytes=int(band_bytes),
                     stored_tiles=int(t_d.sum()), nnz_flop_per_launch=float(2 * sum(infos[i]["nnz"] for i in dense) * R),
                     note="dense FP8 class per step: sum_b (4096 T_b + 4 N_b + 20 N_b R) bytes, 2 * 4096 T_b R flop "
                          "(T_b stored tiles of block b)")
@@ -356,7 +363,8 @@ def bench_batched(a):
                            blocks=len(gs), dense_blocks=len(dense), snp_blocks=len(sparse), nnz=int(nnz),
                            dense_entries=int((n_d ** 2).sum()), vertices=int(sum(i["n"] for i in infos)),
                            replicas=R, bsb_steps=STEPS, dt=DT, seed=SEED,
-                           plan="per-step, hipGraph replay" if use_graph else f"plan {r['plan_used']}",
+                           plan=("teams where blocks fit on chip; " if plan == 0 else "") +
+                                ("per-step, hipGraph replay" if use_graph else f"plan {r['plan_used']}"),
                            parallelism="single GPU"),
                plan_used=r["plan_used"], build_s=round(build_s, 3), roofline=roof)
     if ref is not None:
@@ -412,7 +420,7 @@ def fp32_form_batched(qh, batch, R, STEPS, DT, SEED, ref, a):
     import torch
     gs = build_batch(qh, batch, dtype="f32")
     nnz = sum(g.info()["nnz"] for g in gs)
-    kw = dict(dt=DT, seed=SEED, use_graph=True, plan=1)
+    kw = dict(dt=DT, seed=SEED, use_graph=True)
     r = qh.bsb_solve_batched(gs, R, STEPS, **kw)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
@@ -455,9 +463,9 @@ def bench_read_mhc(a):
         qh.bsb_solve(g, R, STEPS, dt=DT, seed=seed, plan=0, readout=False)
         tune = g.plan_info(R)
         g.free()
-        plan = tune["plan_used"]
-        kw = dict(replica_tile=tune["replica_tile"], tiles_in_flight=tune["tiles_in_flight"]) if plan == 1 else \
-            dict(persistent_sync=tune["persistent_sync"])
+        # (2: all steps in one launch, which plan 0 takes by rule)
+        plan = 1 if tune["plan_used"] == 1 else 0
+        kw = dict(replica_tile=tune["replica_tile"], tiles_in_flight=tune["tiles_in_flight"]) if plan == 1 else {}
     elif plan == 2:
         kw = dict(persistent_sync=a.persistent_sync)
     use_graph = bool(a.graph) if a.graph is not None else False
@@ -480,14 +488,17 @@ def bench_read_mhc(a):
                                             plan=plan, **kw))
     eb = {"f32": 4, "f16": 2, "bf16": 2, "fp8": 1}[dtype]
     # algorithmic work (§ measurement): 2 nnz R flop per step on the true nonzeros
-    if plan == 2:
+    if plan == 0:
+        kernel = "k_band_persistent<tiles>" if dtype == "f32" else f"k_strip_persistent<{dtype}>"
+        launch_us, steps_per_launch = loop_ms * 1e3, STEPS
+    elif plan == 2:
         kernel = f"k_dense_persistent<{dtype}, {'coherent' if kw.get('persistent_sync') == 2 else 'fences'}>"
         launch_us, steps_per_launch = loop_ms * 1e3, STEPS
     else:
         kernel, launch_us, steps_per_launch = f"k_dense_step<{dtype}>", loop_ms * 1e3 / STEPS, 1
     flops = 2.0 * nnz * R * steps_per_launch
     copy = 0 if dtype == "f32" else 4
-    bytes_ = (tiles * 4096 * eb + n * R * 16 + steps_per_launch * n * R * copy) if plan == 2 else \
+    bytes_ = (tiles * 4096 * eb + n * R * 16 + steps_per_launch * n * R * copy) if plan != 1 else \
         (tiles * 4096 * eb + n * R * (16 + copy))
     roof = roofline("mfma", bytes_, flops, launch_us, dtype, kernel, steps_per_launch=steps_per_launch,
                     us_per_bsb_step=round(loop_ms * 1e3 / STEPS, 3),
@@ -500,7 +511,7 @@ def bench_read_mhc(a):
                config=dict(workload="read_mhc: 4 Mb region, 12,000 het SNPs, 8,000 lognormal 15 kb reads, 1-8% "
                                     "allele errors; dense 8000x8000 signed read graph; R = 256, 2,000 steps",
                            n=n, nnz=nnz, dense_tiles=tiles, replicas=R, bsb_steps=STEPS, dt=DT, precision=dtype,
-                           plan="persistent" if plan == 2 else "per-step", parallelism="single GPU"),
+                           plan="per-step" if plan == 1 else "persistent", parallelism="single GPU"),
                solve_ms=round(solve_ms, 3), solve_edge_updates_per_s=nnz * R * STEPS / (solve_ms * 1e-3),
                best_cut=best_cut, roofline=roof, plan_options=kw)
     if ref is not None:
@@ -587,7 +598,8 @@ def bench_snp(a):
     g = build()     # the autotuner times the band kernels once (untimed); every job then runs its choice
     qh.bsb_solve(g, R, STEPS, dt=DT, seed=SEED, plan=0, readout=False)
     tune = g.plan_info(R)
-    plan = tune["skyline_kernel"]     # 3 per-row, 4 band FMA, 5 band MFMA: the plan that runs it
+    # 0: all steps in one launch, by rule; else 3 per-row, 4 band FMA, 5 band MFMA
+    plan = 0 if tune["plan_used"] == 2 and not a.graph else tune["skyline_kernel"]
     g.free()
     use_graph = bool(a.graph) if a.graph is not None else False
 
@@ -608,9 +620,13 @@ def bench_snp(a):
     # one step: the stored band (no column indices) and the long-range CSR once, x and y read
     # and written once (gathers of x rows by long-range entries are cache traffic)
     bytes_ = info["stored_bytes"] - 16 * n + n * R * 16
-    kernel = {4: "k_band_step", 5: "k_band_step_mfma", 3: "k_sky_step"}[plan] + ("+k_lr_packets" if lr else "")
-    roof = roofline("hbm", bytes_, 2.0 * nnz * R, step_us, "f32", kernel + f"<{dtype}>",
-                    note="one launch = one bSB step (all kernels of the step)")
+    if plan == 0:
+        bytes_ = bytes_ / STEPS            # couplings in, state in and out, once per launch
+    kernel = {0: "k_band_persistent", 4: "k_band_step", 5: "k_band_step_mfma",
+              3: "k_sky_step"}[plan] + ("+k_lr_packets" if lr else "")
+    roof = roofline("mfma" if plan == 0 else "hbm", bytes_, 2.0 * nnz * R, step_us, "f32", kernel + f"<{dtype}>",
+                    note="per bSB step: a launch runs them all, state and couplings on chip" if plan == 0 else
+                         "one launch = one bSB step (all kernels of the step)")
     best_cut = float(r["best_cut"].cpu()[0])
     out = dict(metric=METRIC, value=nnz * R * STEPS / (ms * 1e-3), unit="edge-updates/s", n_gpus=1, steps=a.steps,
                warmup=a.warmup, ms_per_step=round(ms, 3), higher_is_better=True, scaling="weak", vs_baseline=None,
