@@ -1517,14 +1517,14 @@ static void autotune_dense(const qh_graph *g, SolvePlan &p, const qh_bsb_opts *o
     p.run_depth = p.tuned_depth;
 }
 
-// SNP graphs: time the two band kernels (a warm step, then four steps each) and keep the faster;
+// SNP graphs: time the two band kernels (a warm step, then nt steps each) and keep the faster;
 // the band FMA kernel needs 64-replica tiles.  The two differ by 1.6x (2,001 SNPs, R = 128) to
-// 3.2x (the Pore-C chromosome graph), so four steps tell them apart; 64 steps twice cost a
+// 3.2x (the Pore-C chromosome graph), so a few steps tell them apart; 64 steps twice cost a
 // quarter of a 1,000-step chromosome job.  The state's values do not matter to the timing.
 static void autotune_sky(const qh_graph *g, SolvePlan &p, const qh_bsb_opts *o, const float *pump, double c0,
-                         double a0, hipStream_t st) {
+                         double a0, int nt, hipStream_t st) {
     const int R = p.R;
-    const int nt = std::min(o->steps, 4);
+    nt = std::min(o->steps, nt);
     std::vector<int> cands;
     if (R >= 64) cands.push_back(kSkyBandFma);
     cands.push_back(kSkyBandMfma);
@@ -1608,7 +1608,7 @@ void autotune(const qh_graph *g, const qh_bsb_opts *o, qh_bsb_opts *chosen, floa
             us[0] = p.tuned_us[0];
         }
     } else {
-        if (!p.sky_tuned) autotune_sky(g, p, o, pump, c0, a0, st);
+        if (!p.sky_tuned) autotune_sky(g, p, o, pump, c0, a0, 4, st);
         chosen->plan = p.sky_best == kSkyBandMfma ? 5 : p.sky_best == kSkyBandFma ? 4 : 3;
         us[0] = p.sky_us[kSkyBandFma];
         us[1] = p.sky_us[kSkyBandMfma];
@@ -1630,13 +1630,26 @@ void bsb_solve(const qh_graph *g, const qh_bsb_opts *o, qh_result *res, hipStrea
     const bool dense16 = !x_pingpong(g);
     const bool dense = g->storage == QH_STORE_DENSE;
     if (dense && o->plan >= 3) fail(QH_EINVAL, "plans 3-5 choose the step kernel of SNP (skyline) graphs");
+    // plan 0: every step in one launch with state and couplings on chip, where the graph fits (the
+    // per-step kernels' results bit for bit); a stream being captured takes the per-step launches
+    bool band = false;
+    if (o->plan == 0 && ke > kb && n > 0 && !stream_capturing(st)) {
+        if (!p.bp_tried) {
+            p.bp = std::make_shared<BandPersist>();
+            build_band_plan(g, p, *p.bp, st);
+            p.bp_tried = true;
+        }
+        // (a column tile that a row tile skips multiplies by 0 there: the caller's own state or
+        // field might not be finite)
+        band = p.bp->ok && !(p.bp->gaps && (!o->init || o->field)) && (int64_t)p.bp->passes * (ke - kb) < ((int64_t)1 << 30);
+    }
     if (!dense) {
         // SNP graphs: plan 3 per-row kernel, 4 band blocks on FMAs, 5 band blocks on MFMAs;
         // plan 0 times the two band kernels on this graph once, plan 1 keeps that choice
         // (band FMAs when never tuned)
         int want = o->plan == 3 ? kSkyRows : o->plan == 4 ? kSkyBandFma : o->plan == 5 ? kSkyBandMfma : -1;
         if (want < 0) {
-            if (o->plan == 0 && !p.sky_tuned && ke > kb && n > 0) autotune_sky(g, p, o, pump, c0, a0, st);
+            if (o->plan == 0 && !p.sky_tuned && ke > kb && n > 0) autotune_sky(g, p, o, pump, c0, a0, band ? 2 : 4, st);
             want = p.sky_tuned ? p.sky_best : kSkyBandFma;
         }
         if (p.sky_kernel != want) {
@@ -1652,19 +1665,6 @@ void bsb_solve(const qh_graph *g, const qh_bsb_opts *o, qh_result *res, hipStrea
     int final_half = 0;
     bool persistent = false;
     const bool want_persistent = o->plan == 0 || o->plan == 2;
-    // plan 0: every step in one launch with state and couplings on chip, where the graph fits (the
-    // per-step kernels' results bit for bit); a stream being captured takes the per-step launches
-    bool band = false;
-    if (o->plan == 0 && ke > kb && n > 0 && !stream_capturing(st)) {
-        if (!p.bp_tried) {
-            p.bp = std::make_shared<BandPersist>();
-            build_band_plan(g, p, *p.bp, st);
-            p.bp_tried = true;
-        }
-        // (a column tile that a row tile skips multiplies by 0 there: the caller's own state or
-        // field might not be finite)
-        band = p.bp->ok && !(p.bp->gaps && (!o->init || o->field)) && (int64_t)p.bp->passes * (ke - kb) < ((int64_t)1 << 30);
-    }
     if (dense && ke > kb && n > 0) {
         if (dense16 && want_persistent && !band && !p.pp_tried) {
             p.pp = std::make_shared<PersistPlan>();
@@ -1672,7 +1672,7 @@ void bsb_solve(const qh_graph *g, const qh_bsb_opts *o, qh_result *res, hipStrea
             p.pp_tried = true;
         }
         // (a graph on the band plan is timed briefly, for the report and for later plan-1 solves)
-        if (o->plan == 0 && !p.tuned_plan) autotune_dense(g, p, o, pump, c0, a0, band ? 4 : 16, st);
+        if (o->plan == 0 && !p.tuned_plan) autotune_dense(g, p, o, pump, c0, a0, band ? 2 : 16, st);
         if (dense16 && want_persistent && !band && p.pp->ok) persistent = o->plan == 2 || p.tuned_plan == 2;
     }
     // replica tile of the per-step dense kernel: the caller's, else the tuned one, else by the fill
