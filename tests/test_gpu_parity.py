@@ -1637,3 +1637,16 @@ def test_default_replica_tile_bit_exact(reads, R, dtype):
         qh.bsb_solve(g, R, 40, seed=3, x=x, y=y, plan=1, replica_tile=tile, readout=False)
         out.append((x, y))
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("reads,snps,span", [(900, 70, (20, 60)), (130, 600, (250, 260)), (64, 40, (2, 3))])
+@pytest.mark.parametrize("kind", ["read_signed", "read_conflict"])
+def test_read_rows_list_lengths(reads, snps, span, kind):
+    """Read graph rows over coverage lists of several hundred (a wave each), of around 64 with a read
+    of more SNPs than one chunk of observations, and short ones."""
+    w = synth.read_small(14, snps, reads, span)
+    g = gpu_graph(w, kind, "f32")
+    go = oracle_graph(w, kind)
+    assert np.array_equal(cpu(g.export_rows(0, go.n)), go.dense())
+    comp, nc = oracle.components(go)
+    assert g.info()["n_comp"] == nc and np.array_equal(cpu(g.components()), comp)
