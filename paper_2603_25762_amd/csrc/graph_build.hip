@@ -141,10 +141,11 @@ __device__ inline int32_t duf_root(int32_t *p, int32_t x) {
 // Joins the trees of x and y (Rem's order of the walk): the side with the larger parent climbs, and when it
 // is a root it is hooked by compare-and-swap under the other side's parent, which is smaller and
 // need not be a root itself.  A chain of neighbours thus links at once, where walks to both
-// roots follow the chain as it grows (k_snp_structure, 2,001 SNPs: 84 -> 42 us).  The first attempt reads parents through the caches;
-// a stale parent is an earlier one and still an ancestor, and a vertex that only looks like a root
-// fails the swap, after which the reads are device-coherent.  Climbing splits the path as duf_root
-// does (device-coherent stores; plain stores never touch the parent array).
+// roots follow the chain as it grows (k_snp_structure, 2,001 SNPs: 84 -> 42 us).  The first
+// attempt reads parents through the caches; a stale parent is an earlier one and still an
+// ancestor, and a vertex that only looks like a root fails the swap, after which the reads are
+// device-coherent.  Climbing splits the path as duf_root does (device-coherent stores; plain
+// stores never touch the parent array).
 __device__ inline void duf_link(int32_t *p, int32_t x, int32_t y) {
     bool coherent = false;
     while (true) {
