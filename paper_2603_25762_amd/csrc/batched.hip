@@ -231,7 +231,7 @@ void bsb_solve_batched(const qh_graph *const *gs, int nb, const qh_bsb_opts *o, 
     QH_HIP(hipMemcpyAsync(d_sptr.p, sptr.data(), (workers + 1) * sizeof(int32_t), hipMemcpyHostToDevice, st));
     if (nr) QH_HIP(hipMemcpyAsync(d_sched.p, sched.data(), nr * sizeof(int32_t), hipMemcpyHostToDevice, st));
 
-    auto run = [&](int plan, int steps, uint64_t seed) {
+    auto run = [&](int plan, int steps, uint64_t seed, hipStream_t st) {
         if (plan == 2) launch_batched(R, workers, d_desc.p, d_sptr.p, d_sched.p, steps, (float)o->dt, (float)a0, pump,
                                       seed, st);
         else launch_batched_steps(R, nr, d_desc.p, d_items.p, class_ptr, splits.data(), steps, (float)o->dt,
@@ -241,7 +241,7 @@ void bsb_solve_batched(const qh_graph *const *gs, int nb, const qh_bsb_opts *o, 
     // block table and items from buffers owned by the cache entry; the table is uploaded into
     // it on every call (same graphs and R: same layout), so a replay sees this call's c0,
     // variant and field.
-    auto run_captured = [&](int steps, uint64_t seed) {
+    auto run_captured = [&](int steps, uint64_t seed, hipStream_t st) {
         std::vector<uint64_t> key(nr + 2);
         for (int b = 0; b < nr; ++b) key[b] = gs[rest[b]]->serial;
         key[nr] = (uint64_t)R;
@@ -316,9 +316,9 @@ void bsb_solve_batched(const qh_graph *const *gs, int nb, const qh_bsb_opts *o, 
             QH_HIP(hipEventCreate(&e1));
             float ms[2] = {0, 0};
             for (int c = 0; c < 2; ++c) {
-                run(c + 1, nt, 0x5eed);                         // warm
+                run(c + 1, nt, 0x5eed, st);                         // warm
                 QH_HIP(hipEventRecord(e0, st));
-                run(c + 1, nt, 0x5eed);
+                run(c + 1, nt, 0x5eed, st);
                 QH_HIP(hipEventRecord(e1, st));
                 QH_HIP(hipEventSynchronize(e1));
                 QH_HIP(hipEventElapsedTime(&ms[c], e0, e1));
@@ -329,13 +329,34 @@ void bsb_solve_batched(const qh_graph *const *gs, int nb, const qh_bsb_opts *o, 
             store_batch_plan(key, plan);
         }
     }
-    if (!bt.launches.empty()) {
-        launch_batched_init(R, nb - nr, d_desc.p + nr, o->seed, st);
-        run_batch_teams(bt, o, a0, pump, st);
-    }
-    if (o->steps > 0 && nr) {
-        if (o->use_graph) run_captured(o->steps, o->seed);
-        else run(plan, o->steps, o->seed);
+    // Few others (too few row tiles to fill the chip) run beside the teams on the side stream, on CUs that
+    // the teams leave or no longer use; the teams' launches are enqueued first, and a per-step
+    // kernel always ends, so a team's workgroups always get their CUs.  Many gain nothing.  us per step one after the other / beside: 40 F16 and SNP blocks of
+    // 50-5,000 29.3 / 17.8; 300 FP8 and SNP blocks 92.3 / 88.5; 815 at R = 64 430 / 428; 3,000 812 / 808.
+    try {
+        hipStream_t rs = st;
+        SideStream *side = nullptr;
+        if (!bt.launches.empty()) {
+            launch_batched_init(R, nb - nr, d_desc.p + nr, o->seed, st);
+            if (nr && n_items < kRowtileItems) {
+                side = &side_stream(dev);
+                rs = side->stream;
+                QH_HIP(hipEventRecord(side->fork, st));
+                QH_HIP(hipStreamWaitEvent(rs, side->fork, 0));
+            }
+            run_batch_teams(bt, o, a0, pump, st);
+        }
+        if (o->steps > 0 && nr) {
+            if (o->use_graph) run_captured(o->steps, o->seed, rs);
+            else run(plan, o->steps, o->seed, rs);
+        }
+        if (side) {
+            QH_HIP(hipEventRecord(side->join, rs));
+            QH_HIP(hipStreamWaitEvent(st, side->join, 0));
+        }
+    } catch (...) {
+        (void)hipDeviceSynchronize();          // nothing queued may outlive this call's buffers
+        throw;
     }
     res->plan_used = plan;
     // the per-step plan ping-pongs x like the single-graph solve; the whole-block plan and the

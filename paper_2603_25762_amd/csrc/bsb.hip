@@ -920,13 +920,12 @@ static unsigned xcd_grid(const XcdSplit &xs, int per) {
     return (unsigned)(m * kXcds);
 }
 
-// Fewer row tiles than this (two per SIMD): four waves per row tile (k_batched_step) instead of
+// Fewer row tiles than kRowtileItems (two per SIMD): four waves per row tile (k_batched_step) instead of
 // one.  A wave walks its row tile's stored tiles one after another, so few row tiles take as long
 // as the longest one, whose four strips four waves walk in a quarter of the time; with many, the B
 // fragments loaded once per row tile instead of once per strip count more.  FP8, R = 32,
 // k_batched_rowtile / k_batched_step per step: 1,091 row tiles 83 / 45 us, 1,485 83 / 42,
 // 4,224 152 / 165, 9,510 268 / 336.
-constexpr int64_t kRowtileItems = 2048;
 
 template <int NB>
 static void launch_class(int cls, hipStream_t st, const BlockDesc *blocks, const int2 *items, const XcdSplit &xs,
@@ -951,15 +950,11 @@ static void launch_class(int cls, hipStream_t st, const BlockDesc *blocks, const
 #undef QH_CLS
 }
 
-// Side stream of a device for the SNP band classes of a batched solve (default priority,
-// non-blocking), with the two events that fork it from and join it to the caller's stream;
+// Side stream of a device for the SNP band classes, or the blocks beside the teams, of a batched
+// solve (default priority, non-blocking), with the two events that fork it from and join it to the caller's stream;
 // one set per device, created once and kept for the life of the process (a captured graph
 // may refer to them until it is instantiated).
-struct SideStream {
-    hipStream_t stream = nullptr;
-    hipEvent_t fork = nullptr, join = nullptr;
-};
-static SideStream &side_stream(int dev) {
+SideStream &side_stream(int dev) {
     constexpr int kMaxDevices = 64;
     static std::mutex mu;
     static SideStream sides[kMaxDevices];

@@ -365,6 +365,12 @@ constexpr int kXcds = 8;
 struct XcdSplit {
     int64_t off[kXcds + 1];
 };
+constexpr int64_t kRowtileItems = 2048;   // row tiles that give every SIMD two waves
+struct SideStream {
+    hipStream_t stream = nullptr;
+    hipEvent_t fork = nullptr, join = nullptr;
+};
+SideStream &side_stream(int dev);
 void launch_batched_init(int R, int nb, const BlockDesc *blocks, uint64_t seed, hipStream_t st);
 bool stream_capturing(hipStream_t st);
 void launch_batched_steps(int R, int nb, const BlockDesc *blocks, const int2 *items, const int64_t *class_ptr,
