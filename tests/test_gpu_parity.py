@@ -1650,3 +1650,54 @@ def test_read_rows_list_lengths(reads, snps, span, kind):
     assert np.array_equal(cpu(g.export_rows(0, go.n)), go.dense())
     comp, nc = oracle.components(go)
     assert g.info()["n_comp"] == nc and np.array_equal(cpu(g.components()), comp)
+
+
+def _one_step_case(kind, dtype, n, reads, R):
+    w = synth.snp_small(5, n_snp=n) if kind == "snp_llr" else synth.read_small(6, n, reads, (20, 60))
+    return gpu_graph(w, kind, dtype), 3 if kind == "snp_llr" else 1
+
+
+@pytest.mark.parametrize("kind,dtype,n,reads,R", [
+    ("snp_llr", "f16", 30011, 0, 512), ("snp_llr", "f32", 2001, 0, 128), ("read_signed", "f32", 2300, 1501, 64),
+    ("read_signed", "bf16", 9000, 3000, 512), ("read_signed", "fp8", 2300, 1501, 32)])
+def test_one_launch_of_one_step(kind, dtype, n, reads, R):
+    """Ranges of one step on the one-launch plan, several workgroups per graph and several replica groups
+    per workgroup: no workgroup's final state may reach a neighbour that still reads the initial
+    one.  Steps one by one, a readout after every step and a last range of one step, against one
+    launch per step, bit for bit."""
+    g, ref = _one_step_case(kind, dtype, n, reads, R)
+    nv = g.info()["n"]
+    out = []
+    for plan in (ref, 0):
+        x = torch.empty((nv, R), dtype=torch.float32, device="cuda")
+        y = torch.empty_like(x)
+        got = []
+        for k in range(6):
+            qh.bsb_solve(g, R, 40, seed=9, x=x, y=y, plan=plan, readout=False, init=k == 0, step_begin=k, step_end=k + 1)
+            got += [x.clone(), y.clone()]
+        for every, end in ((1, 5), (3, 7)):
+            r = qh.bsb_solve(g, R, 40, seed=9, plan=plan, step_end=end, eval_every=every, energy=True)
+            got += [r["best_spins"], r["cuts"], r["best_cut"], r["energy"]]
+        out.append(got)
+    assert g.plan_info(R)["plan_used"] == 2
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("steps", [1, 2])
+@pytest.mark.parametrize("kind,dtype,n", [("snp_llr", "bf16", 2500), ("read_signed", "fp8", 1300)])
+def test_batch_of_one_step_teams(kind, dtype, n, steps):
+    """More teams of several workgroups than the chip holds at once, so that a team's workgroups start at
+    different times: schedules of one and two steps, against one launch per step, bit for bit."""
+    w = synth.snp_small(41, n_snp=n) if kind == "snp_llr" else synth.read_small(42, 400, n, (20, 120))
+    d = device_reads(w)
+    gs = qh.build_graphs([dict(frag_ptr=d["frag_ptr"], snp=d["snp"], allele=d["allele"], phred=d["phred"],
+                               init_h1=d["init_h1"], kind=kind, dtype=dtype, alpha=d["alpha"], deterministic=True)
+                          for _ in range(200)])
+    a = qh.bsb_solve_batched(gs, 64, steps, plan=1, return_state=True, seed=5)
+    for _ in range(3):
+        b = qh.bsb_solve_batched(gs, 64, steps, plan=0, return_state=True, seed=5)
+        for k in ("x", "y", "cuts", "best_spins", "best_cut"):
+            assert torch.equal(a[k], b[k]), k
+    for g in gs:
+        g.free()
