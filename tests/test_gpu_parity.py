@@ -1652,7 +1652,7 @@ def test_read_rows_list_lengths(reads, snps, span, kind):
     assert g.info()["n_comp"] == nc and np.array_equal(cpu(g.components()), comp)
 
 
-def _one_step_case(kind, dtype, n, reads, R):
+def _one_launch_case(kind, dtype, n, reads, R):
     w = synth.snp_small(5, n_snp=n) if kind == "snp_llr" else synth.read_small(6, n, reads, (20, 60))
     return gpu_graph(w, kind, dtype), 3 if kind == "snp_llr" else 1
 
@@ -1665,7 +1665,7 @@ def test_one_launch_of_one_step(kind, dtype, n, reads, R):
     per workgroup: no workgroup's final state may reach a neighbour that still reads the initial
     one.  Steps one by one, a readout after every step and a last range of one step, against one
     launch per step, bit for bit."""
-    g, ref = _one_step_case(kind, dtype, n, reads, R)
+    g, ref = _one_launch_case(kind, dtype, n, reads, R)
     nv = g.info()["n"]
     out = []
     for plan in (ref, 0):
