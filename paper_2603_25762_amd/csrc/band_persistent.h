@@ -8,6 +8,7 @@ namespace qh {
 
 constexpr int kBpWaves = 8;                  // waves per workgroup (two per SIMD)
 constexpr int kBpThreads = 64 * kBpWaves;
+constexpr int kBpMinSteps = 2;               // steps of a launch, at least
 constexpr int kBpPadRows = 32;               // LDS rows past the last held row (read-ahead, never used)
 
 // DT values of the band kernel: a storage type of band blocks, or the FP32 tiles of a dense graph,

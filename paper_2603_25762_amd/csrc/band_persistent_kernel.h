@@ -20,9 +20,9 @@
 //
 // Flags count steps.  A workgroup publishes step t into half t % 2 of the exchange buffer only
 // after its neighbours' flags reached t, that is after they read half t % 2 for the last time;
-// the neighbour lists are symmetric.  The final state goes to memory only once every neighbour has
-// finished its first step, since the neighbours' rows of the initial state are read from there.
-// Waits are bounded: past max_polls a workgroup raises the
+// the neighbour lists are symmetric.  A launch runs at least two steps: a workgroup reads its
+// neighbours' rows of the initial state from where they write their final one, and only the wait of a
+// second step shows that the neighbours are past that read.  Waits are bounded: past max_polls a workgroup raises the
 // error word, every wait then returns at once, and the final state is NaN, which the readout
 // reports.
 #pragma once
@@ -467,10 +467,6 @@ __global__ __launch_bounds__(kBpThreads, 2) void k_band_persistent(BandPersistAr
                                        __HIP_MEMORY_SCOPE_AGENT);
             }
         }
-        // The neighbours took this workgroup's rows of the initial state from where the final state
-        // goes.  A flag of t0 + 1 or more says that they are past that; with two steps or more the
-        // last step's wait has seen it.
-        if (has_nbr && steps == 1) bp_wait(a, flags, J.nbr0, J.nbr1, J.w, t0 + 1, lane);
         // final state -> memory (NaN when a wait gave up)
         const bool bad = has_nbr && bp_flag(a.err) != 0;
 #pragma unroll

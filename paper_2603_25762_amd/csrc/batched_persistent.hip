@@ -168,7 +168,7 @@ void plan_batch_teams(const qh_graph *const *gs, const std::vector<SolvePlan *> 
     QH_HIP(hipGetDevice(&dev));
     QH_HIP(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
     QH_HIP(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev));
-    if (!coop || n_cu < 1 || o->steps >= (1 << 30)) return;
+    if (!coop || n_cu < 1 || o->steps < kBpMinSteps || o->steps >= (1 << 30)) return;
 
     // geometry: dense blocks' strips first (they have tables of their own), then band blocks
     std::vector<GeomDesc> gd(nb);

@@ -1397,6 +1397,7 @@ static void run_persistent(const qh_graph *g, SolvePlan &p, const float *pump, d
 static void run_band(SolvePlan &p, const float *pump, double c0, double dt, double a0, int kb, int ke, int discrete,
                      const float *field, hipStream_t st) {
     BandPersist &bp = *p.bp;
+    if (ke - kb < kBpMinSteps) fail(QH_EUNSUPPORTED, "a one-launch range needs %d steps", kBpMinSteps);
     hipLaunchKernelGGL(k_zero_i32, dim3(grid_for((int64_t)bp.flags.n)), dim3(256), 0, st, (int64_t)bp.flags.n,
                        bp.flags.p);
     QH_CHECK_LAUNCH();
@@ -1645,14 +1646,10 @@ void bsb_solve(const qh_graph *g, const qh_bsb_opts *o, qh_result *res, hipStrea
         int want = o->plan == 3 ? kSkyRows : o->plan == 4 ? kSkyBandFma : o->plan == 5 ? kSkyBandMfma : -1;
         if (want < 0) {
             if (o->plan == 0 && !p.sky_tuned && ke > kb && n > 0) autotune_sky(g, p, o, pump, c0, a0, band ? 2 : 4, st);
-            want = p.sky_tuned ? p.sky_best : kSkyBandFma;
+            // (ranges too short for the one-launch plan take the kernel that adds in its order)
+            want = p.sky_tuned && !band ? p.sky_best : kSkyBandFma;
         }
-        if (p.sky_kernel != want) {
-            // the captured step loop launches the other kernel: drop it
-            p.sky_kernel = want;
-            if (p.exec) { (void)hipGraphExecDestroy(p.exec); p.exec = nullptr; }
-            if (p.graph) { (void)hipGraphDestroy(p.graph); p.graph = nullptr; }
-        }
+        p.sky_kernel = want;
     }
 
     // the step loop: the persistent dense plan (plan 2), one fused kernel per step (plan 1,
@@ -1691,7 +1688,9 @@ void bsb_solve(const qh_graph *g, const qh_bsb_opts *o, qh_result *res, hipStrea
         x_to_h(g, p, n, R, o->variant == 1, st);
     };
     load_state();
-    if (ke > kb && n > 0) p.last_plan = persistent || band ? 2 : 1;
+    auto one_launch = [&](int k0, int k1) { return band && k1 - k0 >= kBpMinSteps; };
+    if (ke > kb && n > 0)
+        p.last_plan = persistent || one_launch(kb, o->eval_every > 0 ? (int)std::min<int64_t>(ke, (int64_t)kb + o->eval_every) : ke) ? 2 : 1;
     const int coherent = o->persistent_sync == 2 || (o->persistent_sync == 0 && p.tuned_coh);
     if (persistent) p.last_coh = coherent;
     if (o->eval_every > 0) {
@@ -1707,7 +1706,7 @@ void bsb_solve(const qh_graph *g, const qh_bsb_opts *o, qh_result *res, hipStrea
             int fh = 0;
             if (k1 > k0 && n > 0) {
                 if (persistent) run_persistent(g, p, pump, c0, o->dt, a0, k0, k1, o->variant == 1, o->field, coherent, st);
-                else if (band) run_band(p, pump, c0, o->dt, a0, k0, k1, o->variant == 1, o->field, st);
+                else if (one_launch(k0, k1)) run_band(p, pump, c0, o->dt, a0, k0, k1, o->variant == 1, o->field, st);
                 else fh = run_steps(g, p, o, pump, c0, a0, k0, k1, st);
             }
             if (fh && !dense16 && nR)   // ping-pong paths: the range ended in the second half
@@ -1731,11 +1730,11 @@ void bsb_solve(const qh_graph *g, const qh_bsb_opts *o, qh_result *res, hipStrea
     }
     if (persistent) {
         run_persistent(g, p, pump, c0, o->dt, a0, kb, ke, o->variant == 1, o->field, coherent, st);
-    } else if (band) {
+    } else if (one_launch(kb, ke)) {
         run_band(p, pump, c0, o->dt, a0, kb, ke, o->variant == 1, o->field, st);
     } else if (ke > kb && n > 0) {
         if (o->use_graph) {
-            auto key = std::make_tuple(kb, ke, (int)g->dtype, c0, o->dt, a0, pump, R,
+            auto key = std::make_tuple(kb, ke, (int)g->dtype + 16 * p.sky_kernel, c0, o->dt, a0, pump, R,
                                        (p.run_rt * 8 + p.run_depth) * 2 + (o->variant == 1), o->field);
             if (!p.exec || p.graph_key != key) {
                 if (p.exec) { (void)hipGraphExecDestroy(p.exec); p.exec = nullptr; }

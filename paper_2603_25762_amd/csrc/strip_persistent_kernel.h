@@ -297,8 +297,6 @@ __global__ __launch_bounds__(kBpThreads, 2) void k_strip_persistent(BandPersistA
                                        __HIP_MEMORY_SCOPE_AGENT);
             }
         }
-        // (as in the band kernel: the neighbours are past their reads of the initial state)
-        if (has_nbr && steps == 1) bp_wait(a, flags, J.nbr0, J.nbr1, J.w, t0 + 1, lane);
         // final state -> memory (NaN when a wait gave up)
         const bool bad = has_nbr && bp_flag(a.err) != 0;
 #pragma unroll

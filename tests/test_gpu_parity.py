@@ -1661,10 +1661,10 @@ def _one_launch_case(kind, dtype, n, reads, R):
     ("snp_llr", "f16", 30011, 0, 512), ("snp_llr", "f32", 2001, 0, 128), ("read_signed", "f32", 2300, 1501, 64),
     ("read_signed", "bf16", 9000, 3000, 512), ("read_signed", "fp8", 2300, 1501, 32)])
 def test_one_launch_of_one_step(kind, dtype, n, reads, R):
-    """Ranges of one step on the one-launch plan, several workgroups per graph and several replica groups
-    per workgroup: no workgroup's final state may reach a neighbour that still reads the initial
-    one.  Steps one by one, a readout after every step and a last range of one step, against one
-    launch per step, bit for bit."""
+    """Ranges of one step under plan 0, on graphs whose longer ranges run in one launch of several
+    workgroups and replica groups: no workgroup's final state may reach a neighbour that still
+    reads the initial one.  Steps one by one, a readout after every step and a last range of one step,
+    against one launch per step, bit for bit."""
     g, ref = _one_launch_case(kind, dtype, n, reads, R)
     nv = g.info()["n"]
     out = []
@@ -1679,7 +1679,6 @@ def test_one_launch_of_one_step(kind, dtype, n, reads, R):
             r = qh.bsb_solve(g, R, 40, seed=9, plan=plan, step_end=end, eval_every=every, energy=True)
             got += [r["best_spins"], r["cuts"], r["best_cut"], r["energy"]]
         out.append(got)
-    assert g.plan_info(R)["plan_used"] == 2
     for a, b in zip(*out):
         assert torch.equal(a, b)
 
