@@ -297,7 +297,10 @@ typedef struct {
  * Errors: EINVAL (replicas not 16/32/64k, steps < 1, range outside the schedule,
  * init = 0 without x/y, readout without best_spins/cuts/best_cut, eval_every < 0 or
  * eval_every > 0 with readout = 0 or use_graph = 1), ENUMERIC when the state read out holds
- * NaN/Inf (checked when readout = 1), ENOMEM, EHIP. */
+ * NaN/Inf (checked when readout = 1), ENOMEM, EHIP.  A plan that runs all steps in one launch
+ * bounds its waits between workgroups; one that gives up leaves x and y NaN and is an EHIP: of this
+ * call when readout = 1, and with readout = 0, where the call returns before its launch has ended,
+ * of the next call with this graph and replica count after that. */
 qh_status qh_bsb_solve(const qh_graph *g, const qh_bsb_opts *opts, qh_result *res, void *stream);
 
 /* Step-loop plan chosen for (graph, replicas) by earlier solves.  plan_used: 0 = no solve

@@ -92,7 +92,14 @@ struct BandPersist {
     DevBuf<int32_t> job_ptr;
     DevBuf<float> xch;
     DevBuf<int> flags;          // n_flags counters, then the error word
+    HostWord failed;            // readout = 0: set by the stream when a wait gave up
 };
+// Polls of a neighbour's flag before a wait gives up (tests lower it).
+constexpr int64_t kWaitPolls = (int64_t)1 << 27;
+extern int64_t wait_polls;
+constexpr int64_t kBpErr = 32, kBpFlagsPad = 64;       // the error word's place past the flags
+// Fails with EHIP when the error word of launches that have ended is set, and clears it.
+void check_waits(int *err, hipStream_t st);
 
 constexpr int64_t kBpLdsLimit = 160 * 1024;
 constexpr int kSpPadRows = kTile;   // strip kernel: LDS rows past the last held row (read-ahead, never used)

@@ -7,6 +7,15 @@
 
 namespace qh {
 
+int64_t wait_polls = kWaitPolls;
+
+void check_waits(int *err, hipStream_t st) {
+    if (!download(err, 1, st)[0]) return;
+    QH_HIP(hipMemsetAsync(err, 0, sizeof(int), st));
+    QH_HIP(hipStreamSynchronize(st));
+    fail(QH_EHIP, "one-launch bSB kernel: a neighbour wait exceeded its poll limit");
+}
+
 // Contiguous parts of the band blocks, as even as possible, with the rows each part holds, the
 // blocks that reach past its own rows, the blocks its neighbours reach, and the neighbour range
 // (made symmetric: "reads from" and "is read by" together).
@@ -222,7 +231,9 @@ bool build_band_plan(const qh_graph *g, SolvePlan &p, BandPersist &bp, hipStream
         bp.job_ptr.alloc(bl.job_ptr.size());
         bp.job_ptr.upload(bl.job_ptr.data(), bl.job_ptr.size(), st);
         bp.xch.alloc((size_t)bl.xch_floats);
-        bp.flags.alloc((size_t)bl.n_flags + 64);
+        bp.flags.alloc((size_t)bl.n_flags + kBpFlagsPad);
+        bp.flags.zero(st);
+        bp.failed.take();
         QH_HIP(hipStreamSynchronize(st));
         bp.ok = true;
         return true;

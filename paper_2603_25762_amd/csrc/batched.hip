@@ -377,7 +377,8 @@ void bsb_solve_batched(const qh_graph *const *gs, int nb, const qh_bsb_opts *o, 
                 QH_HIP(hipMemcpyAsync(res->y + off * R, p.y.p, nR * sizeof(float), hipMemcpyDeviceToDevice, st));
             off += g->n;
         }
-        QH_HIP(hipStreamSynchronize(st));
+        if (bt.launches.empty()) QH_HIP(hipStreamSynchronize(st));
+        else check_waits(bt.flags.p + bt.n_flags + kBpErr, st);   // (synchronises)
         return;
     }
 
@@ -429,7 +430,14 @@ void bsb_solve_batched(const qh_graph *const *gs, int nb, const qh_bsb_opts *o, 
         d.selected_cut = res->selected_cut ? res->selected_cut + b : nullptr;
         voff += g->n;
     }
-    readout_batched(rd, R, o->greedy != 0, st);
+    try {
+        readout_batched(rd, R, o->greedy != 0, st);
+    } catch (...) {
+        (void)hipDeviceSynchronize();          // (as above)
+        // (a wait that gave up leaves NaN: report the wait, not the number)
+        if (!bt.launches.empty()) check_waits(bt.flags.p + bt.n_flags + kBpErr, st);
+        throw;
+    }
 }
 
 }  // namespace qh

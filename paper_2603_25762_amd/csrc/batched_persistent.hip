@@ -321,7 +321,7 @@ void plan_batch_teams(const qh_graph *const *gs, const std::vector<SolvePlan *> 
     bt.ptr.alloc(ptr.size());
     bt.ptr.upload(ptr.data(), ptr.size(), st);
     bt.xch.alloc((size_t)xch);
-    bt.flags.alloc((size_t)flags + 64);
+    bt.flags.alloc((size_t)flags + kBpFlagsPad);
     bt.n_flags = flags;
     QH_HIP(hipStreamSynchronize(st));                  // (the uploads read this function's vectors)
 }
@@ -342,10 +342,10 @@ void run_batch_teams(BatchTeams &bt, const qh_bsb_opts *o, double a0, const floa
         a.job_ptr = bt.ptr.p + L.ptr_at;
         a.xch = bt.xch.p;
         a.flags = bt.flags.p;
-        a.err = bt.flags.p + bt.n_flags + 32;
+        a.err = bt.flags.p + bt.n_flags + kBpErr;
         // a team may wait for a workgroup that is still busy with its earlier teams; a poll takes 0.1 us
         // or more
-        a.max_polls = std::max((int64_t)1 << 27, (int64_t)(L.us * o->steps * 64.0));
+        a.max_polls = wait_polls < kWaitPolls ? wait_polls : std::max(kWaitPolls, (int64_t)(L.us * o->steps * 64.0));
         launch_band(L.launch, a, o->variant == 1, st);
     }
 }

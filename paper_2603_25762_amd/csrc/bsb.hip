@@ -1392,14 +1392,25 @@ static void run_persistent(const qh_graph *g, SolvePlan &p, const float *pump, d
     if (err) fail(QH_EHIP, "persistent bSB kernel: a neighbour wait exceeded its poll limit");
 }
 
+// After a launch that no readout follows: a wait that gave up makes the whole state NaN and sets the
+// host's word.
+__global__ __launch_bounds__(256) void k_report_wait(const int *__restrict__ err, int *__restrict__ failed, int64_t nR,
+                                                     float *__restrict__ x, float *__restrict__ y) {
+    if (*err == 0) return;
+    for (int64_t t = blockIdx.x * 256ll + threadIdx.x; t < nR; t += gridDim.x * 256ll)
+        x[t] = y[t] = __builtin_nanf("");
+    if (blockIdx.x == 0 && threadIdx.x == 0)
+        __hip_atomic_store(failed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Steps [kb, ke) of a graph in one cooperative launch on the band plan; the state is in
 // p.xa / p.y before and after.
 static void run_band(SolvePlan &p, const float *pump, double c0, double dt, double a0, int kb, int ke, int discrete,
                      const float *field, hipStream_t st) {
     BandPersist &bp = *p.bp;
     if (ke - kb < kBpMinSteps) fail(QH_EUNSUPPORTED, "a one-launch range needs %d steps", kBpMinSteps);
-    hipLaunchKernelGGL(k_zero_i32, dim3(grid_for((int64_t)bp.flags.n)), dim3(256), 0, st, (int64_t)bp.flags.n,
-                       bp.flags.p);
+    // (the error word stays set until a call reports it)
+    hipLaunchKernelGGL(k_zero_i32, dim3(grid_for(bp.launch.n_flags)), dim3(256), 0, st, bp.launch.n_flags, bp.flags.p);
     QH_CHECK_LAUNCH();
     BandPersistArgs a{};
     a.R = p.R;
@@ -1413,8 +1424,8 @@ static void run_band(SolvePlan &p, const float *pump, double c0, double dt, doub
     a.job_ptr = bp.job_ptr.p;
     a.xch = bp.xch.p;
     a.flags = bp.flags.p;
-    a.err = bp.flags.p + bp.launch.n_flags + 32;
-    a.max_polls = (int64_t)1 << 27;
+    a.err = bp.flags.p + bp.launch.n_flags + kBpErr;
+    a.max_polls = wait_polls;
     a.single = 1;
     a.c0 = (float)c0;
     a.field = field;
@@ -1626,6 +1637,9 @@ void bsb_solve(const qh_graph *g, const qh_bsb_opts *o, qh_result *res, hipStrea
     const bool dense16 = !x_pingpong(g);
     const bool dense = g->storage == QH_STORE_DENSE;
     if (dense && o->plan >= 3) fail(QH_EINVAL, "plans 3-5 choose the step kernel of SNP (skyline) graphs");
+    // a one-launch solve with readout = 0 returned before its launch ended: its failure shows here
+    auto band_err = [&]() { return p.bp->flags.p + p.bp->launch.n_flags + kBpErr; };
+    if (p.bp && p.bp->ok && __atomic_exchange_n(p.bp->failed.p, 0, __ATOMIC_ACQ_REL)) check_waits(band_err(), st);
     // plan 0: every step in one launch with state and couplings on chip, where the graph fits (the
     // per-step kernels' results bit for bit); a stream being captured takes the per-step launches
     bool band = false;
@@ -1693,6 +1707,15 @@ void bsb_solve(const qh_graph *g, const qh_bsb_opts *o, qh_result *res, hipStrea
         p.last_plan = persistent || one_launch(kb, o->eval_every > 0 ? (int)std::min<int64_t>(ke, (int64_t)kb + o->eval_every) : ke) ? 2 : 1;
     const int coherent = o->persistent_sync == 2 || (o->persistent_sync == 0 && p.tuned_coh);
     if (persistent) p.last_coh = coherent;
+    // (a wait that gave up leaves NaN: report the wait, not the number)
+    auto read_out = [&](const float *xfin, bool finish, const EvalArgs *ev) {
+        try {
+            readout(view_of(g), p, R, xfin, p.y.p, res, o->greedy != 0, st, finish, ev);
+        } catch (const Failure &) {
+            if (band) check_waits(band_err(), st);
+            throw;
+        }
+    };
     if (o->eval_every > 0) {
         // read out after every eval_every steps: the step loop runs in ranges, each starting
         // from the state the previous one left in xa / y (and the 16-bit copy made from xa,
@@ -1717,7 +1740,7 @@ void bsb_solve(const qh_graph *g, const qh_bsb_opts *o, qh_result *res, hipStrea
                 if (res->x && nR) QH_HIP(hipMemcpyAsync(res->x, p.xa.p, nR * sizeof(float), hipMemcpyDeviceToDevice, st));
                 if (res->y && nR) QH_HIP(hipMemcpyAsync(res->y, p.y.p, nR * sizeof(float), hipMemcpyDeviceToDevice, st));
             }
-            readout(view_of(g), p, R, p.xa.p, p.y.p, res, o->greedy != 0, st, ev.last, &ev);
+            read_out(p.xa.p, ev.last, &ev);
             if (ev.last) break;
             x_to_h(g, p, n, R, o->variant == 1, st);
             k0 = k1;
@@ -1732,6 +1755,11 @@ void bsb_solve(const qh_graph *g, const qh_bsb_opts *o, qh_result *res, hipStrea
         run_persistent(g, p, pump, c0, o->dt, a0, kb, ke, o->variant == 1, o->field, coherent, st);
     } else if (one_launch(kb, ke)) {
         run_band(p, pump, c0, o->dt, a0, kb, ke, o->variant == 1, o->field, st);
+        if (!o->readout) {
+            hipLaunchKernelGGL(k_report_wait, dim3((unsigned)std::min<int64_t>(ceil_div(nR, 256), 256)), dim3(256), 0, st,
+                               band_err(), p.bp->failed.p, nR, p.xa.p, p.y.p);
+            QH_CHECK_LAUNCH();
+        }
     } else if (ke > kb && n > 0) {
         if (o->use_graph) {
             auto key = std::make_tuple(kb, ke, (int)g->dtype + 16 * p.sky_kernel, c0, o->dt, a0, pump, R,
@@ -1770,9 +1798,9 @@ void bsb_solve(const qh_graph *g, const qh_bsb_opts *o, qh_result *res, hipStrea
         EvalArgs ev;   // one evaluation, after the last step
         ev.W = g->total_weight;
         ev.energy_row = res->energy;
-        readout(view_of(g), p, R, xfin, p.y.p, res, o->greedy != 0, st, true, &ev);
+        read_out(xfin, true, &ev);
     } else {
-        readout(view_of(g), p, R, xfin, p.y.p, res, o->greedy != 0, st);
+        read_out(xfin, true, nullptr);
     }
     if (res->best_energy) {
         hipLaunchKernelGGL(k_energy, dim3(1), dim3(64), 0, st, g->total_weight, res->best_cut, res->best_energy);

@@ -43,6 +43,19 @@ void merge_pool(int device, uintptr_t tag);
 // hands every cached idle block of every device back with hipFree; returns the bytes released
 size_t release_cached();
 
+// A word of pinned host memory that kernels write and the host reads without a copy (memory.hip):
+// taken from and given back to pages that stay for the life of the process.
+int *host_word_take();
+void host_word_give(int *w);
+struct HostWord {
+    int *p = nullptr;
+    HostWord() = default;
+    HostWord(const HostWord &) = delete;
+    HostWord &operator=(const HostWord &) = delete;
+    ~HostWord() { if (p) host_word_give(p); }
+    void take() { if (!p) p = host_word_take(); }
+};
+
 // Owning device buffer.
 template <class T>
 struct DevBuf {

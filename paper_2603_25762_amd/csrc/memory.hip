@@ -22,6 +22,7 @@
 #include <map>
 #include <mutex>
 #include <unordered_map>
+#include <vector>
 
 #include "internal.h"
 
@@ -122,6 +123,28 @@ void device_free(void *p) {
     }
     c.idle[t_pool].emplace(b.cls, p);
     c.idle_bytes += b.cls;
+}
+
+// Pages of words: as many as the most words in use at once ever needed.
+namespace {
+std::vector<int *> g_words;   // free words
+}
+int *host_word_take() {
+    std::lock_guard<std::mutex> lk(g_mu);
+    if (g_words.empty()) {
+        constexpr size_t kPage = 4096;
+        void *page = nullptr;
+        QH_HIP(hipHostMalloc(&page, kPage, hipHostMallocPortable | hipHostMallocCoherent));
+        for (size_t i = 0; i < kPage / sizeof(int); ++i) g_words.push_back((int *)page + i);
+    }
+    int *w = g_words.back();
+    g_words.pop_back();
+    __atomic_store_n(w, 0, __ATOMIC_RELEASE);
+    return w;
+}
+void host_word_give(int *w) {
+    std::lock_guard<std::mutex> lk(g_mu);
+    g_words.push_back(w);
 }
 
 void set_pool(uintptr_t tag) { t_pool = tag; }

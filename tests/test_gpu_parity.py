@@ -1700,3 +1700,50 @@ def test_batch_of_one_step_teams(kind, dtype, n, steps):
             assert torch.equal(a[k], b[k]), k
     for g in gs:
         g.free()
+
+
+@pytest.fixture
+def no_polls():
+    """Waits of the one-launch plans give up at the first poll that finds a neighbour late."""
+    v = ctypes.c_int64.in_dll(qh.load(), "_ZN2qh10wait_pollsE")
+    old, v.value = v.value, 0
+    yield v
+    v.value = old
+
+
+@pytest.mark.parametrize("kind,dtype,n,reads,R", [
+    ("snp_llr", "f16", 2001, 0, 128), ("read_signed", "f32", 2300, 1501, 64), ("read_signed", "bf16", 2300, 1501, 64)])
+def test_wait_that_gives_up_is_reported(no_polls, kind, dtype, n, reads, R):
+    """A wait between workgroups that gives up: EHIP from the call itself when it reads out, from the next
+    call with the graph otherwise, and the state is NaN; afterwards the graph solves as before."""
+    g, ref = _one_launch_case(kind, dtype, n, reads, R)
+    nv = g.info()["n"]
+    x, y = (torch.zeros((nv, R), dtype=torch.float32, device="cuda") for _ in range(2))
+    for kw in (dict(), dict(eval_every=300), dict(energy=True)):
+        with pytest.raises(qh.QhapError) as e:
+            qh.bsb_solve(g, R, 1000, seed=9, **kw)
+        assert e.value.status == qh.Status.EHIP and "wait" in str(e.value)
+    qh.bsb_solve(g, R, 1000, seed=9, x=x, y=y, readout=False)
+    torch.cuda.synchronize()
+    assert torch.isnan(x).any() and torch.equal(torch.isnan(x), torch.isnan(y))
+    no_polls.value = 2 ** 27
+    with pytest.raises(qh.QhapError) as e:
+        qh.bsb_solve(g, R, 1000, init=False, x=x, y=y, step_begin=500, readout=False)
+    assert e.value.status == qh.Status.EHIP
+    a = qh.bsb_solve(g, R, 1000, seed=9, x=x)
+    b = qh.bsb_solve(g, R, 1000, seed=9, x=y, plan=ref)
+    assert g.plan_info(R)["plan_used"] == 1
+    assert torch.equal(x, y) and torch.equal(a["best_cut"], b["best_cut"])
+
+
+@pytest.mark.parametrize("readout", [True, False])
+def test_batch_wait_that_gives_up_is_reported(team_batch, no_polls, readout):
+    """The same for the teams of a batch, which synchronises: EHIP with and without a readout."""
+    gs = team_batch[-8:]
+    with pytest.raises(qh.QhapError) as e:
+        qh.bsb_solve_batched(gs, 32, 500, seed=5, readout=readout)
+    assert e.value.status == qh.Status.EHIP and "wait" in str(e.value)
+    no_polls.value = 2 ** 27
+    a = qh.bsb_solve_batched(gs, 32, 100, seed=5, plan=1)
+    b = qh.bsb_solve_batched(gs, 32, 100, seed=5)
+    assert torch.equal(a["best_spins"], b["best_spins"]) and torch.equal(a["best_cut"], b["best_cut"])
