@@ -1459,14 +1459,15 @@ static int default_tile(const qh_graph *g, int R) {
 // Autotuner for plan 0 on dense 16/8-bit graphs: time a short run of each candidate on
 // scratch state -- one fused kernel per step, and the persistent launch -- and keep the
 // faster.  Both compute bit-identical results, so the choice only affects speed.  A warm step
-// or two, then `nt` steps: 64 steps twice for each of four to six candidates took as long as a
+// or two, then 16 steps (`brief`: two, for the report of a solve that does not act on it): 64 steps twice for each of four to six candidates took as long as a
 // 500-step solve, and the candidates differ by 10 % or more from the first steps on (1,501
 // reads, F32, R = 64: 14.3, 14.2, 8.6 and 8.2 us).
 static void autotune_dense(const qh_graph *g, SolvePlan &p, const qh_bsb_opts *o, const float *pump, double c0,
-                           double a0, int nt, hipStream_t st) {
+                           double a0, bool brief, hipStream_t st) {
     const int64_t n = g->n;
     const int R = p.R;
-    nt = std::min(o->steps, nt);
+    const int nt = std::min(o->steps, brief ? 2 : 16);
+    p.tuned_brief = brief;
     const bool pers_ok = p.pp && p.pp->ok;
     // per-step candidates (replica tile, tiles in flight for 64-replica tiles: 64 + depth 4
     // is coded as 65), then 0 = persistent
@@ -1524,14 +1525,15 @@ static void autotune_dense(const qh_graph *g, SolvePlan &p, const qh_bsb_opts *o
     p.run_depth = p.tuned_depth;
 }
 
-// SNP graphs: time the two band kernels (a warm step, then nt steps each) and keep the faster;
+// SNP graphs: time the two band kernels (a warm step, then four each, or two: brief) and keep the faster;
 // the band FMA kernel needs 64-replica tiles.  The two differ by 1.6x (2,001 SNPs, R = 128) to
 // 3.2x (the Pore-C chromosome graph), so a few steps tell them apart; 64 steps twice cost a
 // quarter of a 1,000-step chromosome job.  The state's values do not matter to the timing.
 static void autotune_sky(const qh_graph *g, SolvePlan &p, const qh_bsb_opts *o, const float *pump, double c0,
-                         double a0, int nt, hipStream_t st) {
+                         double a0, bool brief, hipStream_t st) {
     const int R = p.R;
-    nt = std::min(o->steps, nt);
+    const int nt = std::min(o->steps, brief ? 2 : 4);
+    p.sky_brief = brief;
     std::vector<int> cands;
     if (R >= 64) cands.push_back(kSkyBandFma);
     cands.push_back(kSkyBandMfma);
@@ -1601,7 +1603,7 @@ void autotune(const qh_graph *g, const qh_bsb_opts *o, qh_bsb_opts *chosen, floa
             build_persistent_plan(g, R, *p.pp, st);
             p.pp_tried = true;
         }
-        if (!p.tuned_plan) autotune_dense(g, p, o, pump, c0, a0, 16, st);
+        if (!p.tuned_plan || p.tuned_brief) autotune_dense(g, p, o, pump, c0, a0, false, st);
         if (dense16 && p.pp && p.pp->ok && p.tuned_plan == 2) {
             chosen->plan = 2;
             chosen->persistent_sync = p.tuned_coh ? 2 : 1;
@@ -1615,7 +1617,7 @@ void autotune(const qh_graph *g, const qh_bsb_opts *o, qh_bsb_opts *chosen, floa
             us[0] = p.tuned_us[0];
         }
     } else {
-        if (!p.sky_tuned) autotune_sky(g, p, o, pump, c0, a0, 4, st);
+        if (!p.sky_tuned || p.sky_brief) autotune_sky(g, p, o, pump, c0, a0, false, st);
         chosen->plan = p.sky_best == kSkyBandMfma ? 5 : p.sky_best == kSkyBandFma ? 4 : 3;
         us[0] = p.sky_us[kSkyBandFma];
         us[1] = p.sky_us[kSkyBandMfma];
@@ -1643,7 +1645,8 @@ void bsb_solve(const qh_graph *g, const qh_bsb_opts *o, qh_result *res, hipStrea
     // plan 0: every step in one launch with state and couplings on chip, where the graph fits (the
     // per-step kernels' results bit for bit); a stream being captured takes the per-step launches
     bool band = false;
-    if (o->plan == 0 && ke > kb && n > 0 && !stream_capturing(st)) {
+    const bool capturing = stream_capturing(st);
+    if (o->plan == 0 && ke > kb && n > 0 && !capturing) {
         if (!p.bp_tried) {
             p.bp = std::make_shared<BandPersist>();
             build_band_plan(g, p, *p.bp, st);
@@ -1659,7 +1662,9 @@ void bsb_solve(const qh_graph *g, const qh_bsb_opts *o, qh_result *res, hipStrea
         // (band FMAs when never tuned)
         int want = o->plan == 3 ? kSkyRows : o->plan == 4 ? kSkyBandFma : o->plan == 5 ? kSkyBandMfma : -1;
         if (want < 0) {
-            if (o->plan == 0 && !p.sky_tuned && ke > kb && n > 0) autotune_sky(g, p, o, pump, c0, a0, band ? 2 : 4, st);
+            // (a graph on the band plan is timed briefly, for the report only)
+            if (ke > kb && n > 0 && ((o->plan == 0 && !p.sky_tuned) || (p.sky_brief && !band && !capturing)))
+                autotune_sky(g, p, o, pump, c0, a0, band, st);
             // (ranges too short for the one-launch plan take the kernel that adds in its order)
             want = p.sky_tuned && !band ? p.sky_best : kSkyBandFma;
         }
@@ -1672,13 +1677,15 @@ void bsb_solve(const qh_graph *g, const qh_bsb_opts *o, qh_result *res, hipStrea
     bool persistent = false;
     const bool want_persistent = o->plan == 0 || o->plan == 2;
     if (dense && ke > kb && n > 0) {
-        if (dense16 && want_persistent && !band && !p.pp_tried) {
+        // (a graph on the band plan is timed briefly, for the report only)
+        const bool again = p.tuned_brief && !band && !capturing &&
+                           (o->plan == 0 || (o->plan == 1 ? o->replica_tile == 0 : o->persistent_sync == 0));
+        if (dense16 && (want_persistent || again) && !band && !p.pp_tried) {
             p.pp = std::make_shared<PersistPlan>();
             build_persistent_plan(g, R, *p.pp, st);
             p.pp_tried = true;
         }
-        // (a graph on the band plan is timed briefly, for the report and for later plan-1 solves)
-        if (o->plan == 0 && !p.tuned_plan) autotune_dense(g, p, o, pump, c0, a0, band ? 2 : 16, st);
+        if ((o->plan == 0 && !p.tuned_plan) || again) autotune_dense(g, p, o, pump, c0, a0, band, st);
         if (dense16 && want_persistent && !band && p.pp->ok) persistent = o->plan == 2 || p.tuned_plan == 2;
     }
     // replica tile of the per-step dense kernel: the caller's, else the tuned one, else by the fill

@@ -128,9 +128,12 @@ struct SolvePlan {
     std::shared_ptr<BandPersist> bp;   // persistent band plan (null until tried)
     bool bp_tried = false;
     int tuned_plan = 0;                // autotuner's choice for plan 0: 1 per-step, 2 persistent
+    bool tuned_brief = false;          // timed over two steps beside a one-launch solve, without the
+                                       // persistent plan: a call that acts on the choice times again
     int last_plan = 0;                 // plan the last solve ran
     int sky_kernel = 0;                // SNP graphs: kSkyBandFma, kSkyBandMfma or kSkyRows
     bool sky_tuned = false;            // the band kernels have been timed on this graph
+    bool sky_brief = false;            // (as tuned_brief)
     int sky_best = 0;                  // the faster band kernel
     float sky_us[3] = {0, 0, 0};       // measured microseconds per step of each kernel
     float tuned_us[2] = {0, 0};        // measured microseconds per step: per-step, persistent (fences)

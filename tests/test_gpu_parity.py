@@ -1747,3 +1747,46 @@ def test_batch_wait_that_gives_up_is_reported(team_batch, no_polls, readout):
     a = qh.bsb_solve_batched(gs, 32, 100, seed=5, plan=1)
     b = qh.bsb_solve_batched(gs, 32, 100, seed=5)
     assert torch.equal(a["best_spins"], b["best_spins"]) and torch.equal(a["best_cut"], b["best_cut"])
+
+
+def test_choice_of_plans_after_a_one_launch_solve():
+    """A plan-0 solve in one launch times the per-step kernels briefly and without the persistent plan;
+    whatever acts on the choice later (qh_autotune, plan 2's way to synchronise, plan 0 where the
+    one-launch plan does not apply) times every candidate, as on a fresh graph."""
+    wm = synth.read_mhc(seed=78, n_snp=1500, n_reads=1000, region=500_000)
+
+    def solved(w, R):
+        g = gpu_graph(w, "read_signed", "f16")
+        qh.bsb_solve(g, R, 100, seed=3)
+        info = g.plan_info(R)
+        assert info["plan_used"] == 2 and info["us_per_step"][1] == 0 and info["us_persistent_coherent"] == 0
+        return g
+
+    def timed(g, R):
+        info = g.plan_info(R)
+        assert min(info["us_per_step"]) > 0 and info["us_persistent_coherent"] > 0
+        return info
+
+    g = solved(wm, 64)
+    ch = qh.autotune(g, 64, 200)
+    info = timed(g, 64)
+    best = min(info["us_per_step"][1], info["us_persistent_coherent"])
+    assert ch["plan"] == (2 if best < info["us_per_step"][0] else 1)
+    g = solved(wm, 64)
+    qh.bsb_solve(g, 64, 100, seed=3, plan=2)
+    info = timed(g, 64)
+    assert info["persistent_sync"] == (2 if info["us_persistent_coherent"] < info["us_per_step"][1] else 1) or \
+        info["us_per_step"][0] < min(info["us_per_step"][1], info["us_persistent_coherent"])
+    g = solved(wm, 64)
+    qh.bsb_solve(g, 64, 100, seed=3, plan=1)
+    timed(g, 64)
+    # row tiles that skip column tiles: a field goes through the per-step or the persistent kernel
+    w = synth.read_small(6, 200000, 700, (2, 4))
+    perm = np.random.default_rng(1).permutation(700)
+    cnt = np.diff(w.frag_ptr)
+    idx = np.concatenate([np.arange(w.frag_ptr[f], w.frag_ptr[f + 1]) for f in perm])
+    w.frag_ptr = np.concatenate([[0], np.cumsum(cnt[perm])]).astype(np.int64)
+    w.snp, w.allele, w.phred = w.snp[idx], w.allele[idx], w.phred[idx]
+    g = solved(w, 64)
+    qh.bsb_solve(g, 64, 100, seed=3, field=torch.zeros(700, dtype=torch.float32, device="cuda"))
+    timed(g, 64)
