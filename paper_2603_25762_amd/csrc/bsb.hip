@@ -1473,12 +1473,12 @@ static void autotune_dense(const qh_graph *g, SolvePlan &p, const qh_bsb_opts *o
     // is coded as 65), then 0 = persistent
     std::vector<int> cands;
     if (R >= 64) cands = {64, 65, 32, 16};
-    else cands = {R};
+    else cands = {default_tile(g, R)};
     if (pers_ok) { cands.push_back(0); cands.push_back(-1); }   // persistent: fences; coherent accesses
     p.tuned_plan = 1;
     p.tuned_rt = cands[0];
     p.tuned_depth = 2;
-    p.run_rt = R >= 64 ? 64 : R;
+    p.run_rt = cands[0];
     p.run_depth = 2;
     if (cands.size() == 1) return;          // nothing to choose
     hipEvent_t e0, e1;

@@ -1790,3 +1790,15 @@ def test_choice_of_plans_after_a_one_launch_solve():
     g = solved(w, 64)
     qh.bsb_solve(g, 64, 100, seed=3, field=torch.zeros(700, dtype=torch.float32, device="cuda"))
     timed(g, 64)
+
+
+@pytest.mark.parametrize("reads,R,dtype,tile", [(1600, 32, "f16", 16), (1600, 32, "f32", 32), (1600, 16, "fp8", 16),
+                                                (13000, 32, "bf16", 32)])
+def test_default_tile_outlives_a_plan_0_solve(reads, R, dtype, tile):
+    """Fewer than 64 replicas: the per-step kernel's tile is chosen by the fill before and after a
+    plan-0 solve, and plan_info reports the tile that ran."""
+    g = gpu_graph(synth.read_small(9, reads * 3 // 2, reads, (20, 60)), "read_signed", dtype)
+    for plan in (1, 0, 1):
+        qh.bsb_solve(g, R, 20, seed=3, plan=plan)
+        if plan == 1:
+            assert g.plan_info(R)["replica_tile"] == tile
