@@ -83,6 +83,7 @@ struct BandPersist {
     bool ok = false;
     BandLaunch launch;
     int passes = 0;             // most jobs of one workgroup
+    int min_steps = 0;          // a shorter range is faster in per-step launches
     bool gaps = false;          // dense graphs: some row tile's stored tiles are not consecutive
     DevBuf<BandTeam> team;
     DevBuf<int64_t> off;        // dense graphs: the strips as band blocks

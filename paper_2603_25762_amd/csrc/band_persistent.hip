@@ -224,6 +224,12 @@ bool build_band_plan(const qh_graph *g, SolvePlan &p, BandPersist &bp, hipStream
         T.bscale = tiles ? 1.0f : g->bb_scale;
         T.n = (int32_t)g->n;
         bp.passes = c.passes;
+        // A cooperative launch that loads state and couplings starts 18 us (60 reads) to 50 us (250,000
+        // SNPs) later than a per-step one; a step then saves 3 to 32 us.  us per range, per-step launches / one
+        // launch, at 1, 4 and 8 steps: 2,001 SNPs, R = 64 34 / 58, 59 / 65, 106 / 78; 250,000 SNPs 197 / 244,
+        // 365 / 312, 607 / 412; FP32, 8,000 reads, R = 64 39 / 62, 66 / 76, 110 / 95.  16- and 8-bit dense graphs
+        // took a cooperative launch before: from two steps on.
+        bp.min_steps = strips ? kBpMinSteps : tiles ? 8 : step_us >= 20.0 ? 3 : 6;
         bp.team.alloc(1);
         bp.team.upload(&T, 1, st);
         bp.jobs.alloc(bl.jobs.size());

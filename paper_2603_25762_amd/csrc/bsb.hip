@@ -560,8 +560,10 @@ __device__ inline void band_block_step(int64_t blk, int64_t n, int64_t R, int64_
 // holds row l % 16 of column l / 16), so four columns arrive with one 64-lane load; x rows
 // L + j .. L + j + 3 of 16 replicas are the B operand.  NB = 16-replica blocks per wave
 // (all 64 lanes busy for any replica count).  Values enter in FP32 (16-bit codes widened
-// exactly); the MFMA sums each group of four columns before adding it, so results match
-// the FMA kernels to FP32 rounding, not bit for bit.  Output: lane l owns rows
+// exactly); the MFMA adds its four products one by one, each with one rounding, so a row's sum runs
+// over its columns in the order of the FMA kernels (columns past W add 0 to a sum that is never
+// -0) and the results are theirs bit for bit: plan 0 may change between them and the one-launch
+// plan within a schedule.  Output: lane l owns rows
 // 4 (l / 16) .. + 3 of the block and replica r0 + 16 b + l % 16.
 template <int DT, int NB>
 __device__ inline void band_block_step_mfma(int64_t blk, int64_t n, int64_t R, int64_t r0,
@@ -1665,8 +1667,7 @@ void bsb_solve(const qh_graph *g, const qh_bsb_opts *o, qh_result *res, hipStrea
             // (a graph on the band plan is timed briefly, for the report only)
             if (ke > kb && n > 0 && ((o->plan == 0 && !p.sky_tuned) || (p.sky_brief && !band && !capturing)))
                 autotune_sky(g, p, o, pump, c0, a0, band, st);
-            // (ranges too short for the one-launch plan take the kernel that adds in its order)
-            want = p.sky_tuned && !band ? p.sky_best : kSkyBandFma;
+            want = p.sky_tuned ? p.sky_best : kSkyBandFma;
         }
         p.sky_kernel = want;
     }
@@ -1709,7 +1710,7 @@ void bsb_solve(const qh_graph *g, const qh_bsb_opts *o, qh_result *res, hipStrea
         x_to_h(g, p, n, R, o->variant == 1, st);
     };
     load_state();
-    auto one_launch = [&](int k0, int k1) { return band && k1 - k0 >= kBpMinSteps; };
+    auto one_launch = [&](int k0, int k1) { return band && k1 - k0 >= p.bp->min_steps; };
     if (ke > kb && n > 0)
         p.last_plan = persistent || one_launch(kb, o->eval_every > 0 ? (int)std::min<int64_t>(ke, (int64_t)kb + o->eval_every) : ke) ? 2 : 1;
     const int coherent = o->persistent_sync == 2 || (o->persistent_sync == 0 && p.tuned_coh);

@@ -129,7 +129,7 @@ struct SolvePlan {
     bool bp_tried = false;
     int tuned_plan = 0;                // autotuner's choice for plan 0: 1 per-step, 2 persistent
     bool tuned_brief = false;          // timed over two steps beside a one-launch solve, without the
-                                       // persistent plan: a call that acts on the choice times again
+                                       // persistent plan: other calls that act on it time again
     int last_plan = 0;                 // plan the last solve ran
     int sky_kernel = 0;                // SNP graphs: kSkyBandFma, kSkyBandMfma or kSkyRows
     bool sky_tuned = false;            // the band kernels have been timed on this graph

@@ -1802,3 +1802,37 @@ def test_default_tile_outlives_a_plan_0_solve(reads, R, dtype, tile):
         qh.bsb_solve(g, R, 20, seed=3, plan=plan)
         if plan == 1:
             assert g.plan_info(R)["replica_tile"] == tile
+
+
+@pytest.mark.parametrize("n,gap,dtype,R", BAND_PLAN_CASES[:9])
+def test_band_mfma_equals_per_row_bit_exact(n, gap, dtype, R):
+    """Band blocks on MFMAs against the per-row kernel, bit for bit: plan 0 runs ranges too short for one
+    launch on either, and a schedule split into ranges has to give the same state however it is
+    split."""
+    g = gpu_graph(synth.snp_small(5, n_snp=n, gap_mean=gap), "snp_llr", dtype)
+    field = torch.linspace(-0.3, 0.3, n, dtype=torch.float32, device="cuda")
+    for kw in (dict(step_end=40), dict(step_end=40, field=field), dict(step_end=40, discrete=True)):
+        got = []
+        for plan in (3, 5, 0):
+            x, y = (torch.empty((n, R), dtype=torch.float32, device="cuda") for _ in range(2))
+            if plan:
+                qh.bsb_solve(g, R, 60, seed=9, x=x, y=y, plan=plan, readout=False, **kw)
+            else:
+                for a, b in ((0, 1), (1, 3), (3, 6), (6, 11), (11, 17), (17, 40)):
+                    qh.bsb_solve(g, R, 60, seed=9, x=x, y=y, readout=False, init=a == 0,
+                                 **{**kw, "step_begin": a, "step_end": b})
+            got.append((x, y))
+        for x, y in got[1:]:
+            assert torch.equal(got[0][0], x) and torch.equal(got[0][1], y)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+def test_band_mfma_equals_per_row_bit_exact_long_range(dtype):
+    w = synth.snp_porec(43, n_snp=2500, n_edges=4000, zipf_s=1.0)
+    g = gpu_graph(w, "snp_llr", dtype, band_limit=100)
+    got = []
+    for plan in (3, 5):
+        x, y = (torch.empty((2500, 64), dtype=torch.float32, device="cuda") for _ in range(2))
+        qh.bsb_solve(g, 64, 200, seed=9, x=x, y=y, plan=plan, readout=False)
+        got.append((x, y))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
