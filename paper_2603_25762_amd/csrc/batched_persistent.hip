@@ -50,6 +50,14 @@ __global__ __launch_bounds__(256) void k_batch_geometry(const GeomDesc *__restri
     if (threadIdx.x == 0) gap[blockIdx.x] = any;
 }
 
+// Shorter schedules keep the per-step launches: geometry, placement, tables and cooperative launches cost a
+// call 90 us (2 blocks) to 500 us (200 uneven ones) that they do not earn back.  us per call of 8 / 16 /
+// 32 steps, per-step / teams: 2 blocks of 50-100, R = 16 190 / 268, 244 / 281, 350 / 316; 200 SNP blocks of
+// 50-3,000 896 / 995, 1,182 / 1,062, 1,733 / 1,199; 600 blocks of 50-300, R = 64 1,527 / 1,779, 1,819 / 1,867,
+// 2,424 / 2,030.
+constexpr int kTeamMinSteps = 24;
+static_assert(kTeamMinSteps >= kBpMinSteps);
+
 namespace {
 
 struct Geo {
@@ -168,7 +176,7 @@ void plan_batch_teams(const qh_graph *const *gs, const std::vector<SolvePlan *> 
     QH_HIP(hipGetDevice(&dev));
     QH_HIP(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
     QH_HIP(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev));
-    if (!coop || n_cu < 1 || o->steps < kBpMinSteps || o->steps >= (1 << 30)) return;
+    if (!coop || n_cu < 1 || o->steps < kTeamMinSteps || o->steps >= (1 << 30)) return;
 
     // geometry: dense blocks' strips first (they have tables of their own), then band blocks
     std::vector<GeomDesc> gd(nb);

@@ -1683,11 +1683,11 @@ def test_one_launch_of_one_step(kind, dtype, n, reads, R):
         assert torch.equal(a, b)
 
 
-@pytest.mark.parametrize("steps", [1, 2])
+@pytest.mark.parametrize("steps", [1, 2, 23, 24, 40])
 @pytest.mark.parametrize("kind,dtype,n", [("snp_llr", "bf16", 2500), ("read_signed", "fp8", 1300)])
-def test_batch_of_one_step_teams(kind, dtype, n, steps):
+def test_batch_of_few_steps(kind, dtype, n, steps):
     """More teams of several workgroups than the chip holds at once, so that a team's workgroups start at
-    different times: schedules of one and two steps, against one launch per step, bit for bit."""
+    different times, and schedules too short for teams, against one launch per step, bit for bit."""
     w = synth.snp_small(41, n_snp=n) if kind == "snp_llr" else synth.read_small(42, 400, n, (20, 120))
     d = device_reads(w)
     gs = qh.build_graphs([dict(frag_ptr=d["frag_ptr"], snp=d["snp"], allele=d["allele"], phred=d["phred"],
