@@ -130,39 +130,62 @@ __device__ inline void cut_chunks_body(int64_t bx, int64_t gx, int64_t n_chunks,
     }
 }
 
-// cut_rc[r][c] = sum of the component's chunk partials, chunks in order; a workgroup item is one
-// component and kReduceR replicas.  A component of more than kStage chunks stages them through LDS, so
-// that the partials arrive with all threads' loads in flight and the serial sum reads LDS: a
-// chromosome's 7,813 chunks took 1.25 ms as a chain of loads.
+// cut_rc[r][c] = sum of the component's chunk partials, chunks in order: components of up to kStage
+// chunks a workgroup each, the replicas over its threads.
 constexpr int kStage = 64;
-constexpr int kStageElems = 4096;
-constexpr int kReduceR = 16;
-__host__ __device__ inline int reduce_blocks(int R) { return (R + kReduceR - 1) / kReduceR; }
 __device__ inline void cut_reduce_body(int64_t bx, int64_t gx, int64_t n_comp, int R,
                                        const int32_t *__restrict__ comp_chunk_ptr, const double *__restrict__ part,
                                        double *__restrict__ cut_rc) {
-    __shared__ double sh[kStageElems];
-    const int nrb = reduce_blocks(R);
-    for (int64_t it = bx; it < n_comp * nrb; it += gx) {
-        const int64_t c = it / nrb;
-        const int r0 = (int)(it - c * nrb) * kReduceR, rb = min(R - r0, kReduceR);   // this item's replicas
+    for (int64_t c = bx; c < n_comp; c += gx) {
         const int ch0 = comp_chunk_ptr[c], ch1 = comp_chunk_ptr[c + 1];
+        if (ch1 - ch0 > kStage) continue;
+        for (int r = threadIdx.x; r < R; r += blockDim.x) {
+            double acc = 0.0;
+            for (int ch = ch0; ch < ch1; ++ch) acc += part[(int64_t)ch * R + r];
+            cut_rc[(int64_t)r * n_comp + c] = acc;
+        }
+    }
+}
+
+// The larger components, in a launch of their own: a workgroup item is one component and kReduceR
+// replicas, and stages the partials through LDS, so that they arrive with all threads' loads in
+// flight and the serial sum reads LDS (a chromosome's 7,813 chunks took 1.25 ms as a chain of loads, now
+// 0.19).  Every item on the staged path, small components too, made a readout of 11,582
+// components 4-6 % slower.  An item finds its component by a chunk: every kStage + 1 chunks hold the
+// first multiple of kStage + 1 of at most one larger component, and each larger one has one.
+constexpr int kStageElems = 4096;
+constexpr int kReduceR = 16;
+__host__ __device__ inline int64_t staged_items(int64_t n_comp, int64_t n_chunks, int R) {
+    if (n_chunks < n_comp + kStage) return 0;          // (every component has a chunk: none is larger)
+    return (n_chunks + kStage) / (kStage + 1) * ((R + kReduceR - 1) / kReduceR);
+}
+__device__ inline void cut_reduce_staged_body(int64_t bx, int64_t gx, int64_t n_comp, int64_t n_chunks, int R,
+                                              const int32_t *__restrict__ comp_chunk_ptr,
+                                              const double *__restrict__ part, double *__restrict__ cut_rc) {
+    __shared__ double sh[kStageElems];
+    const int nrb = (R + kReduceR - 1) / kReduceR;
+    const int64_t items = staged_items(n_comp, n_chunks, R);
+    for (int64_t it = bx; it < items; it += gx) {
+        const int q = (int)(it / nrb) * (kStage + 1);
+        int64_t c = 0, hi = n_comp;                    // the last component c with comp_chunk_ptr[c] <= q
+        while (hi - c > 1) {
+            const int64_t m = (c + hi) >> 1;
+            if (comp_chunk_ptr[m] <= q) c = m; else hi = m;
+        }
+        const int ch0 = comp_chunk_ptr[c], ch1 = comp_chunk_ptr[c + 1];
+        if (ch1 - ch0 <= kStage || q - (kStage + 1) >= ch0) continue;
+        const int r0 = (int)(it % nrb) * kReduceR, rb = min(R - r0, kReduceR);   // this item's replicas
         double acc = 0.0;
-        if (ch1 - ch0 <= kStage) {
-            if ((int)threadIdx.x < rb)
-                for (int ch = ch0; ch < ch1; ++ch) acc += part[(int64_t)ch * R + r0 + threadIdx.x];
-        } else {
-            const int nst = min(kStageElems / rb, 1024);                 // chunks per stage
-            for (int b = ch0; b < ch1; b += nst) {
-                const int m = min(nst, ch1 - b);
-                __syncthreads();
-                for (int e = threadIdx.x; e < m * rb; e += blockDim.x)
-                    sh[e] = part[(int64_t)(b + e / rb) * R + r0 + e % rb];
-                __syncthreads();
-                if ((int)threadIdx.x < rb) {
+        const int nst = min(kStageElems / rb, 1024);                     // chunks per stage
+        for (int b = ch0; b < ch1; b += nst) {
+            const int m = min(nst, ch1 - b);
+            __syncthreads();
+            for (int e = threadIdx.x; e < m * rb; e += blockDim.x)
+                sh[e] = part[(int64_t)(b + e / rb) * R + r0 + e % rb];
+            __syncthreads();
+            if ((int)threadIdx.x < rb) {
 #pragma unroll 8
-                    for (int ch = 0; ch < m; ++ch) acc += sh[ch * rb + threadIdx.x];
-                }
+                for (int ch = 0; ch < m; ++ch) acc += sh[ch * rb + threadIdx.x];
             }
         }
         if ((int)threadIdx.x < rb) cut_rc[(int64_t)(r0 + threadIdx.x) * n_comp + c] = acc;
@@ -297,6 +320,19 @@ __global__ void k_cut_chunks(int64_t n_chunks, int R, const int32_t *cb, const i
 __global__ void k_cut_reduce(int64_t n_comp, int R, const int32_t *ccp, const double *part, double *cut_rc) {
     cut_reduce_body(QH_G, n_comp, R, ccp, part, cut_rc);
 }
+__global__ __launch_bounds__(256) void k_cut_reduce_staged(int64_t n_comp, int64_t n_chunks, int R, const int32_t *ccp,
+                                                           const double *part, double *cut_rc) {
+    cut_reduce_staged_body(QH_G, n_comp, n_chunks, R, ccp, part, cut_rc);
+}
+static void launch_cut_reduce(const ReadoutView &g, int R, int threads, const double *part, double *cut_rc,
+                              hipStream_t st) {
+    hipLaunchKernelGGL(k_cut_reduce, dim3((unsigned)std::min<int64_t>(g.n_comp, 1 << 20)), dim3(threads), 0, st, g.n_comp,
+                       R, g.comp_chunk_ptr, part, cut_rc);
+    const int64_t items = staged_items(g.n_comp, g.n_chunks, R);
+    if (items)
+        hipLaunchKernelGGL(k_cut_reduce_staged, dim3((unsigned)std::min<int64_t>(items, 1 << 20)), dim3(256), 0, st,
+                           g.n_comp, g.n_chunks, R, g.comp_chunk_ptr, part, cut_rc);
+}
 __global__ void k_select(int64_t n_comp, int R, const double *cut_rc, int32_t *best_r) {
     select_body(QH_G, n_comp, R, cut_rc, best_r);
 }
@@ -410,8 +446,7 @@ void readout(const ReadoutView &g, SolvePlan &p, int R, const float *xfin, const
                            g.m_ptr, g.m_col, g.m_val, p.spins.p, p.rowcut.p);
         hipLaunchKernelGGL(k_cut_chunks, dim3(grid_for(g.n_chunks * R)), dim3(256), 0, st, g.n_chunks, R,
                            g.chunk_begin, g.chunk_end, p.rowcut.p, p.part.p);
-        hipLaunchKernelGGL(k_cut_reduce, dim3((unsigned)std::min<int64_t>(nc * reduce_blocks(R), 1 << 20)), dim3(256), 0, st, nc, R,
-                           g.comp_chunk_ptr, p.part.p, p.cut_rc.p);
+        launch_cut_reduce(g, R, 256, p.part.p, p.cut_rc.p, st);
         hipLaunchKernelGGL(k_select, dim3(grid_for(nc)), dim3(256), 0, st, nc, R, p.cut_rc.p, p.best_r.p);
         hipLaunchKernelGGL(k_replica_totals, dim3(grid_for(R)), dim3(256), 0, st, nc, R, p.cut_rc.p, res->cuts);
         if (!ev)
@@ -488,8 +523,7 @@ void readout(const ReadoutView &g, SolvePlan &p, int R, const float *xfin, const
                            g.m_ptr, g.m_col, g.m_val, res->best_spins, p.rowcut.p);
         hipLaunchKernelGGL(k_cut_chunks, dim3(grid_for(g.n_chunks)), dim3(256), 0, st, g.n_chunks, 1,
                            g.chunk_begin, g.chunk_end, p.rowcut.p, p.part1.p);
-        hipLaunchKernelGGL(k_cut_reduce, dim3((unsigned)std::min<int64_t>(nc, 1 << 20)), dim3(256), 0, st, nc, 1,
-                           g.comp_chunk_ptr, p.part1.p, p.cut1.p);
+        launch_cut_reduce(g, 1, 64, p.part1.p, p.cut1.p, st);
         hipLaunchKernelGGL(k_selected_total, dim3(1), dim3(256), 0, st, nc, p.cut1.p, (const int32_t *)nullptr,
                            res->best_cut);
         QH_CHECK_LAUNCH();
@@ -561,7 +595,7 @@ __device__ inline void gain_wave_body(int64_t bx, int64_t gx, int64_t n, const i
     }
 }
 
-enum : int { kSigns, kRowsR, kChunksR, kReduce, kComp, kOne, kVert, kRows1, kChunks1, kGain, kSlices };
+enum : int { kSigns, kRowsR, kChunksR, kReduce, kStaged, kStaged1, kComp, kOne, kVert, kRows1, kChunks1, kGain, kSlices };
 
 #define QH_B(slice)                                     \
     int64_t bx, gx;                                     \
@@ -590,6 +624,14 @@ __global__ void kb_cut_reduce(const ReadoutDesc *tbl, const int32_t *wg, int nb,
     if (final_cut && D.integer) return;
     cut_reduce_body(bx, gx, D.n_comp, final_cut ? 1 : R, D.comp_chunk_ptr, final_cut ? D.part1 : D.part,
                     final_cut ? D.cut1 : D.cut_rc);
+}
+// SLICE: kStaged (R replicas) or kStaged1 (the final cut)
+template <int SLICE>
+__global__ __launch_bounds__(256) void kb_cut_reduce_staged(const ReadoutDesc *tbl, const int32_t *wg, int nb, int R) {
+    QH_B(SLICE);
+    const bool one = SLICE == kStaged1;
+    cut_reduce_staged_body(bx, gx, D.n_comp, D.n_chunks, R, D.comp_chunk_ptr, one ? D.part1 : D.part,
+                           one ? D.cut1 : D.cut_rc);
 }
 __global__ void kb_select(const ReadoutDesc *tbl, const int32_t *wg, int nb, int R) {
     QH_B(kComp);
@@ -676,7 +718,9 @@ void readout_batched(const std::vector<ReadoutDesc> &descs_in, int R, bool greed
     fill(kSigns, [&](const ReadoutDesc &d) { return grid_for(d.n * R); });
     fill(kRowsR, [&](const ReadoutDesc &d) { return grid_for(d.n_ord * rows_threads(R)); });
     fill(kChunksR, [&](const ReadoutDesc &d) { return grid_for(d.n_chunks * R); });
-    fill(kReduce, [&](const ReadoutDesc &d) { return (int)std::max<int64_t>(1, std::min<int64_t>(d.n_comp * reduce_blocks(R), 1 << 20)); });
+    fill(kReduce, [&](const ReadoutDesc &d) { return (int)std::max<int64_t>(1, std::min<int64_t>(d.n_comp, 1 << 20)); });
+    fill(kStaged, [&](const ReadoutDesc &d) { return (int)std::min<int64_t>(staged_items(d.n_comp, d.n_chunks, R), 1 << 20); });
+    fill(kStaged1, [&](const ReadoutDesc &d) { return d.integer ? 0 : (int)std::min<int64_t>(staged_items(d.n_comp, d.n_chunks, 1), 1 << 20); });
     fill(kComp, [&](const ReadoutDesc &d) { return grid_for(d.n_comp); });
     fill(kOne, [&](const ReadoutDesc &) { return 1; });
     fill(kVert, [&](const ReadoutDesc &d) { return grid_for(d.n); });
@@ -699,6 +743,7 @@ void readout_batched(const std::vector<ReadoutDesc> &descs_in, int R, bool greed
     hipLaunchKernelGGL(kb_cut_rows, dim3(total(kRowsR)), dim3(256), 0, st, T, W, nb, R, 0);
     hipLaunchKernelGGL(kb_cut_chunks, dim3(total(kChunksR)), dim3(256), 0, st, T, W, nb, R, 0);
     hipLaunchKernelGGL(kb_cut_reduce, dim3(total(kReduce)), dim3(256), 0, st, T, W, nb, R, 0);
+    if (total(kStaged)) hipLaunchKernelGGL(kb_cut_reduce_staged<kStaged>, dim3(total(kStaged)), dim3(256), 0, st, T, W, nb, R);
     hipLaunchKernelGGL(kb_select, dim3(total(kComp)), dim3(256), 0, st, T, W, nb, R);
     hipLaunchKernelGGL(kb_totals, dim3(total(kOne)), dim3(256), 0, st, T, W, nb, R, 0);
     hipLaunchKernelGGL(kb_best_spins, dim3(total(kVert)), dim3(256), 0, st, T, W, nb, R);
@@ -719,7 +764,8 @@ void readout_batched(const std::vector<ReadoutDesc> &descs_in, int R, bool greed
     }
     if (total(kRows1)) hipLaunchKernelGGL(kb_cut_rows, dim3(total(kRows1)), dim3(256), 0, st, T, W, nb, R, 1);
     if (total(kChunks1)) hipLaunchKernelGGL(kb_cut_chunks, dim3(total(kChunks1)), dim3(256), 0, st, T, W, nb, R, 1);
-    hipLaunchKernelGGL(kb_cut_reduce, dim3(total(kReduce)), dim3(256), 0, st, T, W, nb, R, 1);
+    hipLaunchKernelGGL(kb_cut_reduce, dim3(total(kReduce)), dim3(64), 0, st, T, W, nb, R, 1);
+    if (total(kStaged1)) hipLaunchKernelGGL(kb_cut_reduce_staged<kStaged1>, dim3(total(kStaged1)), dim3(256), 0, st, T, W, nb, 1);
     hipLaunchKernelGGL(kb_totals, dim3(total(kOne)), dim3(256), 0, st, T, W, nb, R, 1);
     QH_CHECK_LAUNCH();
     int32_t badb = 0;

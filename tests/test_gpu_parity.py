@@ -1836,3 +1836,33 @@ def test_band_mfma_equals_per_row_bit_exact_long_range(dtype):
         qh.bsb_solve(g, 64, 200, seed=9, x=x, y=y, plan=plan, readout=False)
         got.append((x, y))
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
+def _segments(lengths, seed=8):
+    """SNPs in stretches that no read crosses: one component each, of reads over neighbouring SNPs."""
+    rng = np.random.default_rng(seed)
+    n = int(sum(lengths))
+    last = np.cumsum(lengths) - 1
+    first = np.setdiff1d(np.arange(n), last).repeat(3)
+    w = synth.snp_small(seed, n_snp=n)
+    w.frag_ptr = 2 * np.arange(first.size + 1, dtype=np.int64)
+    w.snp = np.stack([first, first + 1], 1).reshape(-1).astype(np.int32)
+    w.allele = rng.integers(0, 2, w.snp.size).astype(w.allele.dtype)
+    w.phred = rng.integers(5, 40, w.snp.size).astype(np.uint8)
+    w.alpha = np.ones(first.size)
+    return w
+
+
+@pytest.mark.parametrize("R", [16, 64])
+@pytest.mark.parametrize("lengths", [[2048, 2049, 2, 3, 4300, 40] + [2] * 300 + [2080, 2081], [2] * 1500, [2048], [2049]])
+def test_readout_components_around_the_stage(lengths, R):
+    """Components of up to 64 chunks of 32 vertices (summed in one go), of 65 and more (staged), in any
+    order, alone and in a batch."""
+    w = _segments(lengths)
+    _readout_case(w, "snp_llr", R, 4, False)
+    gs = [gpu_graph(w, "snp_llr", "f32"), gpu_graph(_segments([2, 2100, 5]), "snp_llr", "f32")]
+    b = qh.bsb_solve_batched(gs, R, 10, seed=3)
+    for i, g in enumerate(gs):
+        r = qh.bsb_solve(g, R, 10, seed=3)
+        assert torch.equal(b["cuts"][i * R:(i + 1) * R], r["cuts"]) and torch.equal(b["best_cut"][i:i + 1], r["best_cut"])
+        assert torch.equal(b["selected_cut"][i:i + 1], r["selected_cut"])
