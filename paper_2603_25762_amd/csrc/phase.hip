@@ -107,7 +107,7 @@ void phase_noalloc(const qh_graph *g, const int8_t *spins, int8_t *h1, int32_t *
     // the counters keep the previous call's values: clear them (a kernel, so that a captured
     // stream records no memset node)
     hipLaunchKernelGGL(k_zero_counts, dim3(grid_for(2 * nc)), dim3(256), 0, st, 2 * nc, cnt);
-    hipLaunchKernelGGL(k_comp_sizes, dim3(std::min(grid_for(g->n), 256)), dim3(256), 0, st, g->n, g->comp.p, spins, cnt, cnt + nc);
+    hipLaunchKernelGGL(k_comp_sizes, dim3(count_groups(g, grid_for(g->n))), dim3(256), 0, st, g->n, g->comp.p, spins, cnt, cnt + nc);
     hipLaunchKernelGGL(k_phase_parity, dim3(grid_for(g->n)), dim3(256), 0, st, g->n, g->comp.p, spins, cnt, cnt + nc,
                        g->init_h1.p, h1, block);
     QH_CHECK_LAUNCH();
@@ -124,7 +124,7 @@ void phase(const qh_graph *g, const int8_t *spins, int8_t *h1, int32_t *block, h
     if (!g->n) return;
     DevBuf<int32_t> cnt(2 * std::max<int64_t>(g->n_comp, 1));
     cnt.zero(st);
-    hipLaunchKernelGGL(k_comp_sizes, dim3(std::min(grid_for(g->n), 256)), dim3(256), 0, st, g->n, g->comp.p, spins, cnt.p,
+    hipLaunchKernelGGL(k_comp_sizes, dim3(count_groups(g, grid_for(g->n))), dim3(256), 0, st, g->n, g->comp.p, spins, cnt.p,
                        cnt.p + std::max<int64_t>(g->n_comp, 1));
     hipLaunchKernelGGL(k_phase_parity, dim3(grid_for(g->n)), dim3(256), 0, st, g->n, g->comp.p, spins, cnt.p,
                        cnt.p + std::max<int64_t>(g->n_comp, 1), g->init_h1.p, h1, block);

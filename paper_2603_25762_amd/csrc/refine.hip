@@ -164,7 +164,7 @@ void refine(qh_graph *g, const qh_bsb_opts *o, int max_rounds, float deform, int
                 QH_HIP(hipStreamSynchronize(st));   // tk is reused by the next attempt
             }
             cnt.zero(st);
-            hipLaunchKernelGGL(k_ref_counts, dim3(std::min(grid_of(n), 256)), dim3(256), 0, st, n, g->comp.p, best.p, cnt.p,
+            hipLaunchKernelGGL(k_ref_counts, dim3(count_groups(g, grid_of(n))), dim3(256), 0, st, n, g->comp.p, best.p, cnt.p,
                                cnt.p + nc);
             QH_CHECK_LAUNCH();
             QH_HIP(hipMemcpyAsync(pm.data(), cnt.p, 2 * nc * sizeof(int32_t), hipMemcpyDeviceToHost, st));

@@ -1866,3 +1866,16 @@ def test_readout_components_around_the_stage(lengths, R):
         r = qh.bsb_solve(g, R, 10, seed=3)
         assert torch.equal(b["cuts"][i * R:(i + 1) * R], r["cuts"]) and torch.equal(b["best_cut"][i:i + 1], r["best_cut"])
         assert torch.equal(b["selected_cut"][i:i + 1], r["selected_cut"])
+
+
+@pytest.mark.parametrize("lengths", [[65536, 3, 500], [3, 65537, 2, 2, 4000], [2] * 40000])
+def test_phase_counts_of_large_and_small_components(lengths):
+    """The sides of a component are counted by a wave per 64 vertices, or over longer walks where a component
+    has more than 65,536."""
+    w = _segments(lengths)
+    g = gpu_graph(w, "snp_llr", "f32")
+    comp, nc = oracle.components(oracle_graph(w, "snp_llr"))
+    s = np.where(np.random.default_rng(2).random(comp.size) < 0.4, 1, -1).astype(np.int8)
+    h1, blk = qh.phase(g, torch.tensor(s, device="cuda"))
+    ho, bo = oracle.phase_parity(comp, nc, s, w.init_h1)
+    assert np.array_equal(cpu(h1), ho) and np.array_equal(cpu(blk), bo)
