@@ -539,6 +539,15 @@ constexpr int kReduceGroups = 1024;
 // fixed-point mode a term of magnitude 2^20 or more cannot be represented: *clamped is set and
 // the build fails.
 constexpr int kPairFrags = 32;       // most fragments of a workgroup
+
+// LDS accesses of the wave's lanes before it are seen by its lanes after it (a wave's LDS accesses complete
+// in order: the fences only keep the compiler from moving them).
+__device__ inline void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 constexpr int kPairTable = 2048;     // entries
 __global__ __launch_bounds__(256) void k_snp_pairs(int64_t F, const int64_t *__restrict__ kept_obs,
                                                    const int64_t *__restrict__ kept_ptr,
@@ -584,7 +593,10 @@ __global__ __launch_bounds__(256) void k_snp_pairs(int64_t F, const int64_t *__r
         __syncthreads();
         const int32_t u0 = s_lo_u, dist = s_dist;
         const int64_t span = (int64_t)s_hi_u - u0 + 1;
-        if (span < 2) continue;                   // (uniform: no pairs in the group)
+        if (span < 2) {                           // (uniform: no pairs in the group)
+            __syncthreads();                      // the next group's head overwrites what was just read
+            continue;
+        }
         const bool tab = span * dist <= kPairTable;
         if (tab)
             for (int e = threadIdx.x; e < (int)span * dist; e += 256) s_tab[e] = 0;
@@ -599,7 +611,7 @@ __global__ __launch_bounds__(256) void k_snp_pairs(int64_t F, const int64_t *__r
                 sm[a] = M[t];
                 sq[a] = qconf[phred[t]];
             }
-            __builtin_amdgcn_wave_barrier();      // (one wave's LDS accesses complete in order)
+            wave_lds_sync();
             const double af = alpha ? alpha[f] : 1.0;
             int64_t a = lane, d = 1;
             while (true) {
@@ -637,7 +649,7 @@ __global__ __launch_bounds__(256) void k_snp_pairs(int64_t F, const int64_t *__r
                 }
                 a += 64;
             }
-            __builtin_amdgcn_wave_barrier();
+            wave_lds_sync();                      // (the next fragment's values overwrite these)
         }
         __syncthreads();
         if (tab)
