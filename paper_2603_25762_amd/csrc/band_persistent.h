@@ -98,6 +98,9 @@ struct BandPersist {
 // Polls of a neighbour's flag before a wait gives up (tests lower it).
 constexpr int64_t kWaitPolls = (int64_t)1 << 27;
 extern int64_t wait_polls;
+// Most bytes of exchange buffers (tests lower it).
+extern int64_t exchange_limit;
+void alloc_exchange(DevBuf<float> &xch, int64_t floats);
 constexpr int64_t kBpErr = 32, kBpFlagsPad = 64;       // the error word's place past the flags
 // Fails with EHIP when the error word of launches that have ended is set, and clears it.
 void check_waits(int *err, hipStream_t st);

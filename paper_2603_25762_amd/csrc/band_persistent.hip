@@ -8,6 +8,12 @@
 namespace qh {
 
 int64_t wait_polls = kWaitPolls;
+int64_t exchange_limit = INT64_MAX;
+
+void alloc_exchange(DevBuf<float> &xch, int64_t floats) {
+    if (floats * 4 > exchange_limit) fail(QH_ENOMEM, "exchange buffers of %lld bytes", (long long)floats * 4);
+    xch.alloc((size_t)floats);
+}
 
 void check_waits(int *err, hipStream_t st) {
     if (!download(err, 1, st)[0]) return;
@@ -202,6 +208,7 @@ bool build_band_plan(const qh_graph *g, SolvePlan &p, BandPersist &bp, hipStream
                 }
                 bl.job_ptr.push_back((int32_t)bl.jobs.size());
             }
+        alloc_exchange(bp.xch, bl.xch_floats);         // (the largest first: it may find no room)
         BandTeam T{};
         if (tiles) {
             bp.off.alloc(nb);
@@ -236,7 +243,6 @@ bool build_band_plan(const qh_graph *g, SolvePlan &p, BandPersist &bp, hipStream
         bp.jobs.upload(bl.jobs.data(), bl.jobs.size(), st);
         bp.job_ptr.alloc(bl.job_ptr.size());
         bp.job_ptr.upload(bl.job_ptr.data(), bl.job_ptr.size(), st);
-        bp.xch.alloc((size_t)bl.xch_floats);
         bp.flags.alloc((size_t)bl.n_flags + kBpFlagsPad);
         bp.flags.zero(st);
         bp.failed.take();

@@ -153,7 +153,16 @@ void bsb_solve_batched(const qh_graph *const *gs, int nb, const qh_bsb_opts *o, 
     // last in the block table.
     BatchTeams bt;
     bt.in.assign(nb, 0);
-    if (o->plan == 0 && o->steps > 0 && !stream_capturing(st)) plan_batch_teams(gs, plans, desc, o, bt, st);
+    if (o->plan == 0 && o->steps > 0 && !stream_capturing(st)) {
+        try {
+            plan_batch_teams(gs, plans, desc, o, bt, st);
+        } catch (const Failure &e) {
+            if (e.st != QH_ENOMEM) throw;
+            QH_HIP(hipStreamSynchronize(st));   // (no room for the teams' buffers: the per-step launches need none)
+            bt = BatchTeams{};
+            bt.in.assign(nb, 0);
+        }
+    }
     std::vector<int> rest;
     std::vector<BlockDesc> table;
     for (int b = 0; b < nb; ++b)

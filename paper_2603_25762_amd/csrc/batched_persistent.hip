@@ -322,13 +322,13 @@ void plan_batch_teams(const qh_graph *const *gs, const std::vector<SolvePlan *> 
             ptr.push_back((int32_t)all.size());
         }
     }
+    alloc_exchange(bt.xch, xch);                       // (the largest first: it may find no room)
     bt.teams.alloc(teams.size());
     bt.teams.upload(teams.data(), teams.size(), st);
     bt.jobs.alloc(all.size());
     bt.jobs.upload(all.data(), all.size(), st);
     bt.ptr.alloc(ptr.size());
     bt.ptr.upload(ptr.data(), ptr.size(), st);
-    bt.xch.alloc((size_t)xch);
     bt.flags.alloc((size_t)flags + kBpFlagsPad);
     bt.n_flags = flags;
     QH_HIP(hipStreamSynchronize(st));                  // (the uploads read this function's vectors)

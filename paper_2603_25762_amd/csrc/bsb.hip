@@ -1651,7 +1651,13 @@ void bsb_solve(const qh_graph *g, const qh_bsb_opts *o, qh_result *res, hipStrea
     if (o->plan == 0 && ke > kb && n > 0 && !capturing) {
         if (!p.bp_tried) {
             p.bp = std::make_shared<BandPersist>();
-            build_band_plan(g, p, *p.bp, st);
+            try {
+                build_band_plan(g, p, *p.bp, st);
+            } catch (const Failure &e) {
+                if (e.st != QH_ENOMEM) throw;
+                QH_HIP(hipStreamSynchronize(st));   // (no room for its buffers: the per-step launches need none)
+                p.bp = std::make_shared<BandPersist>();
+            }
             p.bp_tried = true;
         }
         // (a column tile that a row tile skips multiplies by 0 there: the caller's own state or

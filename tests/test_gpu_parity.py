@@ -1879,3 +1879,33 @@ def test_phase_counts_of_large_and_small_components(lengths):
     h1, blk = qh.phase(g, torch.tensor(s, device="cuda"))
     ho, bo = oracle.phase_parity(comp, nc, s, w.init_h1)
     assert np.array_equal(cpu(h1), ho) and np.array_equal(cpu(blk), bo)
+
+
+@pytest.fixture
+def no_exchange():
+    """No device memory for the exchange buffers of the one-launch plans."""
+    v = ctypes.c_int64.in_dll(qh.load(), "_ZN2qh14exchange_limitE")
+    old, v.value = v.value, 0
+    yield v
+    v.value = old
+
+
+@pytest.mark.parametrize("kind,dtype,n,reads,R", [
+    ("snp_llr", "f16", 2001, 0, 128), ("read_signed", "f32", 2300, 1501, 64), ("read_signed", "bf16", 2300, 1501, 64)])
+def test_no_memory_for_the_exchange(no_exchange, kind, dtype, n, reads, R):
+    """A graph whose one-launch plan finds no memory for its buffers solves per step, as it did before that
+    plan."""
+    g, ref = _one_launch_case(kind, dtype, n, reads, R)
+    a = qh.bsb_solve(g, R, 60, seed=9, plan=ref)
+    b = qh.bsb_solve(g, R, 60, seed=9)
+    if dtype != "bf16":
+        assert g.plan_info(R)["plan_used"] == 1
+    assert torch.equal(a["best_spins"], b["best_spins"]) and torch.equal(a["cuts"], b["cuts"])
+
+
+def test_no_memory_for_the_teams_of_a_batch(team_batch, no_exchange):
+    gs = team_batch[-8:]
+    a = qh.bsb_solve_batched(gs, 32, 40, seed=5, plan=1, return_state=True)
+    b = qh.bsb_solve_batched(gs, 32, 40, seed=5, return_state=True)
+    for k in ("x", "y", "cuts", "best_spins", "best_cut"):
+        assert torch.equal(a[k], b[k]), k
