@@ -1687,13 +1687,14 @@ void bsb_solve(const qh_graph *g, const qh_bsb_opts *o, qh_result *res, hipStrea
         // (a graph on the band plan is timed briefly, for the report only)
         const bool again = p.tuned_brief && !band && !capturing &&
                            (o->plan == 0 || (o->plan == 1 ? o->replica_tile == 0 : o->persistent_sync == 0));
-        if (dense16 && (want_persistent || again) && !band && !p.pp_tried) {
+        if (dense16 && (want_persistent || again) && !band && !capturing && !p.pp_tried) {
             p.pp = std::make_shared<PersistPlan>();
             build_persistent_plan(g, R, *p.pp, st);
             p.pp_tried = true;
         }
         if ((o->plan == 0 && !p.tuned_plan) || again) autotune_dense(g, p, o, pump, c0, a0, band, st);
-        if (dense16 && want_persistent && !band && p.pp->ok) persistent = o->plan == 2 || p.tuned_plan == 2;
+        if (dense16 && want_persistent && !band && p.pp && p.pp->ok)
+            persistent = o->plan == 2 || (p.tuned_plan == 2 && !capturing);   // (its launch cannot be recorded)
     }
     // replica tile of the per-step dense kernel: the caller's, else the tuned one, else by the fill
     p.run_rt = o->replica_tile ? o->replica_tile : p.tuned_rt ? p.tuned_rt : default_tile(g, R);

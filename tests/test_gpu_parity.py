@@ -1909,3 +1909,27 @@ def test_no_memory_for_the_teams_of_a_batch(team_batch, no_exchange):
     b = qh.bsb_solve_batched(gs, 32, 40, seed=5, return_state=True)
     for k in ("x", "y", "cuts", "best_spins", "best_cut"):
         assert torch.equal(a[k], b[k]), k
+
+
+@pytest.mark.parametrize("kind,dtype,n,reads", [("snp_llr", "f16", 2001, 0), ("read_signed", "f32", 1500, 1000),
+                                                ("read_signed", "f16", 1500, 1000), ("read_signed", "fp8", 12000, 8000)])
+def test_plan_0_under_capture_after_a_warm_solve(kind, dtype, n, reads):
+    """A caller captures a plan-0 range of a graph that it has solved before: the per-step launches are
+    recorded, and every replay gives the eager solve's state, with eager work between the replays."""
+    g, _ = _one_launch_case(kind, dtype, n, reads, 64)
+    nv = g.info()["n"]
+    xe, ye, x, y = (torch.zeros((nv, 64), dtype=torch.float32, device="cuda") for _ in range(4))
+    kw = dict(seed=9, step_end=30, readout=False)
+    qh.bsb_solve(g, 64, 40, x=xe, y=ye, **kw)
+    torch.cuda.synchronize()
+    s = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s, capture_error_mode="thread_local"):
+        qh.bsb_solve(g, 64, 40, x=x, y=y, **kw)
+    for _ in range(3):
+        x.zero_(), y.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(x, xe) and torch.equal(y, ye)
+        qh.bsb_solve(g, 64, 40, seed=4, readout=False)
+        torch.cuda.synchronize()
