@@ -305,8 +305,9 @@ qh_status qh_bsb_solve(const qh_graph *g, const qh_bsb_opts *opts, qh_result *re
 
 /* Step-loop plan chosen for (graph, replicas) by earlier solves.  plan_used: 0 = no solve
  * yet, 1 = one fused kernel per step, 2 = persistent (all steps in one cooperative
- * launch; dense graphs: state in registers, J in LDS; SNP graphs: x in LDS, y and J in
- * registers).  With opts.plan = 0 the first solve of a
+ * launch; plan 2: state in registers, J in LDS; plan 0's one-launch kernels: x in LDS, y and J
+ * in registers).  After a batched solve: 2 for a block that ran as a team of workgroups, else
+ * the batch's plan_used.  With opts.plan = 0 the first solve of a
  * (graph, replicas) pair times the candidates on scratch state (a few steps each) and keeps
  * the fastest: the per-step kernel with 64 (two or four tiles in flight), 32 and 16
  * replicas per workgroup (dense graphs, R >= 64) and the persistent plan where it fits
@@ -319,6 +320,7 @@ qh_status qh_bsb_solve(const qh_graph *g, const qh_bsb_opts *opts, qh_result *re
 typedef struct {
     int32_t plan_used;
     int32_t persistent_ok;      /* 1 when the persistent plan fits this graph */
+    /* persistent plan (the one that the last solve ran, else the one that fits): */
     int32_t replicas_per_group; /* persistent plan: replicas per independent group */
     int32_t groups;             /* persistent plan: replica groups */
     int32_t workgroups_per_group;
@@ -328,7 +330,8 @@ typedef struct {
     int32_t tiles_in_flight;    /* per-step dense plan: stored tiles whose loads are issued together */
     int32_t skyline_kernel;     /* SNP graphs: step kernel of the last solve: 3 rows, 4 band FMA, 5 band MFMA */
     float skyline_us[2];        /* SNP autotuner: [band FMA, band MFMA] microseconds per step (0 = not timed) */
-    int32_t persistent_sync;    /* persistent plan of the last solve: 1 fences, 2 coherent accesses */
+    int32_t persistent_sync;    /* persistent plan of the last solve: 1 fences, 2 coherent accesses
+                                   (one-launch kernels: 2) */
     float us_persistent_coherent; /* autotuner: persistent plan with coherent accesses (0 = not timed) */
 } qh_plan_info;
 

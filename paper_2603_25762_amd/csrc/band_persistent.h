@@ -64,6 +64,7 @@ struct BandLaunch {
     int rt = 0;                 // replicas per group (16 or 32)
     int um = 0;                 // band blocks per wave (kernel variant: 1, 2, 4 or 8)
     int grid = 0;
+    int wpg = 0;                // workgroups per replica group (single-graph launches)
     int dtype = 0;
     bool strips = false;        // the strip kernel (16/8-bit dense graphs), else the band kernel
     int64_t lds_bytes = 0, xch_floats = 0, n_flags = 0;

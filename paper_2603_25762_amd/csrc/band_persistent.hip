@@ -187,6 +187,7 @@ bool build_band_plan(const qh_graph *g, SolvePlan &p, BandPersist &bp, hipStream
         bl.rt = c.rt;
         bl.um = c.um;
         bl.grid = c.wpg * c.slots;
+        bl.wpg = c.wpg;
         bl.dtype = dtype;
         bl.strips = strips;
         bl.lds_bytes = lds;

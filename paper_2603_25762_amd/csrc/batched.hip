@@ -368,6 +368,10 @@ void bsb_solve_batched(const qh_graph *const *gs, int nb, const qh_bsb_opts *o, 
         throw;
     }
     res->plan_used = plan;
+    for (int b = 0; b < nb; ++b) {
+        plans[b]->last_plan = bt.in[b] ? 2 : plan;
+        if (!bt.in[b]) plans[b]->one_rt = 0;
+    }
     // the per-step plan ping-pongs x like the single-graph solve; the whole-block plan and the
     // teams leave the final x in the first half
     const int final_half = plan == 1 ? (o->steps & 1) : 0;

@@ -286,6 +286,9 @@ void plan_batch_teams(const qh_graph *const *gs, const std::vector<SolvePlan *> 
                 T.n = (int32_t)g->n;
                 teams.push_back(T);
                 bt.in[e.b] = 1;
+                plans[e.b]->one_rt = best.rt;
+                plans[e.b]->one_wpg = t.wpg;
+                plans[e.b]->one_lds = band_lds_bytes(s.lds_rows, best.rt, str);
             }
             const int64_t rows = (int64_t)e.nblk * kBandRows;
             for (int w = 0; w < t.wpg; ++w) {

@@ -1718,8 +1718,14 @@ void bsb_solve(const qh_graph *g, const qh_bsb_opts *o, qh_result *res, hipStrea
     };
     load_state();
     auto one_launch = [&](int k0, int k1) { return band && k1 - k0 >= p.bp->min_steps; };
-    if (ke > kb && n > 0)
-        p.last_plan = persistent || one_launch(kb, o->eval_every > 0 ? (int)std::min<int64_t>(ke, (int64_t)kb + o->eval_every) : ke) ? 2 : 1;
+    if (ke > kb && n > 0) {
+        const int first = o->eval_every > 0 ? (int)std::min<int64_t>(ke, (int64_t)kb + o->eval_every) : ke;
+        const bool one = one_launch(kb, first);
+        p.last_plan = persistent || one ? 2 : 1;
+        p.one_rt = one ? p.bp->launch.rt : 0;
+        p.one_wpg = one ? p.bp->launch.wpg : 0;
+        p.one_lds = one ? p.bp->launch.lds_bytes : 0;
+    }
     const int coherent = o->persistent_sync == 2 || (o->persistent_sync == 0 && p.tuned_coh);
     if (persistent) p.last_coh = coherent;
     // (a wait that gave up leaves NaN: report the wait, not the number)

@@ -177,11 +177,17 @@ void plan_info(const qh_graph *g, int R, qh_plan_info *out) {
             i.workgroups_per_group = p.pp->wpg;
             i.lds_bytes = (int32_t)p.pp->lds_bytes;
         }
+        if (p.one_rt) {                // what the last solve ran
+            i.replicas_per_group = p.one_rt;
+            i.groups = R / p.one_rt;
+            i.workgroups_per_group = p.one_wpg;
+            i.lds_bytes = (int32_t)p.one_lds;
+        }
         i.us_per_step[0] = p.tuned_us[0];
         i.us_per_step[1] = p.tuned_us[1];
         i.replica_tile = g->storage == QH_STORE_DENSE ? std::min(p.run_rt, R) : 0;
         i.tiles_in_flight = g->storage == QH_STORE_DENSE ? (R >= 64 && p.run_rt == 64 ? p.run_depth : 4) : 0;
-        i.persistent_sync = p.last_plan == 2 ? 1 + p.last_coh : 0;
+        i.persistent_sync = p.one_rt ? 2 : p.last_plan == 2 ? 1 + p.last_coh : 0;
         i.us_persistent_coherent = p.tuned_us_coh;
         if (g->storage != QH_STORE_DENSE) {
             int sk = p.sky_kernel;

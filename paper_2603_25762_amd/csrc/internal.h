@@ -132,6 +132,8 @@ struct SolvePlan {
     bool tuned_brief = false;          // timed over two steps beside a one-launch solve, without the
                                        // persistent plan: other calls that act on it time again
     int last_plan = 0;                 // plan the last solve ran
+    int one_rt = 0, one_wpg = 0;       // its replicas per group and workgroups per group, where that was a
+    int64_t one_lds = 0;               // one-launch plan (a team of a batch, too), and LDS; else 0
     int sky_kernel = 0;                // SNP graphs: kSkyBandFma, kSkyBandMfma or kSkyRows
     bool sky_tuned = false;            // the band kernels have been timed on this graph
     bool sky_brief = false;            // (as tuned_brief)

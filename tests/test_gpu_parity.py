@@ -1933,3 +1933,106 @@ def test_plan_0_under_capture_after_a_warm_solve(kind, dtype, n, reads):
         assert torch.equal(x, xe) and torch.equal(y, ye)
         qh.bsb_solve(g, 64, 40, seed=4, readout=False)
         torch.cuda.synchronize()
+
+
+@pytest.fixture(scope="module")
+def mixed_batch():
+    """Blocks that run as teams, and one of 5,000 reads (FP8) whose row tiles span more than 64 column tiles:
+    it runs per step, beside the teams."""
+    ws = [synth.read_small(30, 400, 1300, (20, 120)), synth.snp_small(40, 2500), synth.snp_small(41, 300),
+          synth.read_small(31, 200, 90, (20, 60)), synth.read_small(9, 60, 5000, (20, 50))]
+    kinds = ["read_signed", "snp_llr", "snp_llr", "read_signed", "read_signed"]
+    gs = [gpu_graph(w, k, d) for w, k, d in zip(ws, kinds, ["f16", "bf16", "bf16", "f16", "fp8"])]
+    yield gs
+    for g in gs:
+        g.free()
+
+
+@pytest.mark.parametrize("R", [16, 32, 64])
+@pytest.mark.parametrize("graph", [False, True])
+def test_batch_rest_beside_the_teams(mixed_batch, R, graph):
+    """Which blocks of a batch run as teams, some of several workgroups, and that the others, on the side
+    stream beside them, plain or as a captured replay, give the per-step plan's bits; several
+    replays with other work between them, another seed, and the same blocks without the large one."""
+    gs = mixed_batch
+    for seed in (9, 9, 10, 9):
+        a = qh.bsb_solve_batched(gs, R, 100, seed=seed, plan=1, return_state=True)
+        assert [g.plan_info(R)["plan_used"] for g in gs] == [1] * len(gs)
+        torch.cuda.synchronize()
+        b = qh.bsb_solve_batched(gs, R, 100, seed=seed, use_graph=graph, return_state=True)
+        info = [g.plan_info(R) for g in gs]
+        assert [i["plan_used"] for i in info[:4]] == [2] * 4
+        assert info[4]["plan_used"] == b["plan_used"] and info[4]["replicas_per_group"] == 0
+        assert max(i["workgroups_per_group"] for i in info[:2]) > 1 and info[3]["workgroups_per_group"] == 1
+        assert all(i["replicas_per_group"] * i["groups"] == R and i["lds_bytes"] > 0 for i in info[:4])
+        for k in ("x", "y", "cuts", "selected_cut", "best_spins", "best_cut"):
+            assert torch.equal(a[k], b[k]), (seed, k)
+        qh.bsb_solve(gs[0], R, 50, seed=1)
+    a = qh.bsb_solve_batched(gs[:4], R, 100, seed=9, plan=1)
+    b = qh.bsb_solve_batched(gs[:4], R, 100, seed=9, use_graph=graph)
+    assert torch.equal(a["best_spins"], b["best_spins"]) and torch.equal(a["best_cut"], b["best_cut"])
+
+
+def test_which_blocks_run_as_teams(team_batch):
+    """All of team_batch's blocks run as teams, some of them of several workgroups, but the FP32 read block
+    (per step beside them) and, with a field, the one whose row tiles skip column tiles."""
+    gs = team_batch
+    n = sum(g.info()["n"] for g in gs)
+    for field, rest in ((None, [600]), (torch.zeros(n, dtype=torch.float32, device="cuda"), [600, 607])):
+        qh.bsb_solve_batched(gs, 32, 31, seed=5, field=field)
+        info = [g.plan_info(32) for g in gs]
+        assert [b for b, i in enumerate(info) if i["replicas_per_group"] == 0] == rest
+        assert all(i["plan_used"] == 2 for b, i in enumerate(info) if b not in rest)
+        assert sum(i["workgroups_per_group"] > 1 for i in info) >= 7 - len(rest)
+
+
+@pytest.mark.parametrize("plan", [1, 2])
+def test_batched_plan_1_graph_replay_bit_exact(mixed_batch, plan):
+    """use_graph with plan 1: every block's steps captured once and replayed, bit for bit."""
+    for seed in (9, 9, 10, 9):
+        a = qh.bsb_solve_batched(mixed_batch, 32, 60, seed=seed, plan=plan, return_state=True)
+        b = qh.bsb_solve_batched(mixed_batch, 32, 60, seed=seed, plan=1, use_graph=True, return_state=True)
+        assert b["plan_used"] == 1
+        for k in ("x", "y", "cuts", "best_spins", "best_cut"):
+            assert torch.equal(a[k], b[k]), (seed, k)
+        qh.bsb_solve(mixed_batch[1], 32, 50, seed=1)
+
+
+@pytest.mark.parametrize("kind,dtype", RESUME_CASES)
+def test_captured_step_loop_bit_exact(kind, dtype):
+    """use_graph with plan 1: the captured step loop replayed, with the eager steps' bits; a plan-0 solve
+    between the replays (another step kernel on SNP graphs) leaves it valid."""
+    w = synth.read_small(16, n_snp=300, n_reads=140) if kind != "snp_llr" else synth.snp_small(16, n_snp=900)
+    g = gpu_graph(w, kind, dtype)
+    n, R = g.info()["n"], 64
+    out = []
+    for rep in range(5):
+        x, y = (torch.empty((n, R), dtype=torch.float32, device="cuda") for _ in range(2))
+        r = qh.bsb_solve(g, R, 200, seed=5, x=x, y=y, plan=1, use_graph=rep > 0)
+        assert g.plan_info(R)["plan_used"] == 1
+        out.append((x, y, r["best_spins"], r["best_cut"], r["cuts"]))
+        qh.bsb_solve(g, R, 200, seed=6, plan=0 if rep % 2 else 1)
+    for o in out[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(out[0], o))
+
+
+def test_plan_info_of_the_last_solve():
+    """The geometry of the plan that the last solve ran, kept over calls that only read out."""
+    g = gpu_graph(synth.read_mhc(seed=78, n_snp=1500, n_reads=1000, region=500_000), "read_signed", "f16")
+    n = g.info()["n"]
+    x, y = (torch.empty((n, 64), dtype=torch.float32, device="cuda") for _ in range(2))
+
+    def info(plan):
+        qh.bsb_solve(g, 64, 60, seed=9, x=x, y=y, plan=plan)
+        a = g.plan_info(64)
+        qh.bsb_solve(g, 64, 60, init=False, x=x, y=y, step_begin=60, step_end=60, plan=plan if plan != 2 else 0)
+        assert g.plan_info(64)["plan_used"] == a["plan_used"]
+        return a
+
+    p2 = info(2)
+    assert p2["plan_used"] == 2 and p2["persistent_sync"] == 1 and p2["workgroups_per_group"] > 1
+    one = info(0)
+    assert one["plan_used"] == 2 and one["persistent_sync"] == 2
+    assert one["replicas_per_group"] * one["groups"] == 64
+    assert (one["workgroups_per_group"], one["lds_bytes"]) != (p2["workgroups_per_group"], p2["lds_bytes"])
+    assert info(1)["plan_used"] == 1
