@@ -131,7 +131,10 @@ double band_step_us(double quads, double past, int64_t blocks, int wpg, int rt, 
 // estimated time of a step times the passes that the replica groups take.
 // The per-step kernels take their state's traffic at 4.6 TB/s and a launch, or the latency of
 // walking the band (2,001 SNPs 8.8, 7,768 SNPs 17.2, 250,000 56.6 measured); the plan has to
-// beat that by a tenth.
+// beat that by a tenth.  Both sides are estimates, fitted to the shapes above and not timed on the
+// graph.  Over 20 more shapes (SNP graphs of 60 to 50,000 SNPs in bands of 14 to 440 columns, read graphs of
+// 60 to 12,000 reads, 16 to 2,048 replicas) plan 0 took from the same time as the per-step plans
+// (8,000 F16 reads, R = 1,024) to a fifth of it (1,000 SNPs in bands of 440, R = 64).
 bool build_band_plan(const qh_graph *g, SolvePlan &p, BandPersist &bp, hipStream_t st) {
     bp.ok = false;
     const int R = p.R;
@@ -175,8 +178,11 @@ bool build_band_plan(const qh_graph *g, SolvePlan &p, BandPersist &bp, hipStream
         }
     }
     std::sort(cands.begin(), cands.end(), [](const Cand &a, const Cand &b) { return a.us < b.us; });
-    const double step_us = strips ? std::max(4.5, 3.0 + quads / 16.0 * 0.2 + (double)g->n * R * 16.0 / 4.6e6) : tiles ? std::max(4.0, 3.0 + 0.1 * quads + (double)g->n * R * 16.0 / 4.6e6)
-                                 : std::max({4.0, 1.5 + 0.43 * quads, 3.0 + (double)g->n * R * 16.0 / 4.6e6});
+    const double state_us = (double)g->n * R * 16.0 / 4.6e6;
+    double step_us;
+    if (strips) step_us = std::max(4.5, 3.0 + quads / 16.0 * 0.2 + state_us);
+    else if (tiles) step_us = std::max(4.0, 3.0 + quads * 0.1 + state_us);
+    else step_us = std::max({4.0, 1.5 + quads * 0.43, 3.0 + state_us});
     for (const Cand &c : cands) {
         if (c.us > 0.9 * step_us) break;
         BandSplit s = split_band(lo.data(), wd.data(), nb, c.wpg);
@@ -237,7 +243,7 @@ bool build_band_plan(const qh_graph *g, SolvePlan &p, BandPersist &bp, hipStream
         // launch, at 1, 4 and 8 steps: 2,001 SNPs, R = 64 34 / 58, 59 / 65, 106 / 78; 250,000 SNPs 197 / 244,
         // 365 / 312, 607 / 412; FP32, 8,000 reads, R = 64 39 / 62, 66 / 76, 110 / 95.  16- and 8-bit dense graphs
         // took a cooperative launch before: from two steps on.
-        bp.min_steps = strips ? kBpMinSteps : tiles ? 8 : step_us >= 20.0 ? 3 : 6;
+        bp.min_steps = strips ? kBpMinSteps : tiles ? 8 : step_us >= 20.0 ? 3 : step_us >= 7.0 ? 4 : 6;
         bp.team.alloc(1);
         bp.team.upload(&T, 1, st);
         bp.jobs.alloc(bl.jobs.size());

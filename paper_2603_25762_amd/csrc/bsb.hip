@@ -1461,9 +1461,10 @@ static int default_tile(const qh_graph *g, int R) {
 // Autotuner for plan 0 on dense 16/8-bit graphs: time a short run of each candidate on
 // scratch state -- one fused kernel per step, and the persistent launch -- and keep the
 // faster.  Both compute bit-identical results, so the choice only affects speed.  A warm step
-// or two, then 16 steps (`brief`: two, for the report of a solve that does not act on it): 64 steps twice for each of four to six candidates took as long as a
-// 500-step solve, and the candidates differ by 10 % or more from the first steps on (1,501
-// reads, F32, R = 64: 14.3, 14.2, 8.6 and 8.2 us).
+// or two, then 16 steps (`brief`: two, for the report of a solve that does not act on it): 64 steps
+// twice for each of four to six candidates took as long as a 500-step solve, and candidates that
+// matter differ by far more than 16 steps vary (1,501 reads, F32, R = 64: 14.3, 14.2, 8.6 and 8.2 us;
+// between the last two the choice may fall either way).
 static void autotune_dense(const qh_graph *g, SolvePlan &p, const qh_bsb_opts *o, const float *pump, double c0,
                            double a0, bool brief, hipStream_t st) {
     const int64_t n = g->n;
