@@ -95,10 +95,13 @@ struct BandPersist {
     DevBuf<float> xch;
     DevBuf<int> flags;          // n_flags counters, then the error word
     HostWord failed;            // readout = 0: set by the stream when a wait gave up
+    bool fresh = true;          // the error word has not been cleared yet
 };
-// Polls of a neighbour's flag before a wait gives up (tests lower it).
+// Polls of a neighbour's flag before a wait gives up.
 constexpr int64_t kWaitPolls = (int64_t)1 << 27;
-extern int64_t wait_polls;
+// Set by tests: every launch finds the error word set, as by a wait that gave up.
+extern int32_t force_wait_error;
+void forced_wait_error(int *err, hipStream_t st);
 // Most bytes of exchange buffers (tests lower it).
 extern int64_t exchange_limit;
 void alloc_exchange(DevBuf<float> &xch, int64_t floats);

@@ -7,7 +7,12 @@
 
 namespace qh {
 
-int64_t wait_polls = kWaitPolls;
+int32_t force_wait_error = 0;
+
+void forced_wait_error(int *err, hipStream_t st) {
+    if (force_wait_error) QH_HIP(hipMemsetAsync(err, 1, sizeof(int), st));
+}
+
 int64_t exchange_limit = INT64_MAX;
 
 void alloc_exchange(DevBuf<float> &xch, int64_t floats) {
@@ -251,7 +256,6 @@ bool build_band_plan(const qh_graph *g, SolvePlan &p, BandPersist &bp, hipStream
         bp.job_ptr.alloc(bl.job_ptr.size());
         bp.job_ptr.upload(bl.job_ptr.data(), bl.job_ptr.size(), st);
         bp.flags.alloc((size_t)bl.n_flags + kBpFlagsPad);
-        bp.flags.zero(st);
         bp.failed.take();
         QH_HIP(hipStreamSynchronize(st));
         bp.ok = true;

@@ -21,10 +21,11 @@
 // Flags count steps.  A workgroup publishes step t into half t % 2 of the exchange buffer only
 // after its neighbours' flags reached t, that is after they read half t % 2 for the last time;
 // the neighbour lists are symmetric.  A launch runs at least two steps: a workgroup reads its
-// neighbours' rows of the initial state from where they write their final one, and only the wait of a
-// second step shows that the neighbours are past that read.  Waits are bounded: past max_polls a workgroup raises the
-// error word, every wait then returns soon, and the final x is NaN; the host fails the call, or,
-// where a call returns before its launch has ended, the next one on the graph.
+// neighbours' rows of the initial state from where they write their final one, and only the wait
+// of a second step shows that the neighbours are past that read.  Waits are bounded: past
+// max_polls a workgroup raises the error word, every wait then returns at its next 1,024th poll,
+// and the final x is NaN; the host fails the call, or, where a call returns before its launch has
+// ended, the next one on the graph.
 #pragma once
 
 #include "band_persistent.h"
@@ -106,7 +107,7 @@ __device__ inline void bp_wait(const BandPersistArgs &a, const int *flags, int n
         while (true) {
             const bool late = f < nf && f / kBpWaves + nbr0 != w && bp_flag(flags + f0 + f) < t;
             if (!__any(late)) break;
-            if (++polls > a.max_polls || ((polls & 1023) == 0 && bp_flag(a.err) != 0)) {
+            if ((++polls & 1023) == 0 && (polls > a.max_polls || bp_flag(a.err) != 0)) {
                 __hip_atomic_fetch_or(a.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 break;
             }

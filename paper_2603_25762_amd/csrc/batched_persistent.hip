@@ -356,7 +356,8 @@ void run_batch_teams(BatchTeams &bt, const qh_bsb_opts *o, double a0, const floa
         a.err = bt.flags.p + bt.n_flags + kBpErr;
         // a team may wait for a workgroup that is still busy with its earlier teams; a poll takes 0.1 us
         // or more
-        a.max_polls = wait_polls < kWaitPolls ? wait_polls : std::max(kWaitPolls, (int64_t)(L.us * o->steps * 64.0));
+        a.max_polls = std::max(kWaitPolls, (int64_t)(L.us * o->steps * 64.0));
+        forced_wait_error(a.err, st);
         launch_band(L.launch, a, o->variant == 1, st);
     }
 }

@@ -1412,8 +1412,10 @@ static void run_band(SolvePlan &p, const float *pump, double c0, double dt, doub
     BandPersist &bp = *p.bp;
     if (ke - kb < kBpMinSteps) fail(QH_EUNSUPPORTED, "a one-launch range needs %d steps", kBpMinSteps);
     // (the error word stays set until a call reports it)
-    hipLaunchKernelGGL(k_zero_i32, dim3(grid_for(bp.launch.n_flags)), dim3(256), 0, st, bp.launch.n_flags, bp.flags.p);
+    const int64_t nz = bp.launch.n_flags + (bp.fresh ? kBpErr + 1 : 0);
+    hipLaunchKernelGGL(k_zero_i32, dim3(grid_for(nz)), dim3(256), 0, st, nz, bp.flags.p);
     QH_CHECK_LAUNCH();
+    bp.fresh = false;
     BandPersistArgs a{};
     a.R = p.R;
     a.kb = kb;
@@ -1427,7 +1429,8 @@ static void run_band(SolvePlan &p, const float *pump, double c0, double dt, doub
     a.xch = bp.xch.p;
     a.flags = bp.flags.p;
     a.err = bp.flags.p + bp.launch.n_flags + kBpErr;
-    a.max_polls = wait_polls;
+    a.max_polls = kWaitPolls;
+    forced_wait_error(a.err, st);
     a.single = 1;
     a.c0 = (float)c0;
     a.field = field;

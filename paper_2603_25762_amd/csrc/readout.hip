@@ -320,18 +320,27 @@ __global__ void k_cut_chunks(int64_t n_chunks, int R, const int32_t *cb, const i
 __global__ void k_cut_reduce(int64_t n_comp, int R, const int32_t *ccp, const double *part, double *cut_rc) {
     cut_reduce_body(QH_G, n_comp, R, ccp, part, cut_rc);
 }
-__global__ __launch_bounds__(256) void k_cut_reduce_staged(int64_t n_comp, int64_t n_chunks, int R, const int32_t *ccp,
-                                                           const double *part, double *cut_rc) {
-    cut_reduce_staged_body(QH_G, n_comp, n_chunks, R, ccp, part, cut_rc);
+// The first `small` workgroups take the components that are not staged.
+__global__ __launch_bounds__(256) void k_cut_reduce_staged(int small, int64_t n_comp, int64_t n_chunks, int R,
+                                                           const int32_t *ccp, const double *part, double *cut_rc) {
+    const int64_t b = blockIdx.x;
+    if (b < small) cut_reduce_body(b, small, n_comp, R, ccp, part, cut_rc);
+    else cut_reduce_staged_body(b - small, gridDim.x - small, n_comp, n_chunks, R, ccp, part, cut_rc);
 }
+// One launch where the LDS of the staged items leaves every small component a workgroup at once (1,024:
+// four per CU); else the small ones first (a launch costs a readout of 3,000 reads 3 us).
 static void launch_cut_reduce(const ReadoutView &g, int R, int threads, const double *part, double *cut_rc,
                               hipStream_t st) {
-    hipLaunchKernelGGL(k_cut_reduce, dim3((unsigned)std::min<int64_t>(g.n_comp, 1 << 20)), dim3(threads), 0, st, g.n_comp,
-                       R, g.comp_chunk_ptr, part, cut_rc);
     const int64_t items = staged_items(g.n_comp, g.n_chunks, R);
-    if (items)
-        hipLaunchKernelGGL(k_cut_reduce_staged, dim3((unsigned)std::min<int64_t>(items, 1 << 20)), dim3(256), 0, st,
-                           g.n_comp, g.n_chunks, R, g.comp_chunk_ptr, part, cut_rc);
+    const bool together = items && g.n_comp <= 1024;
+    if (!together)
+        hipLaunchKernelGGL(k_cut_reduce, dim3((unsigned)std::min<int64_t>(g.n_comp, 1 << 20)), dim3(threads), 0, st,
+                           g.n_comp, R, g.comp_chunk_ptr, part, cut_rc);
+    if (items) {
+        const int small = together && g.n_comp > 1 ? (int)g.n_comp : 0;   // (a single component is the large one)
+        hipLaunchKernelGGL(k_cut_reduce_staged, dim3((unsigned)std::min<int64_t>(items + small, 1 << 20)), dim3(256), 0,
+                           st, small, g.n_comp, g.n_chunks, R, g.comp_chunk_ptr, part, cut_rc);
+    }
 }
 __global__ void k_select(int64_t n_comp, int R, const double *cut_rc, int32_t *best_r) {
     select_body(QH_G, n_comp, R, cut_rc, best_r);

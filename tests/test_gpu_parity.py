@@ -1703,17 +1703,17 @@ def test_batch_of_few_steps(kind, dtype, n, steps):
 
 
 @pytest.fixture
-def no_polls():
-    """Waits of the one-launch plans give up at the first poll that finds a neighbour late."""
-    v = ctypes.c_int64.in_dll(qh.load(), "_ZN2qh10wait_pollsE")
-    old, v.value = v.value, 0
+def wait_error():
+    """Every launch of the one-launch plans finds its error word set, as by a wait that gave up."""
+    v = ctypes.c_int32.in_dll(qh.load(), "_ZN2qh16force_wait_errorE")
+    v.value = 1
     yield v
-    v.value = old
+    v.value = 0
 
 
 @pytest.mark.parametrize("kind,dtype,n,reads,R", [
     ("snp_llr", "f16", 2001, 0, 128), ("read_signed", "f32", 2300, 1501, 64), ("read_signed", "bf16", 2300, 1501, 64)])
-def test_wait_that_gives_up_is_reported(no_polls, kind, dtype, n, reads, R):
+def test_wait_that_gives_up_is_reported(wait_error, kind, dtype, n, reads, R):
     """A wait between workgroups that gives up: EHIP from the call itself when it reads out, from the next
     call with the graph otherwise, and the state is NaN; afterwards the graph solves as before."""
     g, ref = _one_launch_case(kind, dtype, n, reads, R)
@@ -1726,7 +1726,7 @@ def test_wait_that_gives_up_is_reported(no_polls, kind, dtype, n, reads, R):
     qh.bsb_solve(g, R, 1000, seed=9, x=x, y=y, readout=False)
     torch.cuda.synchronize()
     assert torch.isnan(x).any() and torch.equal(torch.isnan(x), torch.isnan(y))
-    no_polls.value = 2 ** 27
+    wait_error.value = 0
     with pytest.raises(qh.QhapError) as e:
         qh.bsb_solve(g, R, 1000, init=False, x=x, y=y, step_begin=500, readout=False)
     assert e.value.status == qh.Status.EHIP
@@ -1737,13 +1737,13 @@ def test_wait_that_gives_up_is_reported(no_polls, kind, dtype, n, reads, R):
 
 
 @pytest.mark.parametrize("readout", [True, False])
-def test_batch_wait_that_gives_up_is_reported(team_batch, no_polls, readout):
+def test_batch_wait_that_gives_up_is_reported(team_batch, wait_error, readout):
     """The same for the teams of a batch, which synchronises: EHIP with and without a readout."""
     gs = team_batch[-8:]
     with pytest.raises(qh.QhapError) as e:
         qh.bsb_solve_batched(gs, 32, 500, seed=5, readout=readout)
     assert e.value.status == qh.Status.EHIP and "wait" in str(e.value)
-    no_polls.value = 2 ** 27
+    wait_error.value = 0
     a = qh.bsb_solve_batched(gs, 32, 100, seed=5, plan=1)
     b = qh.bsb_solve_batched(gs, 32, 100, seed=5)
     assert torch.equal(a["best_spins"], b["best_spins"]) and torch.equal(a["best_cut"], b["best_cut"])
