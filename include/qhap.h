@@ -220,11 +220,13 @@ typedef struct {
                             too, where every row tile's stored tiles are consecutive (sorted
                             reads), with plan 1's results.  SNP (skyline) graphs only: 3 = per-row
                             kernel; 4 = band blocks on FMAs (bit-identical to 3); 5 = band
-                            blocks on MFMAs (four columns summed per MFMA: equal to 3-4 up
-                            to FP32 rounding).  Plan 0 on SNP graphs without long-range pairs
-                            runs all steps in one launch with the state on chip where the graph
-                            fits (plan 4's results bit for bit; not on a stream being captured),
-                            and otherwise the faster of 4 and 5, which it times once. */
+                            blocks on MFMAs (bit-identical to 3 and 4).  Plan 0 on SNP graphs
+                            without long-range pairs runs all steps in one launch with the
+                            state on chip where the graph fits (plan 4's results bit for bit;
+                            not on a stream being captured), and otherwise the faster of 4 and 5,
+                            which it times once.  Step ranges (and readout ranges) too short
+                            for one launch to pay, 1 to 7 steps by graph, run per step under
+                            plan 0, with the same results. */
     int32_t replica_tile; /* dense graphs, per-step plan, R >= 64: replicas per workgroup
                             (16, 32 or 64); 0 = the autotuner's choice (plan 0), or
                             the widest that fills the GPU.
@@ -313,7 +315,8 @@ qh_status qh_bsb_solve(const qh_graph *g, const qh_bsb_opts *opts, qh_result *re
  * replicas per workgroup (dense graphs, R >= 64) and the persistent plan where it fits
  * (every candidate gives bit-identical results), or the two band kernels (SNP graphs); the
  * arrays below hold those measurements (0 when not measured).  Graphs that plan 0 runs in one
- * launch (see qh_bsb_opts.plan) are timed all the same, for plan 1 and this report.
+ * launch (see qh_bsb_opts.plan) are timed briefly, for this report; calls that act on the
+ * choice (plan 1, plan 2 without persistent_sync, qh_autotune) then time them in full, once.
  * Host output.
  * The persistent plan synchronises neighbouring workgroups with agent-scope
  * release / acquire on per-workgroup step counters. */
@@ -357,10 +360,10 @@ qh_status qh_autotune(const qh_graph *g, const qh_bsb_opts *opts, qh_bsb_opts *c
  * bit for bit.  R must be 16, 32 or 64; init = 1; the whole schedule; no long-range
  * couplings; each graph at most once per batch.  opts->plan: 1 = one launch per step over
  * work items of every block (a dense row tile, or four band blocks); 2 = one persistent
- * launch with whole blocks per workgroup (longest-processing-time placement); 0 = blocks
- * whose state and couplings fit on chip run all steps in one launch per class (storage x
- * dtype), as teams of workgroups; for the others both plans are timed on this batch (8 steps
- * each) and the faster is cached for this list of graphs and R.
+ * launch with whole blocks per workgroup (longest-processing-time placement); 0 = in schedules
+ * of 24 steps and more, blocks whose state and couplings fit on chip run all steps in one launch
+ * per class (storage x dtype), as teams of workgroups; for the others both plans are timed on this
+ * batch (8 steps each) and the faster is cached for this list of graphs and R.
  * Results are packed: block b's vertices start at vertex_offset[b] (= sum of the
  * previous blocks' n) in best_spins / x / y, and its replicas at b * R in cuts.
  *  best_spins int8 [sum n]; cuts double [n_blocks * R]; best_cut double [n_blocks];
@@ -373,7 +376,7 @@ qh_status qh_autotune(const qh_graph *g, const qh_bsb_opts *opts, qh_bsb_opts *c
  *  plan 0 with use_graph runs plan 1 without tuning for the blocks that are not teams (whose
  *  launches cannot be captured and are enqueued on every call).  eval_every must be 0.  readout = 0
  *  runs the dynamics only (the result arrays other than x and y may then be NULL).
- *  Synchronises the stream. */
+ *  EHIP when a wait between a team's workgroups gave up.  Synchronises the stream. */
 typedef struct {
     int8_t *best_spins;
     double *cuts;

@@ -123,8 +123,8 @@ static int units_variant(int64_t blocks) {
 // columns each, `past` chunks of 16 columns of a block read from memory.  Fitted to measured
 // steps (f16, estimate / measured): 0.9 for a step's barriers and latencies; per band block of
 // a SIMD 0.0195 per MFMA and 0.12; 1.8 for the exchange with neighbours; 0.25 per chunk read from
-// memory.  2,001 SNPs, R = 128: 3.1 / 3.4; 7,768 SNPs, F32, 36 quads wide, R = 128: 5.7 / 5.8;
-// 100,000 SNPs, R = 64: 12.4 / 12.4; 250,000: 27.7 / 25.9.
+// memory.  2,001 SNPs, R = 128: 3.1 / 3.6; 7,768 SNPs, F32, 36 quads wide, R = 128: 5.7 / 5.3;
+// 100,000 SNPs, R = 64: 12.4 / 11.3; 250,000: 27.7 / 26.7.
 double band_step_us(double quads, double past, int64_t blocks, int wpg, int rt, bool strips) {
     const double units = std::max(1.0, (double)blocks / 4.0);      // per SIMD
     const double unit = strips ? quads / 16.0 * ((rt / 16) * 0.04 + 0.02) + 0.2 + past * 0.1
