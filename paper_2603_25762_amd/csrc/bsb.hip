@@ -1464,9 +1464,9 @@ static int default_tile(const qh_graph *g, int R) {
 // Autotuner for plan 0 on dense 16/8-bit graphs: time a short run of each candidate on
 // scratch state -- one fused kernel per step, and the persistent launch -- and keep the
 // faster.  Both compute bit-identical results, so the choice only affects speed.  A warm step
-// or two, then 16 steps (`brief`: two, for the report of a solve that does not act on it): 64 steps
-// twice for each of four to six candidates took as long as a 500-step solve, and candidates that
-// matter differ by far more than 16 steps vary (1,501 reads, F32, R = 64: 14.3, 14.2, 8.6 and 8.2 us;
+// or two, then 16 steps of a per-step kernel or 64 of a persistent launch (`brief`: two, for the report
+// of a solve that does not act on it): 64 steps twice for each of four to six candidates took
+// as long as a 500-step solve, and per-step candidates that matter differ by far more than 16 steps vary (1,501 reads, F32, R = 64: 14.3, 14.2, 8.6 and 8.2 us;
 // between the last two the choice may fall either way).
 static void autotune_dense(const qh_graph *g, SolvePlan &p, const qh_bsb_opts *o, const float *pump, double c0,
                            double a0, bool brief, hipStream_t st) {
@@ -1490,9 +1490,12 @@ static void autotune_dense(const qh_graph *g, SolvePlan &p, const qh_bsb_opts *o
     hipEvent_t e0, e1;
     QH_HIP(hipEventCreate(&e0));
     QH_HIP(hipEventCreate(&e1));
-    float best = 0.0f, best_step = 0.0f;
+    float best_us = 0.0f, best_step = 0.0f;
     bool first = true;
     for (int cand : cands) {
+        // (a persistent launch loads its couplings first: over 16 steps it looked slower than the per-step
+        // kernel on graphs where whole solves take two thirds of the time)
+        const int nc = cand > 0 || brief ? nt : std::min(o->steps, 64);
         if (cand > 0) {
             p.run_rt = cand == 65 ? 64 : cand;
             p.run_depth = cand == 65 ? 4 : 2;
@@ -1502,7 +1505,7 @@ static void autotune_dense(const qh_graph *g, SolvePlan &p, const qh_bsb_opts *o
         QH_CHECK_LAUNCH();
         if (!x_pingpong(g)) x_to_h(g, p, n, R, o->variant == 1, st);
         for (int rep = 0; rep < 2; ++rep) {   // the first repetition warms caches and code
-            const int ns = rep ? nt : std::min(nt, 2);
+            const int ns = rep ? nc : std::min(nc, 2);
             QH_HIP(hipEventRecord(e0, st));
             if (cand > 0) run_steps(g, p, o, pump, c0, a0, 0, ns, st);
             else run_persistent(g, p, pump, c0, o->dt, a0, 0, ns, o->variant == 1, o->field, cand < 0, st);
@@ -1510,18 +1513,21 @@ static void autotune_dense(const qh_graph *g, SolvePlan &p, const qh_bsb_opts *o
         }
         QH_HIP(hipEventSynchronize(e1));
         QH_HIP(hipEventElapsedTime(&ms, e0, e1));
-        if (cand > 0 && (best_step == 0.0f || ms < best_step)) {
-            best_step = ms;
+        const float us = ms * 1000.0f / nc;
+        if (cand > 0 && (best_step == 0.0f || us < best_step)) {
+            best_step = us;
             p.tuned_rt = p.run_rt;
             p.tuned_depth = p.run_depth;
-            p.tuned_us[0] = ms * 1000.0f / nt;
+            p.tuned_us[0] = us;
         }
-        if (cand == 0) p.tuned_us[1] = ms * 1000.0f / nt;
-        if (cand < 0) p.tuned_us_coh = ms * 1000.0f / nt;
-        if (first || ms < best) {
-            best = ms;
+        if (cand == 0) p.tuned_us[1] = us;
+        if (cand < 0) {
+            p.tuned_us_coh = us;
+            p.tuned_coh = us < p.tuned_us[1];
+        }
+        if (first || us < best_us) {
+            best_us = us;
             p.tuned_plan = cand > 0 ? 1 : 2;
-            if (cand <= 0) p.tuned_coh = cand < 0;
         }
         first = false;
     }

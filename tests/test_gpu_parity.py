@@ -1775,8 +1775,7 @@ def test_choice_of_plans_after_a_one_launch_solve():
     g = solved(wm, 64)
     qh.bsb_solve(g, 64, 100, seed=3, plan=2)
     info = timed(g, 64)
-    assert info["persistent_sync"] == (2 if info["us_persistent_coherent"] < info["us_per_step"][1] else 1) or \
-        info["us_per_step"][0] < min(info["us_per_step"][1], info["us_persistent_coherent"])
+    assert info["persistent_sync"] == (2 if info["us_persistent_coherent"] < info["us_per_step"][1] else 1)
     g = solved(wm, 64)
     qh.bsb_solve(g, 64, 100, seed=3, plan=1)
     timed(g, 64)
@@ -2036,3 +2035,25 @@ def test_plan_info_of_the_last_solve():
     assert one["replicas_per_group"] * one["groups"] == 64
     assert (one["workgroups_per_group"], one["lds_bytes"]) != (p2["workgroups_per_group"], p2["lds_bytes"])
     assert info(1)["plan_used"] == 1
+
+
+def test_autotune_picks_a_plan_that_is_fast_over_a_whole_solve():
+    """The persistent plan loads the couplings before its first step; the tuner's few steps must not make it
+    look slower than the per-step kernel where a whole solve is 1.6 times as fast (1,500 reads, F16, R = 64:
+    3.1 against 5.1 ms per 1,000 steps).  The choice may be at most a quarter slower than the other plan."""
+    g = gpu_graph(synth.read_small(9, 2250, 1500, (20, 60)), "read_signed", "f16")
+    ch = qh.autotune(g, 64, 1000)
+
+    def ms(**opts):
+        ts = []
+        for _ in range(4):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            qh.bsb_solve(g, 64, 1000, seed=3, readout=False, **opts)
+            e1.record()
+            e1.synchronize()
+            ts.append(e0.elapsed_time(e1))
+        return min(ts)
+
+    opts = {k: ch[k] for k in ("plan", "replica_tile", "tiles_in_flight", "persistent_sync")}
+    assert ms(**opts) <= 1.25 * min(ms(plan=1), ms(plan=2))
