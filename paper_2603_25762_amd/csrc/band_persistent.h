@@ -85,7 +85,7 @@ struct BandPersist {
     BandLaunch launch;
     int passes = 0;             // most jobs of one workgroup
     int min_steps = 0;          // a shorter range is faster in per-step launches
-    bool gaps = false;          // dense graphs: some row tile's stored tiles are not consecutive
+    bool gaps = false;          // dense graphs: some row tile's stored tiles are none, or not consecutive
     DevBuf<BandTeam> team;
     DevBuf<int64_t> off;        // dense graphs: the strips as band blocks
     DevBuf<int32_t> lo, w;

@@ -101,7 +101,7 @@ static bool strips_of(const qh_graph *g, std::vector<int64_t> &off, std::vector<
         const int32_t t0 = tptr[rt], t1 = tptr[rt + 1];
         const int32_t c0 = t1 > t0 ? tcol[t0] : (int32_t)rt, nt = t1 > t0 ? tcol[t1 - 1] - c0 + 1 : 1;
         if (nt > 64) return false;
-        if (t1 > t0 && nt != t1 - t0) gaps = true;
+        gaps |= nt != t1 - t0;                 // (a row tile without stored tiles multiplies its own rows by 0)
         uint64_t m = 0;
         for (int32_t t = t0; t < t1; ++t) m |= 1ull << (tcol[t] - c0);
         for (int s = 0; s < kTile / kBandRows; ++s) {

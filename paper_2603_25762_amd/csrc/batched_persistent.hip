@@ -37,7 +37,7 @@ __global__ __launch_bounds__(256) void k_batch_geometry(const GeomDesc *__restri
         uint64_t m = 0;
         if (nt <= 64)
             for (int32_t t = t0; t < t1; ++t) m |= 1ull << (g.p1[t] - c0);
-        gaps |= t1 > t0 && nt != t1 - t0;
+        gaps |= nt != t1 - t0;
         for (int s = 0; s < S; ++s) {
             const int64_t e = g.at + i * S + s;
             off[e] = ((int64_t)t0 * kTileElems + s * (kTileElems / S)) * g.eb;

@@ -2057,3 +2057,32 @@ def test_autotune_picks_a_plan_that_is_fast_over_a_whole_solve():
 
     opts = {k: ch[k] for k in ("plan", "replica_tile", "tiles_in_flight", "persistent_sync")}
     assert ms(**opts) <= 1.25 * min(ms(plan=1), ms(plan=2))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16", "fp8"])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_non_finite_state_in_a_row_tile_without_couplings(dtype, bad):
+    """A caller's state with one non-finite value among 64 reads that share no SNP with any other: it stays in
+    its row (no tile of theirs is stored), under plan 0 as in the per-step kernels."""
+    w = synth.read_small(6, 400, 200, (20, 60))
+    lone = np.arange(128, dtype=np.int32)
+    w.frag_ptr = np.concatenate([2 * np.arange(64), 128 + w.frag_ptr]).astype(np.int64)
+    w.snp = np.concatenate([lone, w.snp + 128]).astype(np.int32)
+    w.allele = np.concatenate([lone % 2, w.allele]).astype(w.allele.dtype)
+    w.phred = np.concatenate([np.full(128, 30), w.phred]).astype(np.uint8)
+    w.init_h1 = np.concatenate([np.zeros(128), w.init_h1]).astype(w.init_h1.dtype)
+    w.alpha = np.ones(264)
+    d = device_reads(w)
+    g = qh.build_graph(d["frag_ptr"], d["snp"], d["allele"], d["phred"], d["init_h1"], kind="read_signed", dtype=dtype)
+    assert g.info()["n"] == 264
+    rng = np.random.default_rng(3)
+    x0 = torch.tensor(rng.uniform(-0.5, 0.5, (264, 64)), dtype=torch.float32, device="cuda")
+    x0[5, 3] = bad
+    out = []
+    for plan in (1, 0):
+        x, y = x0.clone(), torch.zeros_like(x0)
+        qh.bsb_solve(g, 64, 40, init=False, x=x, y=y, step_end=20, plan=plan, readout=False)
+        out.append((x, y))
+    assert torch.isfinite(out[0][1][6:64]).all()
+    for a, b in zip(*out):
+        assert torch.equal(a.isnan(), b.isnan()) and torch.equal(a.nan_to_num(7.0), b.nan_to_num(7.0))
